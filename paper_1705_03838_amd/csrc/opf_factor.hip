@@ -19,129 +19,142 @@ __device__ inline double wave_max(double v) {
     return v;
 }
 
-// Twisted elimination of the band held in T (N = NB rows, offsets -8..+4)
-// and the twisted substitution image (layout and scaling as described at
-// solve_twisted): columns 0..h-1 top-down (lane t updates row j+1+t/4,
-// column j+1+t%4), columns NB-1..h+4 bottom-up (lane t updates row
-// j-1-t/8, column j-8+t%8), both without pivoting; the multipliers replace
-// the eliminated entries.  The middle block is inverted by Gauss-Jordan with
-// row pivoting.  Called by all 64 lanes.
-__device__ void twisted_image(const FactorArgs& a, double* T, double* G, double* Dv, double amax, int& bad) {
-    const int N = a.N, NB = a.NB, h = tw_h(NB), n = threadIdx.x;
-    for (int j = 0; j < h; ++j) {
-        const double piv = T[j * BW + 8];
-        if (!(fabs(piv) > 1e-14 * amax)) bad = bad ? bad : 2;
-        const int i = j + 1 + (n & 31) / 4, col = j + 1 + (n & 3);
-        if (n < 32 && i < N) {
-            const double l = T[i * BW + (j - i + 8)] / piv;
-            if (col < N && col - i >= -8) T[i * BW + (col - i + 8)] -= l * T[j * BW + (col - j + 8)];
-            if ((n & 3) == 0) T[i * BW + (j - i + 8)] = l;
-        }
-        __syncthreads();
-    }
-    for (int j = N - 1; j >= h + 4; --j) {
-        const double piv = T[j * BW + 8];
-        if (!(fabs(piv) > 1e-14 * amax)) bad = bad ? bad : 2;
-        const int i = j - 1 - (n & 31) / 8, col = j - 8 + (n & 7);
-        if (n < 32 && i >= 0) {
-            const double u = T[i * BW + (j - i + 8)] / piv;
-            if (col >= 0) T[i * BW + (col - i + 8)] -= u * T[j * BW + (col - j + 8)];
-            if ((n & 7) == 0) T[i * BW + (j - i + 8)] = u;
-        }
-        __syncthreads();
-    }
-    // element growth of the eliminated rows (the multipliers left out: the
-    // bottom-up ones against the identity wall row are the wall stencil's
-    // entries themselves, large by construction and exact)
-    double g = 0.0;
-    if (n < N) {
-        const int lo = n < h ? n : (n < h + 4 ? h : max(n - 8, 0)), hi = n < h ? n + 4 : (n < h + 4 ? h + 3 : n);
-        for (int c = lo; c <= hi && c < N; ++c) g = fmax(g, fabs(T[n * BW + (c - n + 8)]));
-    }
-    if (wave_max(g) > 1e3 * amax) bad = bad ? bad : 3;
-    auto sv = [&](int i) { return i >= h && i < h + 4 ? 1.0 : 1.0 / T[i * BW + 8]; };
-    if (n == 0) {
-        double m[4][8];
-        for (int r = 0; r < 4; ++r)
-            for (int c = 0; c < 4; ++c) {
-                m[r][c] = T[(h + r) * BW + (c - r + 8)];
-                m[r][4 + c] = r == c ? 1.0 : 0.0;
-            }
-        for (int c = 0; c < 4; ++c) {
-            int pr = c;
-            for (int r = c + 1; r < 4; ++r)
-                if (fabs(m[r][c]) > fabs(m[pr][c])) pr = r;
-            if (!(fabs(m[pr][c]) > 1e-14 * amax)) bad = bad ? bad : 2;
-            if (pr != c)
-                for (int e = 0; e < 8; ++e) {
-                    const double x = m[c][e];
-                    m[c][e] = m[pr][e];
-                    m[pr][e] = x;
-                }
-            const double inv = 1.0 / m[c][c];
-            for (int e = 0; e < 8; ++e) m[c][e] *= inv;
-            for (int r = 0; r < 4; ++r)
-                if (r != c) {
-                    const double f = m[r][c];
-                    for (int e = 0; e < 8; ++e) m[r][e] -= f * m[c][e];
-                }
-        }
-        for (int r = 0; r < 4; ++r)
-            for (int c = 0; c < 4; ++c) G[tw_mi(NB) + 4 * r + c] = m[r][4 + c];
-    }
-    if (n < h) {
-        const int t = n, j = NB - 1 - t;
-        for (int d = 0; d < 4; ++d) {
-            const int i = t + 1 + d, ib = j - 1 - d;
-            G[4 * t + d] = sv(i) * T[i * BW + (t - i + 8)] * T[t * BW + 8];
-            G[tw_p1b(NB) + 4 * t + d] = sv(ib) * T[ib * BW + (j - ib + 8)] * T[j * BW + 8];
-        }
-    }
-    if (n < 4) G[tw_z4(NB) + n] = 0.0;
-    if (n < h + 4) {
-        const int t = n, ja = h + 3 - t, jb = h + t;
-        for (int d = 0; d < 4; ++d) {
-            const int i = ja - 1 - d;
-            G[tw_p3a(NB) + 4 * t + d] = i >= 0 && i < h ? T[i * BW + (ja - i + 8)] * sv(i) : 0.0;
-        }
-        double* g = G + tw_p3b_rec(NB, t);
-        for (int d = 0; d < (tw_wide(NB, t) ? 8 : 4); ++d) {
-            const int i = jb + 1 + d;
-            g[d] = i >= h + 4 && i < NB ? T[i * BW + (jb - i + 8)] * sv(i) : 0.0;
-        }
-    }
-    if (n < NB) Dv[n] = sv(n);
+// Unevaluated sums of two doubles (Dekker 1971; products by multiply-add):
+// about 106 bits.
+struct dd {
+    double hi, lo;
+};
+__device__ inline dd two_sum(double a, double b) {
+    const double s = a + b, t = s - a;
+    return {s, (a - (s - t)) + (b - t)};
+}
+__device__ inline dd renorm(double a, double b) {  // |a| >= |b|
+    const double s = a + b;
+    return {s, b - (s - a)};
+}
+__device__ inline dd operator-(dd a) { return {-a.hi, -a.lo}; }
+__device__ inline dd operator+(dd a, dd b) {
+    const dd s = two_sum(a.hi, b.hi), t = two_sum(a.lo, b.lo);
+    const dd u = renorm(s.hi, s.lo + t.hi);
+    return renorm(u.hi, u.lo + t.lo);
+}
+__device__ inline dd operator*(dd a, dd b) {
+    const double p = a.hi * b.hi;
+    return renorm(p, fma(a.hi, b.hi, -p) + (a.hi * b.lo + a.lo * b.hi));
 }
 
-// One system per 64-thread workgroup.  System q < MU K is H_{mu,|k|} with
+// LDS of one block elimination, entry [r][c] of a block at 8 r + c.
+struct BlockLds {
+    dd d[64], inv[64], gc[64];
+    double x[64];
+};
+
+// Inverse of the n x n matrix (n = 4 or 8) in w.d, entry [r][c] returned in
+// lane 8 r + c as a pair: Gauss-Jordan elimination in double precision (the
+// pivots are those of the operator's LU factors, which the caller checks), then
+// one Newton step X + X (I - D X) with the residual in pairs.  Called by all
+// 64 lanes of one wave; bad is set where a pivot is zero or not finite.
+__device__ dd small_inverse(BlockLds& w, int n, int lane, int& bad) {
+    const int r = lane >> 3, c = lane & 7;
+    double m = w.d[lane].hi, v = r == c ? 1.0 : 0.0;
+    for (int q = 0; q < n; ++q) {
+        const double piv = __shfl(m, 9 * q), f = __shfl(m, 8 * r + q);
+        if (!(fabs(piv) > 0.0) || isinf(piv)) bad = bad ? bad : 2;
+        const double ip = 1.0 / piv, rm = __shfl(m, 8 * q + c) * ip, rv = __shfl(v, 8 * q + c) * ip;
+        m = r == q ? rm : m - f * rm;
+        v = r == q ? rv : v - f * rv;
+    }
+    w.x[lane] = v;
+    __builtin_amdgcn_wave_barrier();
+    dd e = {r == c ? 1.0 : 0.0, 0.0};
+    for (int k = 0; k < n; ++k) e = e + -(w.d[8 * r + k] * dd{w.x[8 * k + c], 0.0});
+    __builtin_amdgcn_wave_barrier();
+    w.gc[lane] = e;
+    __builtin_amdgcn_wave_barrier();
+    double s = 0.0;
+    for (int k = 0; k < n; ++k) s += w.x[8 * r + k] * w.gc[8 * k + c].hi;
+    __builtin_amdgcn_wave_barrier();
+    return two_sum(v, s);
+}
+
+// The image of the operator L - shift whose band rows (of L; the wall row is
+// the identity's) are in T, offsets -8..+4: the block elimination described
+// at btd_nt.  It runs on pairs of doubles, so that the inverse blocks are
+// right to about a unit in the last place: their errors act on every step in
+// the same way, and in plain double precision they made the state drift twice
+// as fast as a banded LU's (2.4e-15 against 1.2e-15 of the state after 16
+// steps of the 64 x 48 x 127-mode grid).  Called by all 64 lanes of one wave.
+__device__ void block_image(const FactorArgs& a, const double* T, double shift, double* G, BlockLds& w, int lane, int& bad) {
+    const int N = a.N, nt = a.nt, pad = btd_rows(nt) - N, r = lane >> 3, c = lane & 7;
+    auto at = [&](int row, int col) {  // padded row and column; padding rows are rows of the identity
+        const int n = row - pad, k = col - pad;
+        if (n < 0 || k < 0) return row == col ? 1.0 : 0.0;
+        const int off = k - n;
+        return n < N && k < N && off >= -8 && off <= 4 ? T[n * BW + off + 8] : 0.0;
+    };
+    auto at_image = [](int tile, int i, int k) { return 32 * (tile >> 1) + 2 * (4 * k + i) + (tile & 1); };
+    for (int I = 0; I <= nt; ++I) {
+        const int n = I < nt ? 4 : 8, r0 = 4 * I;
+        dd d = {r < n && c < n ? at(r0 + r, r0 + c) : (r == c ? 1.0 : 0.0), 0.0};
+        if (r == c && r < n && r0 + r >= pad && r0 + r < pad + N - 1) d = two_sum(d.hi, -shift);
+        if (I > 0) {
+            // D_{I-1}^{-1} C_{I-1}; C reaches the first four columns of block I only
+            dd s = {0.0, 0.0};
+            if (r < 4 && c < 4)
+                for (int k = 0; k < 4; ++k) s = s + w.inv[8 * r + k] * dd{at(r0 - 4 + k, r0 + c), 0.0};
+            w.gc[lane] = s;
+            __builtin_amdgcn_wave_barrier();
+            if (r < n && c < 4)
+                for (int k = 0; k < 4; ++k) d = d + dd{-at(r0 + r, r0 - 4 + k), 0.0} * w.gc[8 * k + c];
+            __builtin_amdgcn_wave_barrier();
+        }
+        w.d[lane] = d;
+        __builtin_amdgcn_wave_barrier();
+        const dd v = small_inverse(w, n, lane, bad);
+        w.inv[lane] = v;
+        __builtin_amdgcn_wave_barrier();
+        if (I < nt) {
+            if (r < 4 && c < 4) G[at_image(I, r, c)] = v.hi;
+        } else {
+            G[at_image(nt + 2 * (r >> 2) + (c >> 2), r & 3, c & 3)] = v.hi;
+        }
+    }
+}
+
+// One system per workgroup of two waves.  System q < MU K is H_{mu,|k|} with
 // mu = q / K, |k| = q % K; q >= MU K is the pressure operator L_{m,|k|},
 // m = mp (q - MU K) / K, with P(1) = 0 (the unused (0,0) record gets
-// 1/U = 1).  The band (rows in LDS) is eliminated without pivoting, one
-// column per pass (8 rows x 4 columns of updates in parallel), then written
-// as column records: main record i holds L[i+1..i+4][i], U[i-1..i-4][i] and
-// 1/U_ii, tail record i holds L[i+5..i+8][i].  flags[q]: 0 ok, 1 entry outside the band, 2 pivot below
+// 1/U = 1, its image zeros).  Wave 1 makes the image; wave 0 eliminates the
+// band (rows in LDS) without pivoting, one column per pass (8 rows x 4 columns
+// of updates in parallel), and writes it as column records: main record i
+// holds L[i+1..i+4][i], U[i-1..i-4][i] and 1/U_ii, tail record i holds
+// L[i+5..i+8][i].  flags[q]: 0 ok, 1 entry outside the band, 2 pivot below
 // 1e-14 max|A|, 3 element growth (|U| > 1e3 max|A| or |L| > 1e3).
-__global__ __launch_bounds__(64) void k_factor(FactorArgs a, int first) {
+__global__ __launch_bounds__(128) void k_factor(FactorArgs a, int first) {
     __shared__ double B[NMAX * BW];
-    __shared__ double T[NMAX * BW];  // the band again, for the twisted elimination
+    __shared__ double T[NMAX * BW];  // the band of L, as the block elimination takes it
+    __shared__ BlockLds blk;
+    __shared__ int image_bad;
     const int q = first + blockIdx.x;
-    const int N = a.N, n = threadIdx.x;
+    const int N = a.N, n = threadIdx.x & 63;
+    const bool lu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;
     const bool helm = q < a.MU * a.K;
     const int mu = helm ? q / a.K : a.mp * ((q - a.MU * a.K) / a.K);
     const int ka = helm ? q % a.K : (q - a.MU * a.K) % a.K;
     double* F = a.fac + (size_t)q * N * FACW;
-    // substitution image of this operator: [|k|][mu] (Helmholtz), [|k|][m] (pressure)
-    const int FW = solve_image_doubles(a.NB, a.NW), FWD = solve_image_fwd(a.NB, a.NW);
+    // image of this operator: [|k|][mu] (Helmholtz), [|k|][m] (pressure)
+    const int FW = btd_image(a.nt);
     const size_t iq = helm ? (size_t)ka * a.MU + mu : (size_t)a.MU * a.K + (size_t)ka * a.M + (q - a.MU * a.K) / a.K;
     double* G = a.img + iq * FW;
-    double* Dv = a.dinv + iq * a.NB;
     if (!helm && mu == 0 && ka == 0) {
+        if (!lu) {
+            for (int e = n; e < FW; e += 64) G[e] = 0.0;
+            return;
+        }
         if (n < N) {
             for (int d = 0; d < FMAIN; ++d) F[(size_t)n * FMAIN + d] = d == 8 ? 1.0 : 0.0;
             for (int d = 0; d < FTAIL; ++d) F[(size_t)N * FMAIN + (size_t)n * FTAIL + d] = 0.0;
         }
-        for (int e = n; e < FW; e += 64) G[e] = 0.0;
-        if (n < a.NB) Dv[n] = 0.0;
         if (n == 0) a.flags[q] = 0;
         return;
     }
@@ -149,10 +162,11 @@ __global__ __launch_bounds__(64) void k_factor(FactorArgs a, int first) {
     const int par = mu & 1;
     int bad = 0;
     double amax = 0.0;
+    double* band = lu ? B : T;
     if (n < N) {
-        for (int d = 0; d < BW; ++d) B[n * BW + d] = 0.0;
+        for (int d = 0; d < BW; ++d) band[n * BW + d] = 0.0;
         if (n == N - 1) {
-            B[n * BW + 8] = 1.0;  // wall row: the boundary value
+            band[n * BW + 8] = 1.0;  // wall row: the boundary value
             amax = 1.0;
         } else {
             const int s = a.s0[n];
@@ -161,7 +175,7 @@ __global__ __launch_bounds__(64) void k_factor(FactorArgs a, int first) {
                 const int col = s + j;
                 double v = a.d2[(par * N + n) * W9 + j] + ri * a.d1[(par * N + n) * W9 + j];
                 if (col == n) v -= double(mu) * mu * ri * ri + kap * kap;
-                if (helm) {
+                if (helm && lu) {
                     v = -a.cr * v;
                     if (col == n) v += a.inv_dt;
                 }
@@ -169,20 +183,21 @@ __global__ __launch_bounds__(64) void k_factor(FactorArgs a, int first) {
                 if (off < -8 || off > 4) {
                     if (v != 0.0) bad = 1;
                 } else {
-                    B[n * BW + off + 8] = v;
+                    band[n * BW + off + 8] = v;
                 }
                 amax = fmax(amax, fabs(v));
             }
         }
     }
-    amax = wave_max(amax);
-    __syncthreads();
-    const bool tw = solve_twisted(a.NB, a.NW);
-    if (tw) {
-        for (int e = n; e < N * BW; e += 64) T[e] = B[e];
-        if (N != a.NB) bad = 1;  // the twisted images assume N = NB
+    __builtin_amdgcn_wave_barrier();
+    if (!lu) {
+        block_image(a, T, helm ? a.shift : 0.0, G, blk, n, bad);
+        for (int o = 32; o > 0; o >>= 1) bad = max(bad, __shfl_xor(bad, o));
+        if (n == 0) image_bad = bad;
+        __syncthreads();
+        return;
     }
-    __syncthreads();
+    amax = wave_max(amax);
     // elimination: lane t updates row j+1+t/4, column j+1+t%4
     const int ti = 1 + (n & 31) / 4, tc = 1 + (n & 3);
     for (int j = 0; j < N; ++j) {
@@ -192,9 +207,10 @@ __global__ __launch_bounds__(64) void k_factor(FactorArgs a, int first) {
         if (n < 32 && i < N) {
             const double l = B[i * BW + (j - i + 8)] / piv;
             if (col < N && col - i >= -8) B[i * BW + (col - i + 8)] -= l * B[j * BW + (col - j + 8)];
+            __builtin_amdgcn_wave_barrier();  // every lane has read its multiplier's entry
             if (tc == 1) B[i * BW + (j - i + 8)] = l;
         }
-        __syncthreads();
+        __builtin_amdgcn_wave_barrier();
     }
     double umax = 0.0, lmax = 0.0;
     if (n < N)
@@ -217,24 +233,11 @@ __global__ __launch_bounds__(64) void k_factor(FactorArgs a, int first) {
         f[8] = 1.0 / B[n * BW + 8];
         f[9] = 0.0;
     }
-    // image: Lh[n+d][n] = L[n+d][n] U_nn / U_{n+d,n+d}, W[n-d][n] = U[n-d][n] / U_{n-d,n-d}
-    if (tw) {
-        twisted_image(a, T, G, Dv, amax, bad);
-    } else if (n < a.NB) {
-        const int nd = n < a.NW ? 4 : 8;
-        double* g = G + (n < a.NW ? 4 * n : 4 * a.NW + 8 * (n - a.NW));
-        for (int d = 1; d <= nd; ++d)
-            g[d - 1] = n < N && n + d < N ? B[(n + d) * BW + (8 - d)] * B[n * BW + 8] / B[(n + d) * BW + 8] : 0.0;
-        if (n >= 1) {
-            double* gb = G + FWD + 4 * (n - 1);
-            for (int d = 1; d <= 4; ++d)
-                gb[d - 1] = n < N && n - d >= 0 ? B[(n - d) * BW + (8 + d)] / B[(n - d) * BW + 8] : 0.0;
-        }
-        Dv[n] = n < N ? 1.0 / B[n * BW + 8] : 0.0;
-    }
     // the band check is per row: any lane's flag marks the system
     for (int o = 32; o > 0; o >>= 1) bad = max(bad, __shfl_xor(bad, o));
     if (bad == 0 && (umax > 1e3 * amax || lmax > 1e3)) bad = 3;
+    __syncthreads();
+    if (bad == 0) bad = image_bad;
     if (n == 0) a.flags[q] = bad;
 }
 
@@ -419,7 +422,7 @@ __global__ __launch_bounds__(64) void k_green(FactorArgs a, double* qg) {
 
 hipError_t launch_operator_tables(const FactorArgs& a, bool pressure, hipStream_t s) {
     const int nh = a.MU * a.K, np = a.M * a.K;
-    hipLaunchKernelGGL(k_factor, dim3(pressure ? nh + np : nh), dim3(64), 0, s, a, 0);
+    hipLaunchKernelGGL(k_factor, dim3(pressure ? nh + np : nh), dim3(128), 0, s, a, 0);
     hipError_t he = hipGetLastError();
     if (he != hipSuccess) return he;
     if (pressure) {

@@ -24,7 +24,6 @@ struct opf_ctx {
     std::vector<int> s0;
     int nk = 0, MU = 0, nfac = 0, gm = 1;
     int tz = DEFAULT_TZ, ztile = DEFAULT_ZTILE;  // transform tile shapes
-    int narrow = 0;  // see SolveArgs::narrow
     double qG_inv = 0.0;
     hipStream_t stream = nullptr;
     hipStream_t cap = nullptr;
@@ -186,15 +185,6 @@ void build_grid(opf_ctx* c, const double* r_nodes) {
             }
         }
     }
-    // Row i of every radial operator is zero left of column s0[i] (the wall
-    // row is the identity), and LU without pivoting fills nothing left of a
-    // row's first nonzero.  So L[i][j] != 0 with i > j + 4 needs a row with
-    // s0[i] <= j <= i - 5, and columns before the smallest such s0[i] have at
-    // most four nonzero entries below the diagonal.
-    c->narrow = N;
-    for (int i = 0; i < N - 1; ++i)
-        if (c->s0[i] <= i - 5) c->narrow = std::min(c->narrow, c->s0[i]);
-
     // quadrature: exact integral of each interval's stencil interpolant times r
     {
         std::vector<double> gx, gw;
@@ -220,7 +210,7 @@ void build_grid(opf_ctx* c, const double* r_nodes) {
 }
 
 struct Layout {
-    size_t r, rinv, quad, d1, d2, wl, s0, fac, img, dinv, hom, ainv, green, flags, qg, wall, twz, twt;
+    size_t r, rinv, quad, d1, d2, wl, s0, fac, img, coup, hom, ainv, green, flags, qg, wall, twz, twt;
     size_t u, up, w64, w, Nn, Np, H, G, u32, up32, beta, partial, dpart, cflw, cpart, total;
 };
 
@@ -241,9 +231,9 @@ Layout layout(const opf_params& p) {
     L.wl = take(2 * N * W9 * 8);
     L.s0 = take(N * 4);
     L.fac = take(nfac * N * FACW * 8);
-    // substitution images at the largest size (no narrow rows)
-    L.img = take(nfac * solve_image_doubles(solve_nb((int)N), 0) * 8);
-    L.dinv = take(nfac * solve_nb((int)N) * 8);
+    const int nt = btd_nt((int)N);
+    L.img = take(nfac * btd_image(nt) * 8);
+    L.coup = take(btd_coupling(nt) * 8);
     L.hom = take(M * K * NHOM * N * 8);
     L.ainv = take(M * nk * 16 * 16);
     L.green = take(N * 8);
@@ -467,6 +457,28 @@ NLArgs nl_args(const opf_ctx* c, const void* u, const void* w, void* out) {
     return a;
 }
 
+// The scale of the Helmholtz systems, Re / c, and the shift Re / (c dt) of the
+// scaled operator.  Steps multiply the state by scale / (dt shift), which has
+// to be 1: of the doubles within four units in the last place of Re / c the
+// one whose product with 1/dt rounds least is taken.
+void helmholtz_scale(const opf_params& p, double* scale, double* shift) {
+    const double inv_dt = 1.0 / p.dt, mid = p.Re / p.c;
+    double h = mid, best = INFINITY;
+    for (int j = 0; j < 4; ++j) h = std::nextafter(h, 0.0);
+    for (int j = 0; j < 9; ++j, h = std::nextafter(h, INFINITY)) {
+        const double k = h * inv_dt, err = std::fabs(std::fma(h, inv_dt, -k)) / k;
+        if (err < best) {
+            best = err;
+            *scale = h;
+            *shift = k;
+        }
+    }
+    if (!(best < INFINITY)) {
+        *scale = mid;
+        *shift = mid * inv_dt;
+    }
+}
+
 SolveArgs solve_args(const opf_ctx* c, int kind) {
     SolveArgs a{};
     a.N = c->p.N;
@@ -476,7 +488,6 @@ SolveArgs solve_args(const opf_ctx* c, int kind) {
     a.mp = c->p.mp;
     a.MU = c->MU;
     a.gm = c->gm;
-    a.narrow = c->narrow;
     a.kind = kind;
     a.fixed_flux = c->p.fixed_flux;
     a.alpha = c->p.alpha;
@@ -485,6 +496,9 @@ SolveArgs solve_args(const opf_ctx* c, int kind) {
     a.inv_dt = 1.0 / c->p.dt;
     a.aexp = (1.0 - c->p.c) / c->p.Re;
     a.force = 4.0 / c->p.Re;
+    double shift = 0.0;
+    helmholtz_scale(c->p, &a.hscale, &shift);
+    a.hscale = -a.hscale;
     a.beta_out = c->beta;
     a.wall = c->has_wall ? c->wall : nullptr;
     a.t = c->t;
@@ -514,9 +528,9 @@ opf_status device_tables(opf_ctx* c, bool pressure) {
     a.s0 = c->t.s0;
     a.fac = reinterpret_cast<double*>(c->ws + Lo.fac);
     a.img = reinterpret_cast<double*>(c->ws + Lo.img);
-    a.dinv = reinterpret_cast<double*>(c->ws + Lo.dinv);
-    a.NB = solve_nb(p.N);
-    a.NW = solve_nw(p.N, c->narrow);
+    a.nt = btd_nt(p.N);
+    double scale = 0.0;
+    helmholtz_scale(p, &scale, &a.shift);
     a.hom = reinterpret_cast<double*>(c->ws + Lo.hom);
     a.ainv = reinterpret_cast<double*>(c->ws + Lo.ainv);
     a.green = reinterpret_cast<double*>(c->ws + Lo.green);
@@ -725,7 +739,7 @@ opf_status opf_create(const opf_params* p, void* dev_workspace, size_t bytes, vo
     c->nk = nk;
     c->MU = p->mp * (M - 1) + 2;
     c->nfac = c->MU * K + M * K;
-    c->gm = default_gm(p->mp);
+    c->gm = context_gm(p->mp, M, K);
     c->ztile = default_ztile(p->precision);
 
     build_grid(c, p->r_nodes);
@@ -769,6 +783,26 @@ opf_status opf_create(const opf_params* p, void* dev_workspace, size_t bytes, vo
                 wl[i] = c->d2[i] + c->rinv[n] * c->d1[i];
             }
     if (he == hipSuccess) he = up(Lo.wl, wl.data(), wl.size() * 8);
+    // coupling tiles of the block form (see btd_nt), signs as the solve uses them
+    const int nt = btd_nt(N), pad = btd_rows(nt) - N;
+    std::vector<double> coup(btd_coupling(nt), 0.0);
+    auto coupling = [&](int at, int q, int par) {  // -B_{q+1} (q < nt), the last block's second half (q == nt), then -C
+        const bool sub = q <= nt;
+        const int rb = sub ? 4 * (q + 1) : 4 * (q - nt - 1), cb = sub ? 4 * std::min(q, nt - 1) : rb + 4;
+        for (int i = 0; i < 4; ++i)
+            for (int k = 0; k < 4; ++k) {
+                const int n = rb + i - pad, col = cb + k - pad;
+                if (n < 0 || col < 0 || n >= N - 1 || col < c->s0[n] || col >= c->s0[n] + W9) continue;
+                coup[16 * at + 4 * k + i] = -wl[((size_t)par * N + n) * W9 + col - c->s0[n]];
+            }
+    };
+    for (int q = 0; q < 2 * nt + 1; ++q) coupling(q, q, 0);
+    for (int par = 0; par < 2; ++par)
+        for (int j = 0; j < 2; ++j) {
+            coupling(2 * nt + 1 + 4 * par + j, j, par);
+            coupling(2 * nt + 1 + 4 * par + 2 + j, nt + 1 + j, par);
+        }
+    if (he == hipSuccess) he = up(Lo.coup, coup.data(), coup.size() * 8);
     // CFL weights: 1/dr_n (nearer neighbour; the axis mirror -r_0 for n = 0) and 1/(r_n dtheta)
     std::vector<double> cflw(2 * N);
     for (int n = 0; n < N; ++n) {
@@ -794,7 +828,7 @@ opf_status opf_create(const opf_params* p, void* dev_workspace, size_t bytes, vo
     c->t.s0 = reinterpret_cast<const int*>(ws + Lo.s0);
     c->t.fac = reinterpret_cast<const double*>(ws + Lo.fac);
     c->t.img = reinterpret_cast<const double*>(ws + Lo.img);
-    c->t.dinv = reinterpret_cast<const double*>(ws + Lo.dinv);
+    c->t.coup = reinterpret_cast<const double*>(ws + Lo.coup);
     c->t.wl = reinterpret_cast<const double*>(ws + Lo.wl);
     c->t.hom = reinterpret_cast<const double*>(ws + Lo.hom);
     c->t.ainv = reinterpret_cast<const double*>(ws + Lo.ainv);

@@ -23,62 +23,34 @@ constexpr int FACW = 14;  // doubles per LU factor row: 8 of L, 4 of U, 1/U_ii, 
 constexpr int FMAIN = 10;
 constexpr int FTAIL = 4;
 constexpr int NHOM = 7;   // real radial lines of influence data per (m,|k|)
-// Substitution images of the LU factors (see solve_image_doubles): with
-// A = L U = L D W (D = diag U, W unit upper), A x = b is solved as
-// (D^-1 L D) y = D^-1 b, then W x = y.  Per operator, padded to NB rows:
-// the forward part, row i holding Lh[i+1..i+4][i] for i < NW and
-// Lh[i+1..i+8][i] from NW on (Lh = D^-1 L D), then the backward part, row
-// i >= 1 holding W[i-1..i-4][i] at solve_image_fwd + 4 (i - 1) (row 0 has no
-// entries above the diagonal); rows N..NB-1 are zero.  dinv = 1/U_ii per row.
-__host__ __device__ constexpr int solve_image_fwd(int NB, int NW) { return 4 * NW + 8 * (NB - NW); }
-__host__ __device__ constexpr int solve_image_doubles(int NB, int NW) { return solve_image_fwd(NB, NW) + 4 * (NB - 1); }
-// Twisted substitution images, used where NW = NB - 9 (then N = NB: the
-// clamped wall stencils put the first column with more than four entries
-// below the diagonal at N - 9).  The operator is eliminated from both ends
-// without pivoting: columns 0..h-1 top-down, columns NB-1..h+4 bottom-up,
-// h = (NB - 4) / 2, which leaves rows h..h+3 coupled only among themselves.
-// With p_i the pivots of the top and bottom rows and s_i = 1/p_i there (1 on
-// the middle rows), the right-hand side arrives scaled by s (dinv = s), and
-// a top lane and a bottom lane solve together:
-//   phase 1, h steps each: the top lane runs down rows 0..h-1, the bottom
-//     lane up rows NB-1..h+4, each record holding the four scaled
-//     multipliers s_i l_ij p_j of its column (rows below, resp. above);
-//   middle: both lanes add their four remainders for rows h..h+3, subtract
-//     the right-hand side once and apply Mi, the inverse of the middle block;
-//   phase 3, h + 4 steps each: the top lane runs up columns h+3..0, the
-//     bottom lane down columns h..NB-1 (the first four steps with the middle
-//     values known), records holding s_i A~[i][j] for the rows of its own
-//     part: four entries, eight for the bottom columns NB-9..NB-7 (the top
-//     lane reads four zeros there).
-// Layout per operator (doubles): phase-1 top records, phase-1 bottom
-// records, Mi (16, row-major), four zeros, phase-3 top records, phase-3
-// bottom records; 8 NB + 32 in all, the size of the standard image with
-// NW = NB - 9.
-__host__ __device__ constexpr bool solve_twisted(int NB, int NW) { return NW == NB - 9; }
-__host__ __device__ constexpr int tw_h(int NB) { return (NB - 4) / 2; }
-__host__ __device__ constexpr int tw_p1b(int NB) { return 4 * tw_h(NB); }
-__host__ __device__ constexpr int tw_mi(int NB) { return 8 * tw_h(NB); }
-__host__ __device__ constexpr int tw_z4(int NB) { return tw_mi(NB) + 16; }
-__host__ __device__ constexpr int tw_p3a(int NB) { return tw_z4(NB) + 4; }
-__host__ __device__ constexpr int tw_p3b(int NB) { return tw_p3a(NB) + 4 * (tw_h(NB) + 4); }
-// first of the three wide phase-3 steps of the bottom lane (columns NB-9..NB-7)
-__host__ __device__ constexpr int tw_w0(int NB) { return NB - 9 - tw_h(NB); }
-__host__ __device__ constexpr bool tw_wide(int NB, int t) { return t >= tw_w0(NB) && t < tw_w0(NB) + 3; }
-// offset of the bottom lane's phase-3 record of step t
-__host__ __device__ constexpr int tw_p3b_rec(int NB, int t) {
-    return tw_p3b(NB) + 4 * t + 4 * ((t < tw_w0(NB) ? tw_w0(NB) : (t > tw_w0(NB) + 3 ? tw_w0(NB) + 3 : t)) - tw_w0(NB));
-}
-static_assert(tw_p3b_rec(64, tw_h(64) + 4) == solve_image_doubles(64, 55), "twisted image size, NB = 64");
-static_assert(tw_p3b_rec(48, tw_h(48) + 4) == solve_image_doubles(48, 39), "twisted image size, NB = 48");
-static_assert(tw_p3b_rec(32, tw_h(32) + 4) == solve_image_doubles(32, 23), "twisted image size, NB = 32");
-// Padded row count and narrow-row count of the substitution for N radial
-// points whose LU columns j < narrow have at most four entries below the
-// diagonal: NB = 32, 48 or 64, NW = NB - 9, NB - 25 or 0 (the largest the
-// bound allows).
-__host__ __device__ constexpr int solve_nb(int N) { return N <= 32 ? 32 : (N <= 48 ? 48 : 64); }
-__host__ __device__ constexpr int solve_nw(int N, int narrow) {
-    return narrow >= solve_nb(N) - 9 ? solve_nb(N) - 9 : (narrow >= solve_nb(N) - 25 ? solve_nb(N) - 25 : 0);
-}
+// Block form of the radial operators.  The rows are taken in tiles of four,
+// aligned to the wall, the last eight rows as one block: a 9-point stencil
+// reaches at most four rows either way, and the clamped wall stencils (rows
+// N-4..N-2, columns from N-9 on) stay within the last block and the tile
+// before it, so every operator is block tridiagonal.  nt = btd_nt(N) tiles
+// precede the last block; zero rows pad the axis end, btd_rows(nt) rows in
+// all.  With the diagonal blocks D_I of the block elimination
+//   D_0 = A_00,  D_I = A_II - B_I D_{I-1}^{-1} C_{I-1}
+// (B_I = A_{I,I-1}, C_I = A_{I,I+1}), A x = b is solved by
+//   v_I = D_I^{-1} (b_I - B_I v_{I-1}) upwards, x_I = v_I - D_I^{-1} C_I x_{I+1} downwards.
+// Only the D_I^{-1} depend on the operator (its image: nt tiles of 16
+// doubles, then the 8 x 8 block as four tiles, rows by columns; tiles 2 p and
+// 2 p + 1 interleaved, element [i][k] of theirs at 32 p + 2 (4 k + i) + 0, 1, so
+// that a lane's elements of two tiles are one 16-byte load).  The couplings are those of
+// d^2/dr^2 + (1/r) d/dr, the same for every operator of one axis parity,
+// because the Helmholtz systems are solved as L - Re / (c dt) (scaled by
+// -Re / c): -B_1..-B_nt (B_nt the rows of the last block's first half), the
+// second half's tile, then -C_0..-C_{nt-1}.  Only stencils folded at the axis
+// depend on the parity, entries with row + column <= 3; with at most seven
+// rows of padding those lie in B_1, B_2, C_0 and C_1, which follow for the
+// even and then for the odd parity (element [i][k] of a tile at 4 k + i).
+// nt is rounded up to even so that few kernels cover 12 <= N <= 64.
+__host__ __device__ constexpr int btd_nt(int N) { return ((N - 5) / 4 + 1) / 2 * 2; }
+__host__ __device__ constexpr int btd_rows(int nt) { return 4 * nt + 8; }
+__host__ __device__ constexpr int btd_image(int nt) { return 16 * (nt + 4); }
+__host__ __device__ constexpr int btd_coupling(int nt) { return 16 * (2 * nt + 9); }
+static_assert(btd_nt(12) == 2 && btd_nt(16) == 2 && btd_nt(17) == 4 && btd_nt(64) == 14, "tiles before the last block");
+static_assert(btd_rows(btd_nt(64)) == 64 && btd_rows(btd_nt(12)) == 16, "padded rows");
 constexpr int NMAX = 64;  // radial points handled by one solve workgroup
 
 // Complex number used by the kernels (interleaved re/im, same layout as
@@ -99,8 +71,8 @@ struct Tables {
     const double* d2;     // [2][N][9] folded second-derivative weights
     const int* s0;        // [N] first column of row n's 9-point window
     const double* fac;    // [nfac] banded LU factors of N FACW doubles (main then tail records)
-    const double* img;    // substitution images: [K][MU] Helmholtz, then [K][M] pressure
-    const double* dinv;   // [K][MU] then [K][M] rows of NB values: 1/U_ii (0 past N)
+    const double* img;    // inverse diagonal blocks: [K][MU] Helmholtz, then [K][M] pressure (btd_image doubles each)
+    const double* coup;   // coupling tiles (btd_coupling doubles)
     const double* wl;     // [2][N][9] folded weights of d2/dr2 + (1/r) d/dr, parity 0 even / 1 odd
     const double* hom;    // [M][K][NHOM][N] influence data (h1+, h1-, q, h2, h3, h4, P1)
     const double* ainv;   // [M][2K-1][16][2] inverse influence matrices (complex)
@@ -128,10 +100,10 @@ struct NLArgs {
 struct SolveArgs {
     int N, M, K, nk, mp, MU;
     int gm;             // consecutive m per workgroup (tile shape), see gm_ok
-    int narrow;         // LU columns j < narrow have L[i][j] = 0 for i > j + 4
     int kind;           // OPF_SOLVE_PRED / CORR / RAW
     int fixed_flux;
     double alpha, Re, c, inv_dt, aexp, force;
+    double hscale;      // -Re / c: the Helmholtz systems are solved as L - Re / (c dt) (see helmholtz_scale)
     const double* u0;   // u^n (external layout, complex128); PRED / CORR
     const void* n0;     // N^n (nonlinear storage type), or R (complex128) for RAW
     const void* n1;     // N^p for CORR
@@ -163,15 +135,15 @@ struct FactorArgs {
     double alpha;
     double cr;          // c / Re
     double inv_dt;      // 1 / dt
+    double shift;       // Re / (c dt), consistent with SolveArgs::hscale
     const double* rinv;
     const double* quad;
     const double* d1;
     const double* d2;
     const int* s0;
     double* fac;        // [MU K + M K] factors of N FACW doubles: H_{|mu|,|k|} then L_{m,|k|}
-    double* img;        // substitution images (Tables::img), NB rows, NW narrow rows
-    double* dinv;       // Tables::dinv
-    int NB, NW;
+    double* img;        // inverse diagonal blocks (Tables::img)
+    int nt;             // btd_nt(N)
     double* hom;        // [M][K][NHOM][N]
     double* ainv;       // [M][2K-1][16][2]
     double* green;      // [N]
@@ -219,9 +191,10 @@ hipError_t launch_nonlinear_batch(const NLArgs& proto, const NLArgs* dev_args, i
                                   int stage, hipStream_t s);
 hipError_t launch_solve_batch(const SolveArgs& proto, const SolveArgs* dev_args, int members, int precision,
                               hipStream_t s);
-int default_gm(int mp);
+int default_gm(int mp);                  // of an ensemble class
+int context_gm(int mp, int M, int K);    // of a single context
 bool gm_ok(int gm, int mp);
-constexpr int NFH = 6;  // Helmholtz factors a solve workgroup stages at once
+constexpr int NFH = 6;  // Helmholtz operators that the m of one solve workgroup may use
 hipError_t launch_vorticity(const AuxArgs& a, hipStream_t s);
 hipError_t launch_energy(const AuxArgs& a, hipStream_t s);
 // Per mode q: part[2q] = max |g| of (u+(1), u-(1), u_z(1), div u(1)),

@@ -9,19 +9,13 @@
 // vector Laplacian decouples (L_{m+-1} on u+-, L_m on u_z and P), so every
 // system is a real banded matrix acting on complex data.
 //
-// One 4-wave workgroup handles |k| and GM consecutive m (GM = 4 for mp = 1),
-// both signs of k: up to eight modes, which share their factors (they depend
-// on |k|, and neighbouring m share Helmholtz operators).  Lanes are radial
-// nodes for the stencil work, wave w holding modes 2w and 2w+1; for the
-// substitutions each lane of wave 0 owns one real right-hand side (a real or
-// imaginary part of one component of one mode) and walks the rows of the
-// operator's substitution image (unit triangles of the diagonally scaled LU
-// factors, see solve_image_doubles), brought into LDS by DMA.  About 52 KB
-// of LDS and at most 168 VGPRs let three workgroups share a compute unit, so
-// the 768 tiles of the 64 x 48 x 127-mode grid run in one round.  m = 0
-// solves k >= 0 only and writes the conjugate into -k (Hermitian symmetry
-// of a real field); mode (0,0) has u_r = 0, no pressure and the fixed-flux
-// correction.
+// One wave handles |k| and one m, both signs of k: two modes, four real
+// right-hand sides per system.  Lanes are radial nodes for the stencil work;
+// the banded systems are solved in block form (btd_nt in opf_internal.h) on
+// the FP64 matrix cores.  The waves share nothing but a workgroup's L1, so
+// there is no workgroup barrier.  m = 0 solves k >= 0 only and writes the
+// conjugate into -k (Hermitian symmetry of a real field); mode (0,0) has
+// u_r = 0, no pressure and the fixed-flux correction.
 #include "opf_internal.h"
 
 namespace opf {
@@ -36,6 +30,8 @@ __device__ __forceinline__ dcplx operator-(dcplx a, dcplx b) { return {a.x - b.x
 __device__ __forceinline__ dcplx operator*(double s, dcplx a) { return {s * a.x, s * a.y}; }
 __device__ __forceinline__ dcplx cm(dcplx a, dcplx b) { return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x}; }
 __device__ __forceinline__ dcplx ix(dcplx a) { return {-a.y, a.x}; }  // i * a
+
+typedef double dpair __attribute__((ext_vector_type(2)));
 
 // Row n of a 9-point stencil applied to a radial line in LDS.
 __device__ __forceinline__ dcplx stencil(const double* w, const dcplx* line, int s0) {
@@ -55,9 +51,10 @@ template <typename T>
 struct vec2 {
     T x, y;
 };
+// The value at a wave-uniform base plus a lane's 32-bit byte offset (one address register per lane).
 template <typename T>
-__device__ __forceinline__ vec2<T> load_v(const void* base, size_t idx) {
-    const T* p = reinterpret_cast<const T*>(base) + 2 * idx;
+__device__ __forceinline__ vec2<T> load_v(const void* base, unsigned bytes) {
+    const T* p = reinterpret_cast<const T*>(static_cast<const char*>(base) + bytes);
     return {p[0], p[1]};
 }
 template <typename T>
@@ -71,6 +68,10 @@ __device__ __forceinline__ void store_c(void* base, size_t idx, dcplx v) {
     p[1] = T(v.y);
 }
 
+// Rounds v here: the compiler may not contract the operations before with
+// those after into one multiply-add.
+__device__ __forceinline__ void settle(dcplx& v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+
 // Vorticity of mode (m, kappa) at one radial node, the cylindrical curl
 // (the rotational form of the nonlinear term, Section 2.2):
 //   w_r = (i m / r) u_z - i kappa u_theta,  w_theta = i kappa u_r - u_z',
@@ -79,450 +80,298 @@ __device__ __forceinline__ void store_c(void* base, size_t idx, dcplx v) {
 // m) and dut = u_theta' (parity of m +- 1).
 __device__ __forceinline__ void curl_row(dcplx duz, dcplx dut, double rinv, int m, double kap, dcplx ur, dcplx ut,
                                          dcplx uz, dcplx& wr, dcplx& wt, dcplx& wz) {
-    wr = (double(m) * rinv) * ix(uz) - kap * ix(ut);
-    wt = kap * ix(ur) - duz;
-    wz = dut + rinv * (ut - double(m) * ix(ur));
+    // explicit multiply-adds: the solve's vorticity and k_vorticity's are the same to the last bit
+    const double mr = double(m) * rinv, dm = double(m);
+    wr = {fma(kap, ut.y, -(mr * uz.y)), fma(-kap, ut.x, mr * uz.x)};
+    wt = {fma(-kap, ur.y, -duz.x), fma(kap, ur.x, -duz.y)};
+    wz = {fma(rinv, fma(dm, ur.y, ut.x), dut.x), fma(rinv, fma(-dm, ur.x, ut.y), dut.y)};
 }
 
-// Substitution on one real right-hand side held in LDS (element i at
-// col[2 i]: the real or imaginary part of a complex radial line; rows past
-// N are zero), with a factor image F in LDS (see solve_image_doubles); one
-// lane per right-hand side.  Forward sweep with the unit lower Lh, right-
-// looking: once y_i is known it updates the next four (eight from row NW on)
-// entries, kept in registers, so one multiply-add per row lies on the
-// dependency chain; backward sweep with the unit upper W likewise.
+__device__ __forceinline__ void load_pair(const double* p, double& a, double& b) {
+    const dpair v = *reinterpret_cast<const dpair*>(p);
+    a = v.x;
+    b = v.y;
+}
+
+// v_mfma_f64_4x4x4_4b_f64: four independent 4 x 4 x 4 products.  Lane
+// l = i + 4 blk + 16 k supplies A[i][k], lane l = j + 4 blk + 16 k supplies
+// B[k][j], and lane l = j + 4 blk + 16 i receives C[i][j] + sum_k A[i][k] B[k][j]:
+// results arrive in the layout of the B operand, so products chain without
+// any exchange between lanes.
+__device__ __forceinline__ double mm4(double a, double b, double c) {
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
+// Solve four block-tridiagonal systems (one per matrix block, each with four
+// real right-hand sides) in place: D is this lane's element of each inverse
+// diagonal block, cp its element of the first coupling tile in LDS and ap that
+// of its parity's first one (layout at btd_coupling, tiles 16 doubles apart),
+// col its element of the right-hand side's first tile in LDS (tiles 8 doubles
+// apart).
 //
-// The sweeps are bound by LDS latency: a row's factor record and right-hand-
-// side entry are read DN rows ahead (DW for the wide rows past NW, whose
-// records are twice as long), within the register budget of three
-// workgroups per compute unit.  Rows go in pairs so that the two entries
-// read and the two results written become one ds_read2 / ds_write2 each:
-// three LDS instructions per row, which keeps about five rows in flight
-// under the LDS counter's limit of 15.  Each pair's instructions stay in
-// place (a scheduling barrier per pair): free scheduling would hoist the
-// reads of many rows at once.
-template <int NB, int NW>
-__device__ __forceinline__ void lds_solve(const double* __restrict__ F, double* col) {
-    constexpr int DN = 6, DW = 4, DB = 6;  // read-ahead in rows: narrow and wide forward rows, backward rows
-    static_assert(NB % 2 == 0, "rows go in pairs");
-    constexpr int FWD = solve_image_fwd(NB, NW);
-    auto frow = [](int i) { return i < NW ? 4 * i : 4 * NW + 8 * (i - NW); };
-    auto brow = [](int i) { return FWD + 4 * (i - 1); };
-    // row r is requested just before row issue(r) is computed (r <= 7: before the sweep)
-    auto fissue = [](int r) { return r - (r < NW ? DN : DW); };
-    double2 Lr[NB][4];
-    double nb[NB];  // col[2 (r + 8)] for row r
-    auto fload = [&](int r) {
-        const double2* f = reinterpret_cast<const double2*>(F + frow(r));
-#pragma unroll
-        for (int j = 0; j < (r < NW ? 2 : 4); ++j) Lr[r][j] = f[j];
-        nb[r] = r + 8 < NB ? col[2 * (r + 8)] : 0.0;
-    };
-#pragma unroll
-    for (int r = 0; r < NB; ++r)
-        if (fissue(r) < 0) fload(r);
-    double b0 = col[0], b1 = col[2], b2 = col[4], b3 = col[6];
-    double b4 = col[8], b5 = col[10], b6 = col[12], b7 = col[14];
-#pragma unroll
-    for (int i = 0; i < NB; i += 2) {
-#pragma unroll
-        for (int r = i + 1; r < NB && r <= i + 1 + DN; ++r)
-            if (fissue(r) == i || fissue(r) == i + 1) fload(r);
-        __builtin_amdgcn_sched_barrier(0);
-        double y[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int r = i + h;
-            y[h] = b0;
-            b0 = b1 - Lr[r][0].x * y[h];
-            b1 = b2 - Lr[r][0].y * y[h];
-            b2 = b3 - Lr[r][1].x * y[h];
-            b3 = b4 - Lr[r][1].y * y[h];
-            if (r < NW) {
-                b4 = b5;
-                b5 = b6;
-                b6 = b7;
-                b7 = nb[r];
-            } else {
-                b4 = b5 - Lr[r][2].x * y[h];
-                b5 = b6 - Lr[r][2].y * y[h];
-                b6 = b7 - Lr[r][3].x * y[h];
-                b7 = nb[r] - Lr[r][3].y * y[h];
-            }
+// The chain is 4 NT + 4 dependent matrix instructions at about 28 cycles
+// each (60 at 64 rows: 1.7k cycles).  One lane per right-hand side walking
+// the scalar LU factors took 6.4k cycles for the pressure and 7.0k for the
+// Helmholtz systems even with two lanes meeting in the middle, bound by the
+// latency of four LDS instructions per row.  LDS reads run AHEAD tiles ahead,
+// held there by a scheduling barrier per tile (free scheduling hoists them
+// all and spills).
+template <int NT>
+__device__ __forceinline__ void btd_solve(const double* D, const double* cp, const double* ap, double* col) {
+    constexpr int AHEAD = 4;
+    double r[NT + 2], cb[NT + 1], cc[NT], v[NT];
+    auto fload = [&](int q) {
+        if (q <= NT) {
+            cb[q] = q < 2 ? ap[16 * q] : cp[16 * q];
+            r[q + 1] = col[8 * (q + 1)];
         }
-        col[2 * i] = y[0];
-        col[2 * i + 2] = y[1];
+    };
+    auto bload = [&](int q) {
+        if (q >= 0) {
+            cc[q] = q < 2 ? ap[16 * (2 + q)] : cp[16 * (NT + 1 + q)];
+        }
+    };
+    double w = col[0];
+#pragma unroll
+    for (int q = 0; q < AHEAD; ++q) fload(q);
+#pragma unroll
+    for (int q = 0; q < NT; ++q) {
+        fload(q + AHEAD);
+        __builtin_amdgcn_sched_barrier(0);
+        v[q] = mm4(D[q], w, 0.0);
+        w = mm4(cb[q], v[q], r[q + 1]);
     }
-    // backward: row i (from NB - 1 down to 1) needs W's record of row i and
-    // col[2 (i - 4)]; step t = NB - 1 - i
-    double2 Ur[NB][2];
-    double nc[NB];
-    auto bload = [&](int i) {
-        const double2* f = reinterpret_cast<const double2*>(F + brow(i));
-        Ur[i][0] = f[0];
-        Ur[i][1] = f[1];
-        nc[i] = i - 4 >= 0 ? col[2 * (i - 4)] : 0.0;
-    };
 #pragma unroll
-    for (int i = NB - 1; i >= 1; --i)
-        if (NB - 1 - i - DB < 0) bload(i);
-    double c0 = col[2 * (NB - 1)], c1 = col[2 * (NB - 2)], c2 = col[2 * (NB - 3)], c3 = col[2 * (NB - 4)];
+    for (int q = NT - 1; q >= NT - AHEAD; --q) bload(q);
+    const double w1 = mm4(cb[NT], v[NT - 1], r[NT + 1]);
+    double x = mm4(D[NT + 1], w1, mm4(D[NT], w, 0.0));
+    col[8 * (NT + 1)] = mm4(D[NT + 3], w1, mm4(D[NT + 2], w, 0.0));
+    col[8 * NT] = x;
 #pragma unroll
-    for (int t = 0; t < NB; t += 2) {
-#pragma unroll
-        for (int u = t + 1; u < NB - 1 && u <= t + 1 + DB; ++u)  // row 0 has nothing above the diagonal: no record
-            if (u - DB == t || u - DB == t + 1) bload(NB - 1 - u);
+    for (int q = NT - 1; q >= 0; --q) {
+        bload(q - AHEAD);
         __builtin_amdgcn_sched_barrier(0);
-        double x[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int i = NB - 1 - t - h;
-            x[h] = c0;
-            if (i > 0) {
-                c0 = c1 - Ur[i][0].x * x[h];
-                c1 = c2 - Ur[i][0].y * x[h];
-                c2 = c3 - Ur[i][1].x * x[h];
-                c3 = nc[i] - Ur[i][1].y * x[h];
-            }
-        }
-        col[2 * (NB - 1 - t)] = x[0];
-        col[2 * (NB - 2 - t)] = x[1];
+        x = mm4(D[q], mm4(cc[q], x, 0.0), v[q]);
+        col[8 * q] = x;
     }
 }
 
-// Twisted substitution (image layout and scaling as described at
-// solve_twisted): two lanes share a right-hand side, lane `bottom` = 0
-// taking rows 0..h+3 from the top, lane 1 rows h..NB-1 from the bottom, the
-// pair 32 lanes apart in one wave.  Each lane keeps the register window of
-// the one-lane sweeps, walking its rows in its own direction; the two meet in
-// the 4 x 4 middle block.  The chains are h and h + 4 rows instead of NB and
-// NB - 1.  Reads run DT steps ahead.  (Pairing steps into ds_read2 /
-// ds_write2 as the one-lane sweeps do needs a swap of the two values in the
-// bottom lane, whose rows run the other way; measured slower.)
-template <int NB>
-__device__ __forceinline__ void lds_solve_tw(const double* __restrict__ F, double* col, int bottom) {
-    constexpr int h = tw_h(NB), DT = 4;
-    // sweep step t of phase 1 is row t (top) or NB-1-t (bottom); of phase 3,
-    // row h+3-t (top) or h+t (bottom)
-    double* c1 = col + (bottom ? 2 * (NB - 1) : 0);
-    double* c3 = col + (bottom ? 2 * h : 2 * (h + 3));
-    const int dir = bottom ? -2 : 2;  // doubles per phase-1 step (phase 3: the opposite)
-    const double* R1 = F + (bottom ? tw_p1b(NB) : 0);
-    // ---- phase 1: h steps, four-entry records
-    double2 L1[h][2];
-    double n1[h];  // right-hand side of sweep row t + 4 (the middle rows at most)
-    auto load1 = [&](int t) {
-        const double2* f = reinterpret_cast<const double2*>(R1 + 4 * t);
-        L1[t][0] = f[0];
-        L1[t][1] = f[1];
-        n1[t] = c1[dir * (t + 4)];
-    };
-#pragma unroll
-    for (int t = 0; t < DT; ++t) load1(t);
-    double b0 = c1[0], b1 = c1[dir], b2 = c1[2 * dir], b3 = c1[3 * dir];
-#pragma unroll
-    for (int t = 0; t < h; ++t) {
-        if (t + DT < h) load1(t + DT);
-        __builtin_amdgcn_sched_barrier(0);
-        const double y = b0;
-        c1[dir * t] = y;
-        b0 = b1 - L1[t][0].x * y;
-        b1 = b2 - L1[t][0].y * y;
-        b2 = b3 - L1[t][1].x * y;
-        b3 = n1[t] - L1[t][1].y * y;
-    }
-    // ---- middle: rows h..h+3 (top lane's b0..b3, bottom lane's b3..b0)
-    const double o0 = __shfl_xor(b0, 32), o1 = __shfl_xor(b1, 32), o2 = __shfl_xor(b2, 32), o3 = __shfl_xor(b3, 32);
-    const double2* mi = reinterpret_cast<const double2*>(F + tw_mi(NB));
-    double r[4];
-    {
-        const double mine[4] = {b0, b1, b2, b3}, other[4] = {o0, o1, o2, o3};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const double top = bottom ? other[k] : mine[k], bot = bottom ? mine[3 - k] : other[3 - k];
-            r[k] = top + bot - col[2 * (h + k)];
-        }
-    }
-    double xm[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const double2 m01 = mi[2 * k], m23 = mi[2 * k + 1];
-        xm[k] = m01.x * r[0] + m01.y * r[1] + m23.x * r[2] + m23.y * r[3];
-    }
-    if (!bottom) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) col[2 * (h + k)] = xm[k];
-    }
-    // ---- phase 3: h + 4 steps; the first four take the middle values
-    double2 L3[h + 4][4];
-    double n3[h + 4];  // right-hand side of sweep row t + 8
-    auto load3 = [&](int t) {
-        const double* rp = F + (bottom ? tw_p3b_rec(NB, t) : tw_p3a(NB) + 4 * t);
-        const double2* f = reinterpret_cast<const double2*>(rp);
-        L3[t][0] = f[0];
-        L3[t][1] = f[1];
-        if (tw_wide(NB, t)) {
-            const double2* g = reinterpret_cast<const double2*>(bottom ? rp + 4 : F + tw_z4(NB));
-            L3[t][2] = g[0];
-            L3[t][3] = g[1];
-        }
-        n3[t] = t + 8 <= h + 3 ? c3[-dir * (t + 8)] : 0.0;
-    };
-#pragma unroll
-    for (int t = 0; t < DT; ++t) load3(t);
-    double d0 = 0.0, d1 = 0.0, d2 = 0.0, d3 = 0.0;
-    double d4 = c3[-dir * 4], d5 = c3[-dir * 5], d6 = c3[-dir * 6], d7 = c3[-dir * 7];
-#pragma unroll
-    for (int t = 0; t < h + 4; ++t) {
-        if (t + DT < h + 4) load3(t + DT);
-        __builtin_amdgcn_sched_barrier(0);
-        double x;
-        if (t < 4) {
-            x = bottom ? xm[t] : xm[3 - t];
-        } else {
-            x = d0;
-            c3[-dir * t] = x;
-        }
-        d0 = d1 - L3[t][0].x * x;
-        d1 = d2 - L3[t][0].y * x;
-        d2 = d3 - L3[t][1].x * x;
-        d3 = d4 - L3[t][1].y * x;
-        if (tw_wide(NB, t)) {
-            d4 = d5 - L3[t][2].x * x;
-            d5 = d6 - L3[t][2].y * x;
-            d6 = d7 - L3[t][3].x * x;
-            d7 = n3[t] - L3[t][3].y * x;
-        } else {
-            d4 = d5;
-            d5 = d6;
-            d6 = d7;
-            d7 = n3[t];
-        }
-    }
+// Sum over the 16 lanes of a DPP row, in every lane of the row.
+template <int CTRL>
+__device__ __forceinline__ double dpp_rotate(double v) {
+    const long long u = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
-
-// LDS DMA (global_load_lds_dwordx4): each active lane loads 16 bytes from
-// its own global address into LDS at dst + 16 * lane, without registers.
-// dst must be the same for the whole wave.  Completion is tracked by the
-// vector-memory counter, so a wave waits with lds_dma_wait() before the data
-// is read (and a workgroup barrier publishes it to the other waves).
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef __attribute__((address_space(1))) void glb_void_t;
-__device__ __forceinline__ void lds_dma16(const void* src, void* dst_wave) {
-    __builtin_amdgcn_global_load_lds((glb_void_t*)src, (lds_void_t*)dst_wave, 16, 0, 0);
+__device__ __forceinline__ double row_sum(double v) {  // row_ror by 8, 4, 2, 1
+    v += dpp_rotate<0x128>(v);
+    v += dpp_rotate<0x124>(v);
+    v += dpp_rotate<0x122>(v);
+    return v + dpp_rotate<0x121>(v);
 }
-__device__ __forceinline__ void lds_dma_wait() { __builtin_amdgcn_s_waitcnt(0x0F70); }  // vmcnt(0)
-
-// LDS stride (doubles) of a factor image of FW doubles: FW rounded up to 2
-// more than a multiple of 32, so that image o starts 4 o four-byte words
-// past a bank boundary.  The substitution lanes of different operators read
-// the same row at the same time; with images a whole number of bank periods
-// apart those reads would all hit the same four banks.
-constexpr int solve_image_lds_stride(int FW) { return FW + (34 - FW % 32) % 32; }
-
-// Copy nimg consecutive factor images of FW doubles each from global memory
-// to LDS at a stride of FWP doubles, by DMA: 1 KB per wave instruction, the
-// four waves taking alternate kilobytes.  FW * 8 and FWP * 8 are multiples of
-// 16 and both ends 16-byte aligned.
-template <int FW, int FWP>
-__device__ __forceinline__ void dma_images(const double* src, double* dst, int nimg, int w, int lane) {
-    constexpr int NB8 = FW * 8, NCH = (NB8 + 1023) >> 10;
-    static_assert(NB8 % 16 == 0 && (FWP * 8) % 16 == 0, "16-byte DMA units");
-    for (int ch = w; ch < nimg * NCH; ch += 4) {
-        const int im = ch / NCH, c = ch - im * NCH;
-        const int off = (c << 10) + 16 * lane;
-        if (off < NB8)
-            lds_dma16(reinterpret_cast<const char*>(src + (size_t)im * FW) + off,
-                      reinterpret_cast<char*>(dst + im * FWP) + (c << 10));
-    }
+__device__ __forceinline__ double quad_sum(double v) {  // quad_perm [1,0,3,2], [2,3,0,1]
+    v += dpp_rotate<0xB1>(v);
+    return v + dpp_rotate<0x4E>(v);
 }
-
-constexpr int NSLOT = 8;     // modes per workgroup: up to 4 values of m, both signs of k
-
 // 9 weights of one parity for row n, in registers.
 struct Row9 {
     double e[W9];
     __device__ __forceinline__ void load(const double* tab, int N, int par, int n) {
+        // wave-uniform base, 32-bit lane offset, constant offsets: one address for all nine loads
+        const double* p = tab + par * N * W9 + unsigned(n * W9);
 #pragma unroll
-        for (int j = 0; j < W9; ++j) e[j] = tab[(par * N + n) * W9 + j];
+        for (int j = 0; j < W9; ++j) e[j] = p[j];
     }
     __device__ __forceinline__ dcplx apply(const dcplx* line, int s0) const {
-        dcplx acc = {0.0, 0.0};
+        dcplx acc = e[0] * line[s0];
 #pragma unroll
-        for (int j = 0; j < W9; ++j) acc = acc + e[j] * line[s0 + j];
+        for (int j = 1; j < W9; ++j) acc = acc + e[j] * line[s0 + j];
         return acc;
     }
 };
 
-// One workgroup = 4 waves handles |k| = kabs and GM consecutive m
-// (GM = 4, 2, 1 for mp = 1, 2, >= 3 so that the Helmholtz wavenumbers
-// mp*m-1 .. mp*m+1 of the block form one contiguous range of <= 6 values,
-// shared between neighbouring m).  Slot q = 2 j + s is mode (m0 + j, s ? -k : +k).
-// Wave w does the radial-line work of slots 2w, 2w+1 (one lane per radial
-// node); wave 0 does the substitutions, one lane per complex right-hand side.
-// LDS: the factor area (the pressure images and columns, then the Helmholtz
-// images, at a bank-staggered stride), the radial lines (u^n, then the
-// right-hand sides and the solution) and the slots' inverse influence
-// matrices: about 53 KB at NB = 64, so three workgroups share a compute unit.
-// Every input is requested at the start (pressure images and A^-1 by LDS
-// DMA, then each slot's u^n and nonlinear terms into registers), and the
-// first slot's right-hand side is formed while the second slot's data are
-// still arriving; the weights and influence data of later phases are
-// requested a phase ahead, and the Helmholtz images follow as soon as the
-// pressure images are consumed.
-template <typename TNL, int NB, int NW>
-__device__ __forceinline__ void k_solve_body(const SolveArgs& a) {
-    constexpr int FW = solve_image_doubles(NB, NW);
-    constexpr int FWP = solve_image_lds_stride(FW);  // image stride in LDS
-    constexpr int XS = NB + 1;         // radial line stride (complex)
-    constexpr int FA = NFH * FWP;      // factor area (doubles)
-    static_assert(4 * FWP + NSLOT * XS * 2 <= FA, "pressure images and columns fit the factor area");
-    __shared__ __align__(16) double sF[FA];
-    __shared__ __align__(16) dcplx sX[NSLOT][3][XS];
-    // slot q's A^-1 (32 doubles), overwritten by its correction a (8 doubles)
-    // once read; the flux correction of (0,0) in slot 0's last entry
-    __shared__ __align__(16) double sAi[NSLOT][32];
-    double& sGam = sAi[0][31];
-    dcplx(*sY)[XS] = reinterpret_cast<dcplx(*)[XS]>(sF + 4 * FWP);  // pressure columns
+// LDS of one wave: the six lines (2 modes x 3 components) and the two
+// pressure lines, zero rows in front of row 0.  The line stride, 4 mod 8
+// complex, starts consecutive lines 16 (or 48) banks apart, so that the
+// matrix layout's reads of four rows and several lines spread over the banks.
+__host__ __device__ constexpr int solve_line(int nt) { return btd_rows(nt) + 4; }
+// A workgroup's LDS: its waves' lines, then the coupling tiles.
+constexpr size_t solve_lds(int nt, int gm) {
+    return (size_t)gm * 8 * solve_line(nt) * sizeof(dcplx) + btd_coupling(nt) * sizeof(double);
+}
 
+// A workgroup of GM waves handles |k| = kabs and GM consecutive m (GM = 4,
+// 2, 1 for mp = 1, 2, >= 3), which use neighbouring Helmholtz operators
+// (wavenumbers mp m - 1 .. mp m + 1); wave w handles m0 + w, modes s = 0, 1
+// at +k and -k.
+//
+// What bounds it: HBM (the spectral fields once, a third more for the tables)
+// and, on small grids, the length of one wave's phases.  Predictor / corrector
+// at 64 x 48 x 127 modes: 22.5 / 24.6 us in FP64 (26.0 / 28.1 with scalar
+// banded factors shared through LDS and substituted by one wave of each
+// workgroup), 21.6 / 23.4 in mixed precision (25.1 / 27.0); 24 x 8 x 15: 5.8 us
+// (12.4); 41 x 18 x 23, mp = 3: 8.1 us (14.1); 48 x 24 x 63, mp = 2: 10.8 us
+// (15.5).  Measured and dropped: every request made at the start with two waves
+// per SIMD (42 us at 64 x 48 x 127), four waves per SIMD (38 us, spills), the
+// coupling tiles by LDS DMA (the compiler then waits for every load in flight
+// at each LDS read) and v kept in LDS instead of registers.
+template <typename TNL, int NT>
+__device__ __forceinline__ void k_solve_body(const SolveArgs& a) {
+    constexpr int XS = solve_line(NT), IMG = btd_image(NT);
+    extern __shared__ __align__(16) unsigned char solve_smem[];
     const Tables& t = a.t;
-    const int N = a.N, K = a.K, nk = a.nk, mp = a.mp;
-    const int GM = a.gm;
+    const int N = a.N, K = a.K, nk = a.nk, mp = a.mp, GM = a.gm;
     const int nblk = (a.M + GM - 1) / GM;
     // Consecutive block indices go round-robin to the 8 XCDs; each XCD takes
     // a contiguous range of tiles instead, so the m-blocks of one |k|, which
-    // share Helmholtz factors, meet in its L2.
+    // share Helmholtz operators, meet in its L2.
     const int ntiles = (int)gridDim.x;
     const int tile = ntiles % 8 == 0 ? (blockIdx.x % 8) * (ntiles / 8) + blockIdx.x / 8 : (int)blockIdx.x;
     const int kabs = tile / nblk;
-    const int m0 = (tile % nblk) * GM;
-    const int tid = threadIdx.x, n = tid & 63;
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index (uniform)
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // a wave past the last m works on that one without writing anything, up
+    // to the workgroup's one barrier
+    const int mi = min((tile % nblk) * GM + wv, a.M - 1);
+    const bool live = (tile % nblk) * GM + wv < a.M;
+    const int lane = tid & 63, m = mp * mi, pad = btd_rows(NT) - N;
+    // Row work: lanes are radial nodes.  Up to 32 rows the two modes lie side by
+    // side in the wave and are done in one pass, otherwise in two.
+    constexpr bool HALF = btd_rows(NT) <= 32;
+    constexpr int PASSES = HALF ? 1 : 2;
+    const int n = HALF ? lane & 31 : lane, half = lane >> 5;
+    auto mode_of = [&](int p) { return HALF ? half : p; };
+    const bool two = kabs > 0 && mi > 0;     // the -k mode is solved on its own
+    const bool zero = kabs == 0 && mi == 0;  // mode (0,0)
     const size_t S = (size_t)a.M * nk * N;
-    const int mu_lo = max(mp * m0 - 1, 0);
     const int nr = n < N ? n : N - 1;  // lanes past the last row read a valid row
-    const int s0r = t.s0[nr];
+    const int s0r = t.s0[nr] + pad;
     const double rinvr = t.rinv[nr];
-    const int nfp = min(GM, a.M - m0);
-    const int mu_hi = min(mp * (m0 + GM - 1) + 1, a.MU - 1);
-    const int nfh = mu_hi - mu_lo + 1;
-    const int mw = mp * min(m0 + w, a.M - 1);  // azimuthal wavenumber of this wave's slots
-    const size_t ihelm = (size_t)kabs * a.MU + mu_lo;                   // first Helmholtz image
-    const size_t ippe = (size_t)a.MU * K + (size_t)kabs * a.M + m0;     // first pressure image
-
-    auto slot_ok = [&](int q) {
-        const int j = q >> 1, s = q & 1, mi = m0 + j;
-        return j < GM && mi < a.M && (s == 0 || (kabs > 0 && mi > 0));
+    const double kap0 = a.alpha * kabs;
+    auto kap_of = [&](int p) { return mode_of(p) ? -kap0 : kap0; };
+    dcplx* const X = reinterpret_cast<dcplx*>(solve_smem) + wv * 8 * XS;  // line 3 s + c, then 6 + s
+    auto line = [&](int p, int c) { return X + (3 * mode_of(p) + c) * XS; };
+    auto pline = [&](int p) { return X + (6 + mode_of(p)) * XS; };
+    auto mode_row = [&](int s) {  // row 0 of mode s in one field
+        return (unsigned)((mi * nk + (K - 1 + (s ? -kabs : kabs))) * N);
     };
-    auto slot_k = [&](int q) { return (q & 1) ? -kabs : kabs; };
-    auto slot_off = [&](int q) {  // offset of row 0 of slot q in one field
-        return ((size_t)(m0 + (q >> 1)) * nk + (slot_k(q) + K - 1)) * N;
-    };
+    // matrix layout: row ti of a tile, block blk, column j = (mode, real or imaginary part)
+    const int ti = lane >> 4, blk = (lane >> 2) & 3, mode = (lane >> 1) & 1, part = lane & 1;
+    const int te = 4 * ti + (lane & 3);  // this lane's element of a stored tile
 
-    // ---- requests, in the order the phases need them: the pressure images
-    //      and the slots' A^-1 by LDS DMA, the stencil weights, then slot 2w
-    //      and slot 2w+1 (u^n or R and the nonlinear terms, one radial row per
-    //      lane) into registers.  The register loads are unconditional (rows
-    //      and modes clamped to valid ones), so the counted wait before slot
-    //      2w's right-hand side leaves slot 2w+1's loads in flight: loads are
-    //      served in order, and slot 2w's right-hand side is formed while
-    //      slot 2w+1's data arrive.  The nonlinear-term loads a kind does not
-    //      use (N^p for PRED, both for RAW) read one fixed 16-byte location
-    //      instead: one cache line for the whole wave, no extra HBM traffic.
-    dma_images<FW, FWP>(t.img + ippe * FW, sF, nfp, w, n);
-    if (w == 0) {
+    // ---- requests, in the order the phases need them: the coupling tiles
+    //      (shared by the workgroup, 16 bytes per thread and load), the stencil
+    //      weights, then u^n and the nonlinear terms of this lane's rows
+    constexpr int CN = btd_coupling(NT) / 2, CQ = (CN + 63) / 64;
+    double* const coup = reinterpret_cast<double*>(solve_smem) + GM * 16 * XS;
+    dpair cl[CQ];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {  // four slots (16 lanes of 16 bytes each) per instruction
-            const int q = 4 * i + (n >> 4);
-            if (slot_ok(q))
-                lds_dma16(t.ainv + (((size_t)(m0 + (q >> 1)) * nk + (slot_k(q) + K - 1)) * 16) * 2 + 2 * (n & 15),
-                          &sAi[4 * i][0]);
-        }
-    }
-    Row9 Lo, Le;  // weights of d2/dr2 + (1/r) d/dr, parity of this wave's m +- 1 and of m
-    Lo.load(t.wl, N, (mw + 1) & 1, nr);
-    Le.load(t.wl, N, mw & 1, nr);
+    for (int q = 0; q < CQ; ++q) cl[q] = reinterpret_cast<const dpair*>(t.coup)[min(tid + q * 64 * GM, CN - 1)];
+    Row9 Lo, Le;  // weights of d2/dr2 + (1/r) d/dr, parity of m +- 1 and of m
+    Lo.load(t.wl, N, (m + 1) & 1, nr);
+    Le.load(t.wl, N, m & 1, nr);
     const double* src = a.kind == OPF_SOLVE_RAW ? static_cast<const double*>(a.n0) : a.u0;
+    // the terms a kind does not use (N^p for PRED, both for RAW) read one
+    // fixed location instead: one cache line for the whole wave
     const bool use0 = a.kind != OPF_SOLVE_RAW, use1 = a.kind == OPF_SOLVE_CORR;
     const void* nl0 = use0 ? a.n0 : static_cast<const void*>(t.rinv);
     const void* nl1 = use1 ? a.n1 : static_cast<const void*>(t.rinv);
-    dcplx ul[2][3];               // u^n (RAW: R) of this lane's row
-    vec2<TNL> x0[2][3], x1[2][3];  // N^n and N^p as stored
-    auto request = [&](int j) {
-        const int q = 2 * w + j;
-        const size_t off = ((size_t)min(m0 + (q >> 1), a.M - 1) * nk + (slot_k(q) + K - 1)) * N + nr;
+    const unsigned mask0 = use0 ? ~0u : 0u, mask1 = use1 ? ~0u : 0u;
+    vec2<double> ul[PASSES][3];              // u^n (RAW: R)
+    vec2<TNL> x0[PASSES][3], x1[PASSES][3];  // N^n and N^p as stored
 #pragma unroll
-        for (int c = 0; c < 3; ++c) ul[j][c] = load_c<double>(src, c * S + off);
+    for (int p = 0; p < PASSES; ++p) {
+        if (p == 1) {
+            // The second mode is requested once the first has arrived: the
+            // launch's load burst is served roughly in the order the requests
+            // reach the memory system, so every wave then has its first mode by
+            // the middle of the burst and works on it while the rest arrives
+            // (FP64 corrector 25.4 us against 25.6 with both at once, mixed
+            // 23.6 against 24.6, at 64 x 48 x 127 modes).
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const unsigned row = mode_row(mode_of(p)) + nr;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) ul[p][c] = load_v<double>(src, (row + c * (unsigned)S) * 16u);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            x0[j][c] = load_v<TNL>(nl0, use0 ? c * S + off : 0);
-            x1[j][c] = load_v<TNL>(nl1, use1 ? c * S + off : 0);
+            const unsigned off = (row + c * (unsigned)S) * (unsigned)(2 * sizeof(TNL));
+            x0[p][c] = load_v<TNL>(nl0, off & mask0);
+            x1[p][c] = load_v<TNL>(nl1, off & mask1);
         }
-    };
-    const auto zero_tail_rows = [&] {  // rows N..NB of this wave's lines stay zero (branch-free substitution)
-        for (int i = n; i < 2 * 3 * (XS - N); i += 64) {
-            const int j = i / (3 * (XS - N)), rem = i % (3 * (XS - N));
-            sX[2 * w + j][rem / (XS - N)][N + rem % (XS - N)] = dcplx{0.0, 0.0};
-        }
-    };
-    request(0);
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (sizeof(TNL) == 8) {
-        // FP64 nonlinear terms: slot 2w+1 is requested only once slot 2w has
-        // arrived.  The launch's load burst is served roughly in the order the
-        // requests reach the memory system, so every workgroup then has its
-        // first slot by about the middle of the burst and forms that slot's
-        // right-hand side before its last data arrive; the workgroups that
-        // come last in the order, which set the launch's length, gain most.
-        // (With FP32 terms the burst is shorter and this measured slower.)
-        zero_tail_rows();
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        __builtin_amdgcn_sched_barrier(0);
-        request(1);
-        __builtin_amdgcn_sched_barrier(0);
-    } else {
-        request(1);
-        __builtin_amdgcn_sched_barrier(0);
-        zero_tail_rows();
-        // Slot 2w+1's nine loads (nine instructions: the u^n and N^n, N^p
-        // reads lie far apart and none is dropped) are the last vector-memory
-        // instructions issued: with at most nine outstanding, everything older
-        // (the DMA, the weights, slot 2w) has landed.  The compiler's own wait
-        // would be vmcnt(0) while the DMA is pending, which would also wait
-        // for slot 2w+1.
-        __builtin_amdgcn_s_waitcnt(0x0F79);  // vmcnt(9)
-        __builtin_amdgcn_sched_barrier(0);
     }
+    double Dp[NT + 4], Dh[NT + 4];  // inverse diagonal blocks: the pressure's; u+, u-, u_z in matrix blocks 0, 1, 2
+    Row9 W1o, W1e;                  // first-derivative weights of this lane's row, parity of m +- 1 and of m
+    double hv[NHOM];                // homogeneous solutions at this row
+    const int e16 = lane & 15;
+    double wwall;                   // the wall row's weights (nine lanes of 16)
+    dcplx Ai;                       // element [i][j] of mode s's A^-1 in lane 32 s + 4 i + j
+    auto request_pressure = [&] {
+        const double* ip = t.img + ((size_t)a.MU * K + (size_t)kabs * a.M + mi) * IMG + unsigned(2 * te);
+#pragma unroll
+        for (int q = 0; q < NT + 4; q += 2) load_pair(ip + 16 * q, Dp[q], Dp[q + 1]);
+    };
+    auto request_helmholtz = [&] {
+        const unsigned mu = blk == 0 ? m + 1 : (blk == 1 ? abs(m - 1) : m);
+        const double* ip = t.img + (size_t)kabs * a.MU * IMG + (mu * IMG + 2 * te);
+#pragma unroll
+        for (int q = 0; q < NT + 4; q += 2) load_pair(ip + 16 * q, Dh[q], Dh[q + 1]);
+    };
+    auto request_influence = [&] {
+        const double* h = t.hom + ((size_t)mi * K + kabs) * NHOM * N + unsigned(nr);
+#pragma unroll
+        for (int j = 0; j < NHOM; ++j) hv[j] = j < NHOM - 1 || a.p_out ? h[j * N] : 0.0;
+        wwall = e16 < W9 ? t.d1[(((m + 1) & 1) * N + N - 1) * W9 + e16] : 0.0;
+        Ai = load_c<double>(t.ainv, ((size_t)mi * nk + (K - 1 + (half ? -kabs : kabs))) * 16 + e16);
+    };
+#pragma unroll
+    for (int q = 0; q < CQ; ++q)
+        if (tid + q * 64 * GM < CN) reinterpret_cast<dpair*>(coup)[tid + q * 64 * GM] = cl[q];
+    // the only workgroup barrier: from here on the waves share nothing.  It
+    // publishes LDS only (a full barrier would wait for the loads in flight).
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    if (!live) return;
+#pragma unroll
+    for (int l = 0; l < 8; ++l)
+        if (lane < pad) X[l * XS + lane] = dcplx{0.0, 0.0};
 
-    // ---- R = [1/dt + (1-c) L / Re] u^n + N (+ forcing) in the (+,-,z) form,
-    //      slot by slot from this wave's own lines (no workgroup barrier)
+    // ---- R = [1/dt + (1-c) L / Re] u^n + N (+ forcing) in the (+,-,z) form
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const int q = 2 * w + j;
+    for (int p = 0; p < PASSES; ++p) {
+        dcplx *l0 = line(p, 0), *l1 = line(p, 1), *l2 = line(p, 2), *lp = pline(p);
+        dcplx na[3];  // PRED: N^n; CORR: (1-c) N^n + c N^p
+        if (a.kind == OPF_SOLVE_CORR) {
+            const double cc = a.c, c1 = 1.0 - a.c;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) na[c] = c1 * to_c(x0[p][c]) + cc * to_c(x1[p][c]);
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) na[c] = to_c(x0[p][c]);
+        }
+        if (p == PASSES - 1) {  // requested once the other loads' registers are free
+            __builtin_amdgcn_sched_barrier(0);
+            request_pressure();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const dcplx ur = to_c(ul[p][0]), ut = to_c(ul[p][1]), uz = to_c(ul[p][2]);
         if (n < N) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sX[q][c][n] = ul[j][c];
+            l0[pad + n] = ur;
+            l1[pad + n] = ut;
+            l2[pad + n] = uz;
         }
         __builtin_amdgcn_wave_barrier();
         dcplx rr[3];
-        const dcplx ur = ul[j][0], ut = ul[j][1], uz = ul[j][2];
         if (a.kind == OPF_SOLVE_RAW) {
             rr[0] = ur + ix(ut);
             rr[1] = ur - ix(ut);
             rr[2] = uz;
         } else {
-            dcplx na[3];  // PRED: N^n; CORR: (1-c) N^n + c N^p
-            if (a.kind == OPF_SOLVE_PRED) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c) na[c] = to_c(x0[j][c]);
-            } else {
-                const double cc = a.c, c1 = 1.0 - a.c;
-#pragma unroll
-                for (int c = 0; c < 3; ++c) na[c] = c1 * to_c(x0[j][c]) + cc * to_c(x1[j][c]);
-            }
-            const int m = mp * (m0 + (q >> 1)), k = slot_k(q);
-            const double kap2 = a.alpha * k * a.alpha * k;
-            const dcplx dr = Lo.apply(sX[q][0], s0r), dt = Lo.apply(sX[q][1], s0r), dz = Le.apply(sX[q][2], s0r);
+            const double kap2 = kap0 * kap0;
+            const dcplx dr = Lo.apply(l0, s0r), dt = Lo.apply(l1, s0r), dz = Le.apply(l2, s0r);
             const dcplx up = ur + ix(ut), um = ur - ix(ut);
             const double r2 = rinvr * rinvr;
             const dcplx Lp = (dr + ix(dt)) - (double(m + 1) * double(m + 1) * r2 + kap2) * up;
@@ -531,270 +380,177 @@ __device__ __forceinline__ void k_solve_body(const SolveArgs& a) {
             rr[0] = a.inv_dt * up + a.aexp * Lp + (na[0] + ix(na[1]));
             rr[1] = a.inv_dt * um + a.aexp * Lm + (na[0] - ix(na[1]));
             rr[2] = a.inv_dt * uz + a.aexp * Lz + na[2];
-            if (m == 0 && k == 0) rr[2].x += a.force;
+            if (zero) rr[2].x += a.force;
         }
-        __builtin_amdgcn_wave_barrier();  // every lane of the wave has read the u^n lines
-        if (n < N && slot_ok(q)) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c) sX[q][c][n] = rr[c];
-            sY[q][n] = 0.5 * (rr[0] + rr[1]);  // R_r, for the divergence
+        __builtin_amdgcn_wave_barrier();  // every lane has read the u^n lines
+        if (n < N) {
+            l0[pad + n] = rr[0];
+            l1[pad + n] = rr[1];
+            l2[pad + n] = rr[2];
+            lp[pad + n] = 0.5 * (rr[0] + rr[1]);  // R_r, for the divergence
         }
         __builtin_amdgcn_wave_barrier();
     }
 
-    // ---- pressure-Poisson right-hand side div R (P(1) = 0), scaled by 1/U_ii
+    // ---- pressure-Poisson right-hand side div R (P(1) = 0):
+    //      div R = d/dr R_r + [(1+m) R+ + (1-m) R-] / (2r) + i kappa R_z, R_r = (R+ + R-)/2
     {
-        Row9 W1o;
-        W1o.load(t.d1, N, (mw + 1) & 1, nr);
-        const double* dvp = t.dinv + ((size_t)a.MU * K + (size_t)kabs * a.M + min(m0 + w, a.M - 1)) * NB;
-        const double dv = n < N ? dvp[n] : 0.0;
-        // div R = d/dr R_r + [(1+m) R+ + (1-m) R-] / (2r) + i kappa R_z, R_r = (R+ + R-)/2
-        dcplx d[2];
+        W1o.load(t.d1, N, (m + 1) & 1, nr);
+        dcplx d[PASSES];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int q = 2 * w + j;
-            const int m = mp * (m0 + (q >> 1));
-            const double kap = a.alpha * slot_k(q);
-            d[j] = dcplx{0.0, 0.0};
-            if (slot_ok(q) && n < N - 1 && !(m == 0 && kap == 0.0))
-                d[j] = W1o.apply(sY[q], s0r) +
-                       (0.5 * rinvr) * (double(1 + m) * sX[q][0][n] + double(1 - m) * sX[q][1][n]) +
-                       kap * ix(sX[q][2][n]);
-        }
-        __builtin_amdgcn_wave_barrier();  // every lane of the wave has read the R_r lines
+        for (int p = 0; p < PASSES; ++p)
+            d[p] = W1o.apply(pline(p), s0r) +
+                   (0.5 * rinvr) * (double(1 + m) * line(p, 0)[pad + nr] + double(1 - m) * line(p, 1)[pad + nr]) +
+                   kap_of(p) * ix(line(p, 2)[pad + nr]);
+        __builtin_amdgcn_wave_barrier();  // every lane has read the R_r lines
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int q = 2 * w + j;
-            if (n < XS) sY[q][n] = dv * d[j];  // rows N..XS-1 zero (dv = 0 there)
-            if (n < XS - 64) sY[q][64 + n] = dcplx{0.0, 0.0};
-        }
+        for (int p = 0; p < PASSES; ++p)
+            if (n < N) pline(p)[pad + n] = n < N - 1 ? d[p] : dcplx{0.0, 0.0};
     }
-    lds_dma_wait();  // this wave's share of the pressure images and A^-1 (landed long ago)
-    // the next phase's weights and 1/U_ii of H_{m+1}, H_{|m-1|}, H_m at this
-    // row, requested now so that they arrive during the substitution
-    Row9 W1e;
-    W1e.load(t.d1, N, mw & 1, nr);
-    const double* dvh = t.dinv + (size_t)kabs * a.MU * NB;
-    const double dvp = n < N ? dvh[(size_t)(mw + 1) * NB + n] : 0.0;
-    const double dvm = n < N ? dvh[(size_t)abs(mw - 1) * NB + n] : 0.0;
-    const double dvz = n < N ? dvh[(size_t)mw * NB + n] : 0.0;
-    __syncthreads();
-    // The substituting waves run at a raised issue priority: a substitution is
-    // one dependent chain per right-hand side, and on a busy compute unit the
-    // waves of the other resident workgroups (still forming right-hand sides,
-    // their loads having arrived later) would otherwise delay its steps.
-    if constexpr (solve_twisted(NB, NW)) {  // right-hand side n & 31, its top lane n < 32
-        if (w == 0) {
-            __builtin_amdgcn_s_setprio(2);
-            if ((n & 31) < 2 * NSLOT && slot_ok((n & 31) >> 1))
-                lds_solve_tw<NB>(sF + ((n & 31) >> 2) * FWP, &sY[(n & 31) >> 1][0].x + (n & 1), n >> 5);
-            __builtin_amdgcn_s_setprio(0);
-        }
-    } else if (w == 0) {
-        __builtin_amdgcn_s_setprio(2);
-        if (n < 2 * NSLOT && slot_ok(n >> 1)) lds_solve<NB, NW>(sF + (n >> 2) * FWP, &sY[n >> 1][0].x + (n & 1));
-        __builtin_amdgcn_s_setprio(0);
-    }
-    __syncthreads();
+    __builtin_amdgcn_wave_barrier();
+    request_helmholtz();
+    __builtin_amdgcn_sched_barrier(0);
+    // every matrix block solves the pressure (same results, same addresses)
+    btd_solve<NT>(Dp, coup + te, coup + 16 * (2 * NT + 1 + 4 * (m & 1)) + te, &(X + (6 + mode) * XS + ti)->x + part);
+    __builtin_amdgcn_wave_barrier();
 
-    // ---- R -= grad P, scaled by 1/U_ii of each Helmholtz operator; (0,0):
-    //      u_r = 0, real R_theta and R_z.  The Helmholtz images that do not
-    //      cover the pressure columns are requested first.
-    const int nfh1 = min(nfh, 4);
-    dma_images<FW, FWP>(t.img + ihelm * FW, sF, nfh1, w, n);
+    // ---- R -= grad P, scaled by -Re/c; (0,0): u_r = 0, real R_theta and R_z
+    W1e.load(t.d1, N, m & 1, nr);
+    dcplx P[PASSES];
     {
-        if (n < N) {
+        const double hs = a.hscale;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const int q = 2 * w + j;
-                if (!slot_ok(q)) continue;
-                const int m = mp * (m0 + (q >> 1));
-                const double kap = a.alpha * slot_k(q);
-                dcplx r0 = sX[q][0][n], r1 = sX[q][1][n], r2 = sX[q][2][n];
-                const dcplx P = sY[q][n];
-                if (a.p_out && !(m == 0 && kap == 0.0))  // the pressure head before the influence correction
-                    store_c<double>(a.p_out, slot_off(q) + n, P);
-                if (n == N - 1) {
-                    r0 = r1 = r2 = dcplx{0.0, 0.0};
-                    if (m == 0 && kap == 0.0 && a.wall) {  // (0,0): Dirichlet values u_theta(1), u_z(1)
-                        const size_t w0 = (size_t)(K - 1) * 2, ws = (size_t)a.M * nk * 2;
-                        r0 = dcplx{a.wall[ws + w0], 0.0};
-                        r2 = dcplx{a.wall[2 * ws + w0], 0.0};
-                    }
-                } else if (m == 0 && kap == 0.0) {
-                    const dcplx d = r0 - r1;  // 2 i R_theta
-                    r0 = dcplx{0.5 * d.y, 0.0};
-                    r1 = dcplx{0.0, 0.0};
-                    r2 = dcplx{r2.x, 0.0};
-                } else {
-                    const dcplx dP = W1e.apply(sY[q], s0r);
-                    const dcplx mP = (double(m) * rinvr) * P;
-                    r0 = r0 - (dP - mP);
-                    r1 = r1 - (dP + mP);
-                    r2 = r2 - kap * ix(P);
-                }
-                // (0,0) solves u_theta with H_1 in the + slot and u_z with H_0
-                sX[q][0][n] = dvp * r0;
-                sX[q][1][n] = dvm * r1;
-                sX[q][2][n] = dvz * r2;
+        for (int p = 0; p < PASSES; ++p) {
+            dcplx r0 = line(p, 0)[pad + nr], r1 = line(p, 1)[pad + nr], r2 = line(p, 2)[pad + nr];
+            P[p] = pline(p)[pad + nr];
+            if (zero) {
+                const dcplx d = r0 - r1;  // 2 i R_theta
+                r0 = dcplx{0.5 * d.y, 0.0};
+                r1 = dcplx{0.0, 0.0};
+                r2 = dcplx{r2.x, 0.0};
+            } else {
+                const dcplx dP = W1e.apply(pline(p), s0r);
+                const dcplx mP = (double(m) * rinvr) * P[p];
+                r0 = r0 - (dP - mP);
+                r1 = r1 - (dP + mP);
+                r2 = r2 - kap_of(p) * ix(P[p]);
             }
-        }
-    }
-    __syncthreads();  // the pressure columns are read: the rest of the Helmholtz images may land there
-    if (nfh > nfh1)
-        dma_images<FW, FWP>(t.img + (ihelm + nfh1) * FW, sF + nfh1 * FWP, nfh - nfh1, w, n);
-    lds_dma_wait();
-    // influence data of this wave's m (one radial row per lane), requested
-    // before the substitution and used after it
-    double hv[NHOM];
-    {
-        const double* h = t.hom + ((size_t)min(m0 + w, a.M - 1) * K + kabs) * NHOM * N;
-#pragma unroll
-        for (int j = 0; j < NHOM; ++j) hv[j] = h[j * N + nr];
-    }
-    __syncthreads();
-    if constexpr (solve_twisted(NB, NW)) {  // right-hand side 32 w + (n & 31), waves 0 and 1
-        const int rh = 32 * w + (n & 31);
-        if (w < 2) {
-            __builtin_amdgcn_s_setprio(2);
-            if (rh < 6 * NSLOT) {
-                const int q = rh / 6, c = (rh >> 1) % 3;
-                if (slot_ok(q)) {
-                    const int m = mp * (m0 + (q >> 1));
-                    const int mu = c == 0 ? m + 1 : (c == 1 ? abs(m - 1) : m);
-                    lds_solve_tw<NB>(sF + (mu - mu_lo) * FWP, &sX[q][c][0].x + (rh & 1), n >> 5);
+            r0 = hs * r0;
+            r1 = hs * r1;
+            r2 = hs * r2;
+            if (n == N - 1) {
+                r0 = r1 = r2 = dcplx{0.0, 0.0};
+                if (zero && a.wall) {  // (0,0): Dirichlet values u_theta(1), u_z(1)
+                    const size_t w0 = (size_t)(K - 1) * 2, ws = (size_t)a.M * nk * 2;
+                    r0 = dcplx{a.wall[ws + w0], 0.0};
+                    r2 = dcplx{a.wall[2 * ws + w0], 0.0};
                 }
             }
-            __builtin_amdgcn_s_setprio(0);
-        }
-    } else if (w == 0) {
-        __builtin_amdgcn_s_setprio(2);
-        if (n < 6 * NSLOT) {
-            const int q = n / 6, c = (n >> 1) % 3;
-            if (slot_ok(q)) {
-                const int m = mp * (m0 + (q >> 1));
-                const int mu = c == 0 ? m + 1 : (c == 1 ? abs(m - 1) : m);
-                lds_solve<NB, NW>(sF + (mu - mu_lo) * FWP, &sX[q][c][0].x + (n & 1));
+            // (0,0) solves u_theta with H_1 in the + line and u_z with H_0
+            if (n < N) {
+                line(p, 0)[pad + n] = r0;
+                line(p, 1)[pad + n] = r1;
+                line(p, 2)[pad + n] = r2;
             }
         }
-        __builtin_amdgcn_s_setprio(0);
     }
-    __syncthreads();
-    // ---- influence matrix a = -A^{-1} g(u_b); fixed flux on (0,0) --------
-    if (w == 1 && m0 == 0 && kabs == 0) {  // (0,0): flux of u_z,b over the radial quadrature
-        double qs = n < N ? t.quad[n] * sX[0][2][n].x : 0.0;
+    request_influence();  // used after the solve
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_wave_barrier();
+    btd_solve<NT>(Dh, coup + te, coup + 16 * (2 * NT + 1 + 4 * ((blk < 2 ? m + 1 : m) & 1)) + te,
+                  &(X + (3 * mode + min(blk, 2)) * XS + ti)->x + part);
+    __builtin_amdgcn_wave_barrier();
+
+    // ---- influence matrix a = -A^{-1} g(u_b), lanes 32 s + 4 i + j for mode s;
+    //      fixed flux on (0,0)
+    double gamma = 0.0;
+    dcplx* const AV = X + 6 * XS;  // a of mode s at 4 s (the pressure lines are free)
+    if (zero) {  // flux of u_z,b over the radial quadrature
+        double qs = lane < N ? t.quad[lane] * X[2 * XS + pad + lane].x : 0.0;
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) qs += __shfl_xor(qs, o, 64);
-        if (n == 0) {
-            const double gamma = a.fixed_flux ? (0.25 - qs) * t.qG_inv : 0.0;
-            sGam = gamma;
-            if (a.beta_out) *a.beta_out = gamma * a.Re * 0.25;
+        gamma = a.fixed_flux ? (0.25 - qs) * t.qG_inv : 0.0;
+        if (lane == 0 && a.beta_out) *a.beta_out = gamma * a.Re * 0.25;
+    } else {
+        const dcplx* li = X + 3 * half * XS + pad + N - 1;  // the wall row of this half's mode
+        const int e = min(e16, W9 - 1) - (W9 - 1);
+        const dcplx sr = li[e] + li[XS + e];                // u+ + u- at the wall's stencil
+        const dcplx dw = {row_sum(wwall * sr.x), row_sum(wwall * sr.y)};
+        dcplx g0 = li[0], g1 = li[XS], g2 = li[2 * XS];
+        dcplx g3 = 0.5 * (dw + double(1 + m) * g0 + double(1 - m) * g1) + (half ? -kap0 : kap0) * ix(g2);  // r = 1
+        if (a.wall) {  // drive g to the wall velocity (b_r +- i b_theta, b_z, 0) instead of 0
+            const size_t wi = ((size_t)mi * nk + (K - 1 + (half ? -kabs : kabs))) * 2, ws = (size_t)a.M * nk * 2;
+            const dcplx br = {a.wall[wi], a.wall[wi + 1]}, bt = {a.wall[ws + wi], a.wall[ws + wi + 1]};
+            g0 = g0 - (br + ix(bt));
+            g1 = g1 - (br - ix(bt));
+            g2 = g2 - dcplx{a.wall[2 * ws + wi], a.wall[2 * ws + wi + 1]};
         }
+        const int j = lane & 3;
+        const dcplx pr = cm(Ai, j == 0 ? g0 : (j == 1 ? g1 : (j == 2 ? g2 : g3)));
+        const dcplx ai = {-quad_sum(pr.x), -quad_sum(pr.y)};
+        AV[4 * half + ((lane >> 2) & 3)] = ai;  // eight lanes hold and write the same value
     }
-    if (tid < NSLOT && slot_ok(tid)) {
-        const int q = tid;
-        const int mi = m0 + (q >> 1), m = mp * mi, k = slot_k(q);
-        if (m == 0 && k == 0) {
+    __builtin_amdgcn_wave_barrier();
+    // the weights again, for the vorticity (each use loads its own: held any
+    // longer they cost registers, which measured 3% slower)
+    W1o.load(t.d1, N, (m + 1) & 1, nr);
+    W1e.load(t.d1, N, m & 1, nr);
+    const bool mirror = mi == 0 && kabs > 0;  // m = 0: -k is the conjugate of +k
+    const size_t offc = mode_row(1) + n;
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        if (n >= N || (mode_of(p) && !two)) continue;
+        const size_t off = mode_row(mode_of(p)) + n;
+        dcplx up = line(p, 0)[pad + n], um = line(p, 1)[pad + n], uz = line(p, 2)[pad + n];
+        dcplx a1 = {0.0, 0.0};
+        if (zero) {
+            const double ut = up.x;
+            uz = dcplx{uz.x + gamma * t.green[n], 0.0};
+            up = dcplx{0.0, ut};
+            um = dcplx{0.0, -ut};
         } else {
-            const double kap = a.alpha * k;
-            const int e = N - 1, s0 = t.s0[e];
-            const double rinv = t.rinv[e];
-            const double* w1 = t.d1 + (((m + 1) & 1) * N + e) * W9;
-            const dcplx ap = stencil(w1, sX[q][0], s0) + (double(1 + m) * rinv) * sX[q][0][e];
-            const dcplx am = stencil(w1, sX[q][1], s0) + (double(1 - m) * rinv) * sX[q][1][e];
-            dcplx g[4] = {sX[q][0][e], sX[q][1][e], sX[q][2][e], 0.5 * (ap + am) + kap * ix(sX[q][2][e])};
-            if (a.wall) {  // drive g to the wall velocity (b_r +- i b_theta, b_z, 0) instead of 0
-                const size_t wi = ((size_t)mi * nk + (k + K - 1)) * 2, ws = (size_t)a.M * nk * 2;
-                const dcplx br = {a.wall[wi], a.wall[wi + 1]}, bt = {a.wall[ws + wi], a.wall[ws + wi + 1]};
-                g[0] = g[0] - (br + ix(bt));
-                g[1] = g[1] - (br - ix(bt));
-                g[2] = g[2] - dcplx{a.wall[2 * ws + wi], a.wall[2 * ws + wi + 1]};
-            }
-            const double* A = sAi[q];
-            dcplx av[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                dcplx acc = {0.0, 0.0};
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc = acc + cm(dcplx{A[2 * (4 * i + j)], A[2 * (4 * i + j) + 1]}, g[j]);
-                av[i] = dcplx{-acc.x, -acc.y};
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) reinterpret_cast<dcplx*>(sAi[q])[i] = av[i];
+            const double h1p = hv[0], h1m = hv[1], qv = hv[2], h2 = hv[3], h3 = hv[4], h4 = hv[5];
+            const dcplx* av = AV + 4 * mode_of(p);
+            a1 = av[0];
+            const dcplx a2 = av[1], a3 = av[2], a4 = av[3];
+            up = up + h1p * a1 + h2 * a2;
+            um = um + h1m * a1 + h3 * a3;
+            uz = uz - (kap_of(p) * qv) * ix(a1) + h4 * a4;  // h1: u_z = -i kappa q
         }
-    }
-    __syncthreads();
-    Row9 W1o, W1v;  // first-derivative weights of this lane's row, parities of m +- 1 and m (vorticity)
-    W1o.load(t.d1, N, (mw + 1) & 1, nr);
-    W1v.load(t.d1, N, mw & 1, nr);
-    if (n < N) {
+        if (a.p_out) {
+            const dcplx pp = zero ? dcplx{0.0, 0.0} : P[p] + hv[6] * a1;
+            store_c<double>(a.p_out, off, pp);
+            if (mirror) store_c<double>(a.p_out, offc, dcplx{pp.x, -pp.y});
+        }
+        // ---- output u (r, theta, z); omega from the stored components
+        const dcplx ur = 0.5 * (up + um), ut = 0.5 * dcplx{(up - um).y, -(up - um).x};
+        dcplx uo[3] = {ur, ut, uz};
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int q = 2 * w + j;
-            if (!slot_ok(q)) continue;
-            const int mi = m0 + (q >> 1), m = mp * mi, k = slot_k(q);
-            const size_t off = slot_off(q) + n;
-            const bool mirror = (mi == 0 && kabs > 0);  // m = 0: -k is the conjugate of +k
-            const size_t offc = ((size_t)mi * nk + (K - 1 - kabs)) * N + n;
-            dcplx up = sX[q][0][n], um = sX[q][1][n], uz = sX[q][2][n];
-            if (m == 0 && k == 0) {
-                const double ut = up.x;
-                uz = dcplx{uz.x + sGam * t.green[n], 0.0};
-                up = dcplx{0.0, ut};
-                um = dcplx{0.0, -ut};
-            } else {
-                const double kap = a.alpha * k;
-                const double h1p = hv[0], h1m = hv[1], qv = hv[2], h2 = hv[3], h3 = hv[4], h4 = hv[5], P1 = hv[6];
-                const dcplx* sa = reinterpret_cast<const dcplx*>(sAi[q]);
-                const dcplx a1 = sa[0], a2 = sa[1], a3 = sa[2], a4 = sa[3];
-                up = up + h1p * a1 + h2 * a2;
-                um = um + h1m * a1 + h3 * a3;
-                uz = uz - (kap * qv) * ix(a1) + h4 * a4;  // h1: u_z = -i kappa q
-                if (a.p_out) {
-                    const dcplx pp = load_c<double>(a.p_out, off) + P1 * a1;
-                    store_c<double>(a.p_out, off, pp);
-                    if (mirror) store_c<double>(a.p_out, offc, dcplx{pp.x, -pp.y});
-                }
+        for (int c = 0; c < 3; ++c) {
+            settle(uo[c]);
+            const dcplx uc = {uo[c].x, -uo[c].y};
+            if (a.u_out) {
+                store_c<double>(a.u_out, c * S + off, uo[c]);
+                if (mirror) store_c<double>(a.u_out, c * S + offc, uc);
             }
-            // ---- output u (r, theta, z); omega from the stored components
-            const dcplx ur = 0.5 * (up + um), ut = 0.5 * dcplx{(up - um).y, -(up - um).x};
-            const dcplx uo[3] = {ur, ut, uz};
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const dcplx uc = {uo[c].x, -uo[c].y};
-                if (a.u_out) {
-                    store_c<double>(a.u_out, c * S + off, uo[c]);
-                    if (mirror) store_c<double>(a.u_out, c * S + offc, uc);
-                }
-                if (a.u_out32) {
-                    store_c<float>(a.u_out32, c * S + off, uo[c]);
-                    if (mirror) store_c<float>(a.u_out32, c * S + offc, uc);
-                }
+            if (a.u_out32) {
+                store_c<float>(a.u_out32, c * S + off, uo[c]);
+                if (mirror) store_c<float>(a.u_out32, c * S + offc, uc);
             }
-            if (a.p_out && m == 0 && k == 0) store_c<double>(a.p_out, off, dcplx{0.0, 0.0});
             // omega is computed from (u_r, u_theta, u_z) as stored, so it
             // equals what the standalone vorticity kernel gives for the same state
-            sX[q][0][n] = ur;
-            sX[q][1][n] = ut;
-            sX[q][2][n] = uz;
+            line(p, c)[pad + n] = uo[c];
         }
     }
-    // the vorticity stencils read only this wave's own lines: a wave-level
-    // ordering suffices (no wait for the stores above)
     __builtin_amdgcn_wave_barrier();
     if (a.w_out && n < N) {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int q = 2 * w + j;
-            if (!slot_ok(q)) continue;
-            const int mi = m0 + (q >> 1), m = mp * mi, k = slot_k(q);
-            const bool mirror = (mi == 0 && kabs > 0);
+        for (int p = 0; p < PASSES; ++p) {
+            if (mode_of(p) && !two) continue;
+            const size_t off = mode_row(mode_of(p)) + n;
             dcplx wo[3];
-            curl_row(W1v.apply(sX[q][2], s0r), W1o.apply(sX[q][1], s0r), rinvr, m, a.alpha * k, sX[q][0][n],
-                     sX[q][1][n], sX[q][2][n], wo[0], wo[1], wo[2]);
-            const size_t off = slot_off(q) + n;
-            const size_t offc = ((size_t)mi * nk + (K - 1 - kabs)) * N + n;
+            curl_row(W1e.apply(line(p, 2), s0r), W1o.apply(line(p, 1), s0r), rinvr, m, kap_of(p), line(p, 0)[pad + n],
+                     line(p, 1)[pad + n], line(p, 2)[pad + n], wo[0], wo[1], wo[2]);
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 store_c<TNL>(a.w_out, c * S + off, wo[c]);
@@ -804,20 +560,15 @@ __device__ __forceinline__ void k_solve_body(const SolveArgs& a) {
     }
 }
 
-// Three workgroups (12 waves) per compute unit where the LDS allows it (all
-// but the last nine rows narrow: about 53 KB at NB = 64), so at most 168
-// VGPRs; otherwise two.
-constexpr int solve_waves(int NB, int NW) { return NW == NB - 9 ? 3 : 2; }
-template <typename TNL, int NB, int NW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(solve_waves(NB, NW), solve_waves(NB, NW))))
-void k_solve(SolveArgs a) {
-    k_solve_body<TNL, NB, NW>(a);
+// Three waves per SIMD: at most 168 VGPRs.
+template <typename TNL, int NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_solve(SolveArgs a) {
+    k_solve_body<TNL, NT>(a);
 }
-template <typename TNL, int NB, int NW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(solve_waves(NB, NW), solve_waves(NB, NW))))
-void k_solve_b(const SolveArgs* __restrict__ aa) {
+template <typename TNL, int NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_solve_b(const SolveArgs* __restrict__ aa) {
     // the member's record is read in place (a private copy would live in scratch)
-    k_solve_body<TNL, NB, NW>(aa[blockIdx.y]);
+    k_solve_body<TNL, NT>(aa[blockIdx.y]);
 }
 
 // Standalone vorticity of an external-layout state.  With a.mirror set
@@ -893,33 +644,36 @@ __global__ __launch_bounds__(256) void k_energy(AuxArgs a) {
 
 int default_gm(int mp) { return mp == 1 ? 4 : (mp <= 3 ? 2 : 1); }
 
+// A grid of at most one wave per compute unit is spread over all of them (24 x
+// 8 x 15 modes: 5.8 us against 6.2 with four waves to a workgroup, 41 x 18 x 23:
+// 8.1 against 8.4); beyond that neighbouring m gain more from sharing an L1
+// (48 x 32 x 63 modes, 1024 waves: 10.6 us against 11.5).
+int context_gm(int mp, int M, int K) { return M * K <= 256 ? 1 : default_gm(mp); }
+
 bool gm_ok(int gm, int mp) { return gm >= 1 && gm <= 4 && mp * (gm - 1) + 3 <= NFH; }
+
+template <int NT>
+static void launch_solve_nt(const SolveArgs& a, const SolveArgs* batch, int members, int precision, hipStream_t s,
+                            const KernelTiming& kt) {
+    const dim3 grid(a.K * ((a.M + a.gm - 1) / a.gm), batch ? members : 1), block(64 * a.gm);
+    const uint32_t lds = (uint32_t)solve_lds(NT, a.gm);
+    if (precision == OPF_MIXED) {
+        if (batch) hipLaunchKernelGGL((k_solve_b<float, NT>), grid, block, lds, s, batch);
+        else launch_timed((k_solve<float, NT>), grid, block, lds, s, kt, a);
+    } else {
+        if (batch) hipLaunchKernelGGL((k_solve_b<double, NT>), grid, block, lds, s, batch);
+        else launch_timed((k_solve<double, NT>), grid, block, lds, s, kt, a);
+    }
+}
 
 static hipError_t launch_solve_any(const SolveArgs& a, const SolveArgs* batch, int members, int precision,
                                    hipStream_t s, const KernelTiming& kt) {
-    const bool b = batch != nullptr;
-    const dim3 grid(a.K * ((a.M + a.gm - 1) / a.gm), b ? members : 1), block(256);
-    // NB rows and NW narrow rows as the factor images were written
-    // (solve_nb, solve_nw); the members of a batch share N and with it both
-#define OPF_SOLVE_LAUNCH(TNL, NB, NW)                                                   \
-    if (b) hipLaunchKernelGGL((k_solve_b<TNL, NB, NW>), grid, block, 0, s, batch); \
-    else launch_timed((k_solve<TNL, NB, NW>), grid, block, 0, s, kt, a);
-#define OPF_SOLVE_NW(TNL, NB)                                                       \
-    if (solve_nw(a.N, a.narrow) == NB - 9) { OPF_SOLVE_LAUNCH(TNL, NB, NB - 9) }   \
-    else if (solve_nw(a.N, a.narrow) == NB - 25) { OPF_SOLVE_LAUNCH(TNL, NB, NB - 25) } \
-    else { OPF_SOLVE_LAUNCH(TNL, NB, 0) }
-    if (solve_nb(a.N) == 32) {
-        if (precision == OPF_MIXED) { OPF_SOLVE_NW(float, 32) }
-        else { OPF_SOLVE_NW(double, 32) }
-    } else if (solve_nb(a.N) == 48) {
-        if (precision == OPF_MIXED) { OPF_SOLVE_NW(float, 48) }
-        else { OPF_SOLVE_NW(double, 48) }
-    } else {
-        if (precision == OPF_MIXED) { OPF_SOLVE_NW(float, 64) }
-        else { OPF_SOLVE_NW(double, 64) }
+    switch (btd_nt(a.N)) {  // the members of a batch share N
+#define OPF_CASE(V) case V: launch_solve_nt<V>(a, batch, members, precision, s, kt); break;
+        OPF_CASE(2) OPF_CASE(4) OPF_CASE(6) OPF_CASE(8) OPF_CASE(10) OPF_CASE(12) OPF_CASE(14)
+#undef OPF_CASE
+        default: return hipErrorInvalidValue;
     }
-#undef OPF_SOLVE_NW
-#undef OPF_SOLVE_LAUNCH
     return hipGetLastError();
 }
 

@@ -13,7 +13,8 @@
 //             coefficients are packed two real fields per complex line,
 //             inverse FFT over 3M points, u x omega at every point, forward
 //             FFT of (N_r + i N_t) and (N_z + i 0), unpacked and scaled by
-//             1/(9KM) into G[comp][n][m][z].  Physical fields never leave LDS.
+//             1/(9KM) into G[comp][n][m][z].  Physical fields never leave the
+//             compute unit.  k_theta_w does the same for larger grids.
 //   k_zfwd  : per (comp, m, 8 radial nodes): forward c2c over 3K points,
 //             |k| < K kept, written to the spectral layout.
 //
@@ -423,7 +424,7 @@ __device__ __forceinline__ void k_theta_lp_body(const NLArgs& a) {
     cpx<T> twr[RA];  // W_L^{jb r} (TWREG)
     if constexpr (TWREG) {
 #pragma unroll
-        for (int r = 1; r < RA; ++r) twr[r] = twg[(jb * r) % L];
+        for (int r = 1; r < RA; ++r) twr[r] = twg[jb * r];  // jb r < L
         __builtin_amdgcn_wave_barrier();  // pass A results: this wave's own line
     } else {
         __syncthreads();  // pass A results and tw2
@@ -510,6 +511,205 @@ __global__ __launch_bounds__(NT3) void k_theta_lp(NLArgs a) { k_theta_lp_body<T,
 template <typename T, int L, int TZ>
 __global__ __launch_bounds__(NT3) void k_theta_lp_b(const NLArgs* __restrict__ aa) {
     k_theta_lp_body<T, L, false, TZ>(aa[blockIdx.y]);  // ensemble members carry no forcing
+}
+
+// ---------------------------------------------------------------------------
+// k_theta_w: the theta stage of grids that fill the chip, per (n, TZW axial
+// points).  A thread (j, z), z fastest, carries all three packed lines of its
+// axial point one after the other, so the product is formed in its registers
+// and only the exchanges between radix passes go through LDS: 136 accesses per
+// thread (three lines) against 276 in k_theta_lp.  Every one of them and every
+// access to H and G covers 16 consecutive z (128 bytes in FP32, 256 in FP64),
+// and no lane idles where RA = RB.  Two exchange buffers in turn: one barrier
+// per exchange.  The next line is requested before the present one's second
+// pass.  FP64 reads its twiddles from LDS (in registers they spill).
+//
+// What bounds it: latency, at 6 (FP64, 226 VGPRs) and 12 (FP32) waves per
+// compute unit; its VALU work alone is 7 us at 64 x 144 x 192 points and its
+// bytes 12.7 (FP64) and 6.3 us (FP32) at the rate of a large copy.  Measured
+// there: 23.6 us in FP64 (k_theta_lp 26.0) and 13.6 in FP32 (17.9); 64 x 72 x
+// 192: 13.9 (18.4) and 7.8 (12.8); 48 x 96 x 96: 9.8 (12.0) in FP64.  Dropped:
+// three FP64 waves per SIMD with one exchange buffer (38 us, spills), four in
+// FP32 (17.6 us), loads requested just before their use (30.5 us FP64).
+//
+// The longer radix comes first: a thread then keeps the shorter one's points
+// of three lines (12 for 144 and 192, 8 for 96).
+constexpr int TZW = 16;
+template <int L>
+struct WideSplit {
+    static constexpr int RA = radix_max<L>(), RB = L / RA;
+};
+template <int L>
+constexpr int theta_w_threads() { return radix_max<L>() * TZW; }
+// Elements of one exchange buffer: output r of first-pass thread j sits at
+// r (R2 TZW + pad) + j TZW + z; the pad moves consecutive r by half the banks
+// in FP32, where a wave's 16 z fill only half of them.
+template <typename T>
+constexpr int theta_w_pad() { return sizeof(T) == 4 ? 16 : 0; }
+template <typename T, int L>
+constexpr int theta_w_buf() {
+    constexpr int RA = WideSplit<L>::RA, RB = WideSplit<L>::RB, P = theta_w_pad<T>();
+    return RA * (RB * TZW + P) > RB * (RA * TZW + P) ? RA * (RB * TZW + P) : RB * (RA * TZW + P);
+}
+template <typename T, int L>
+constexpr size_t theta_w_lds() { return (2 * (size_t)theta_w_buf<T, L>() + (sizeof(T) == 8 ? L : 0)) * sizeof(cpx<T>); }
+
+template <typename T, int L, bool ROT>
+__device__ __forceinline__ void k_theta_w_body(const NLArgs& a) {
+    constexpr int RA = WideSplit<L>::RA, RB = WideSplit<L>::RB, PAD = theta_w_pad<T>();
+    constexpr int M = L / 3;  // the theta line is the 3/2-padded length 3M
+    constexpr int SA = RB * TZW + PAD, SB = RA * TZW + PAD;  // stride between outputs: inverse, forward
+    extern __shared__ unsigned char smem_raw[];
+    cpx<T>* const E0 = reinterpret_cast<cpx<T>*>(smem_raw);
+    cpx<T>* const E1 = E0 + theta_w_buf<T, L>();
+    const int N = a.N, L3K = 3 * a.K;
+    const int nzt = (L3K + TZW - 1) / TZW;
+    const int n = blockIdx.x / nzt, z0 = (blockIdx.x % nzt) * TZW;
+    const int z = threadIdx.x % TZW, j = threadIdx.x / TZW;
+    const bool actA = RA == RB || j < RB;  // threads of the radix-RA passes (all take part in the radix-RB ones)
+    const size_t fstride = (size_t)N * M * L3K;
+    const cpx<T>* Hn = reinterpret_cast<const cpx<T>*>(a.H) + (size_t)n * M * L3K;  // uniform; lanes add 32-bit offsets
+    unsigned ho[RA];  // byte offset of this thread's bin j + r RB in a field's row n
+#pragma unroll
+    for (int r = 0; r < RA; ++r) {
+        const int bin = j + r * RB, mm = bin < M ? bin : L - bin;
+        ho[r] = (unsigned)(mm * L3K + min(z0 + z, L3K - 1)) * (unsigned)sizeof(cpx<T>);
+    }
+    auto at = [](const cpx<T>* base, unsigned bytes) {
+        return *reinterpret_cast<const cpx<T>*>(reinterpret_cast<const char*>(base) + bytes);
+    };
+    const cpx<T>* twg = reinterpret_cast<const cpx<T>*>(a.twt);  // W_L^t, t < L
+    cpx<T> A[RA], B[RA];
+    auto request = [&](int p) {  // fields 2p, 2p+1 at the bins j + r RB of this thread
+#pragma unroll
+        for (int r = 0; r < RA; ++r) {
+            const int bin = j + r * RB;
+            A[r] = B[r] = cpx<T>{T(0), T(0)};
+            if (actA && (bin < M || bin > L - M)) {
+                A[r] = at(Hn + 2 * p * fstride, ho[r]);
+                B[r] = at(Hn + (2 * p + 1) * fstride, ho[r]);
+            }
+        }
+    };
+    auto passA = [&](cpx<T>* E) {  // Z = A + i B on m >= 0, conj(A) + i conj(B) on bins L - m
+        cpx<T> v[RA];
+#pragma unroll
+        for (int r = 0; r < RA; ++r) {
+            const int bin = j + r * RB;
+            v[r] = bin < M ? cpx<T>{A[r].x - B[r].y, A[r].y + B[r].x} : cpx<T>{A[r].x + B[r].y, B[r].x - A[r].y};
+        }
+        dftn<T, RA, true>(v, +1);
+        if (actA) {
+#pragma unroll
+            for (int r = 0; r < RA; ++r) E[r * SA + j * TZW + z] = v[r];
+        }
+    };
+    constexpr bool TWL = sizeof(T) == 8;  // twiddles in LDS
+    cpx<T>* const twl = E1 + theta_w_buf<T, L>();
+    cpx<T> tw[RA];  // W_L^{j r}, j r < L: between the inverse passes r < RB, the forward ones r < RA
+    if constexpr (TWL) {
+        for (int t = threadIdx.x; t < L; t += theta_w_threads<L>()) twl[t] = twg[t];
+    } else {
+#pragma unroll
+        for (int r = 1; r < RB; ++r) tw[r] = twg[j * r];
+    }
+    auto twid = [&](int r, int jj) { if constexpr (TWL) return twl[jj * r]; else return tw[r]; };
+    auto passB = [&](const cpx<T>* E, cpx<T>* u) {  // theta points j + r RA
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+            const cpx<T> x = E[j * SA + r * TZW + z];
+            u[r] = r == 0 ? x : cmulc(x, twid(r, j));
+        }
+        dftn<T, RB, true>(u, +1);
+    };
+    cpx<T> u0[RB], u1[RB], u2[RB];
+    request(0);
+    passA(E0);
+    request(1);
+    __syncthreads();
+    passB(E0, u0);
+    passA(E1);
+    request(2);
+    __syncthreads();
+    passB(E1, u1);
+    passA(E0);
+    __syncthreads();
+    passB(E0, u2);
+    // u x omega at this thread's points: lines (u_r, u_theta), (u_z, w_r), (w_theta, w_z)
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        const T ur = u0[r].x, ut = u0[r].y, uz = u1[r].x, wr = u1[r].y, wt = u2[r].x, wz = u2[r].y;
+        T nr = ut * wz - uz * wt, nt = uz * wr - ur * wz, nz = ur * wt - ut * wr;
+        // W_L^{j + r RA} = W_L^j W_RB^r
+        if constexpr (ROT) add_coriolis<T>(a, cmul(twid(1, j), unit_root<T, RB>(r)), ur, ut, uz, nr, nt, nz);
+        u0[r] = {nr, nt};
+        u1[r] = {nz, T(0)};
+    }
+    // forward: pass A' (radix RB on the same points), pass B' (radix RA): bins j + r RB
+    auto passC = [&](cpx<T>* u, cpx<T>* E) {
+        dftn<T, RB, true>(u, -1);
+#pragma unroll
+        for (int r = 0; r < RB; ++r) E[r * SB + j * TZW + z] = u[r];
+    };
+    const int jc = actA ? j : 0;
+    if constexpr (RA != RB && !TWL) {
+#pragma unroll
+        for (int r = 1; r < RA; ++r) tw[r] = twg[jc * r];
+    }
+    auto passD = [&](const cpx<T>* E, cpx<T>* x) {
+#pragma unroll
+        for (int r = 0; r < RA; ++r) {
+            const cpx<T> y = E[jc * SB + r * TZW + z];
+            x[r] = r == 0 ? y : cmul(y, twid(r, jc));
+        }
+        dftn<T, RA, true>(x, -1);
+    };
+    cpx<T> x0[RA], x1[RA];
+    passC(u0, E1);
+    __syncthreads();
+    passC(u1, E0);
+    passD(E1, x0);
+    __syncthreads();
+    passD(E0, x1);
+    // the bins L - m, m = 1..M-1, go to their partners through E1 (its last
+    // readers have passed the barrier), line 0 at m, line 1 at M + m
+#pragma unroll
+    for (int r = 0; r < RA; ++r) {
+        const int m = L - (j + r * RB);
+        if ((r + 1) * RB > L - M + 1 && m < M && actA) {
+            E1[m * TZW + z] = x0[r];
+            E1[(M + m) * TZW + z] = x1[r];
+        }
+    }
+    __syncthreads();
+    // unpack the two output lines and store G (scaled by 1/(9KM))
+    cpx<T>* G = reinterpret_cast<cpx<T>*>(a.G) + (size_t)n * M * L3K;
+    auto put = [](cpx<T>* base, unsigned bytes, cpx<T> v) {
+        *reinterpret_cast<cpx<T>*>(reinterpret_cast<char*>(base) + bytes) = v;
+    };
+    const T h = T(0.5) * T(a.scale);
+#pragma unroll
+    for (int r = 0; r < RA; ++r) {
+        const int m = j + r * RB;
+        if (r * RB < M && m < M && actA && z0 + z < L3K) {
+            const cpx<T> Z0 = x0[r], Z1 = x1[r];
+            const cpx<T> Y0 = m == 0 ? Z0 : E1[m * TZW + z], Y1 = m == 0 ? Z1 : E1[(M + m) * TZW + z];
+            // A = (Z + conj Y)/2 -> N_r, B = (Z - conj Y)/(2i) -> N_t; the second line N_z
+            put(G, ho[r], {h * (Z0.x + Y0.x), h * (Z0.y - Y0.y)});
+            put(G + fstride, ho[r], {h * (Z0.y + Y0.y), h * (Y0.x - Z0.x)});
+            put(G + 2 * fstride, ho[r], {h * (Z1.x + Y1.x), h * (Z1.y - Y1.y)});
+        }
+    }
+}
+template <typename T>
+constexpr int theta_w_waves() { return sizeof(T) == 4 ? 3 : 2; }  // per SIMD: 168 or 256 VGPRs
+template <typename T, int L, bool ROT>
+__global__ __launch_bounds__((theta_w_threads<L>())) __attribute__((amdgpu_waves_per_eu(theta_w_waves<T>(), theta_w_waves<T>())))
+void k_theta_w(NLArgs a) { k_theta_w_body<T, L, ROT>(a); }
+template <typename T, int L>
+__global__ __launch_bounds__((theta_w_threads<L>())) __attribute__((amdgpu_waves_per_eu(theta_w_waves<T>(), theta_w_waves<T>())))
+void k_theta_w_b(const NLArgs* __restrict__ aa) {
+    k_theta_w_body<T, L, false>(aa[blockIdx.y]);  // ensemble members carry no forcing
 }
 
 // ---------------------------------------------------------------------------
@@ -735,6 +935,26 @@ static void launch_theta(const NLArgs& a, const NLArgs* batch, int members, hipS
     }
 }
 
+// The wide theta kernel from one of its workgroups per compute unit on (with
+// fewer, the three lines side by side in k_theta_lp finish sooner: 41 x 54 x 36
+// points, 123 workgroups, 5.6 us against 6.1; 53 x 108 x 72, 265 workgroups,
+// 8.1 against 7.9).  Lines of 192 in FP64 need more registers than two waves
+// per SIMD have (65 us against 36 at 64 x 192 x 192).  The rule looks at one
+// member's grid only: the members of a batch and single runs take one path.
+template <typename T, int L>
+static bool launch_theta_wide(const NLArgs& a, const NLArgs* batch, int members, hipStream_t s, const KernelTiming& kt) {
+    if constexpr (sizeof(T) == 4 || L < 192) {
+        const int blocks = a.N * ((3 * a.K + TZW - 1) / TZW);
+        if (blocks < 256) return false;
+        const dim3 g(blocks, batch ? members : 1), b(theta_w_threads<L>());
+        if (batch) hipLaunchKernelGGL((k_theta_w_b<T, L>), g, b, (theta_w_lds<T, L>()), s, batch);
+        else if (a.rotating) launch_timed((k_theta_w<T, L, true>), g, b, (theta_w_lds<T, L>()), s, kt, a);
+        else launch_timed((k_theta_w<T, L, false>), g, b, (theta_w_lds<T, L>()), s, kt, a);
+        return true;
+    }
+    return false;
+}
+
 template <typename TS, typename T>
 static hipError_t launch_typed(const NLArgs& a, const NLArgs* batch, int members, int stage, hipStream_t s,
                                const KernelTiming& kt = KernelTiming{}) {
@@ -744,6 +964,7 @@ static hipError_t launch_typed(const NLArgs& a, const NLArgs* batch, int members
         switch (L3M) {
 #define OPF_CASE(V)                                                        \
     case V:                                                                \
+        if (launch_theta_wide<T, V>(a, batch, members, s, kt)) break;        \
         if (a.tz == 2) launch_theta<T, V, 2>(a, batch, members, s, kt);      \
         else if (a.tz == 4) launch_theta<T, V, 4>(a, batch, members, s, kt); \
         else launch_theta<T, V, 8>(a, batch, members, s, kt);                \

@@ -13,7 +13,7 @@
 // v_mfma_f32_32x32x16_bf16: the forward pass takes B = W, the input gradient
 // takes B = W^T (a transposed bfloat16 copy kept beside each weight), and the
 // weight gradient takes A = dZ^T, B = H^T (transposed activations written by
-// the epilogues of the forward and backward GEMMs).
+// the chains that take a tile of rows through the residual layers).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -29,6 +29,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t bf16_t;  // storage of one bfloat16 value
 
@@ -44,41 +45,15 @@ __host__ __device__ inline bf16_t f2bf(float f) {
     return (bf16_t)(u >> 16);
 }
 
-enum { EPI_PLAIN = 0, EPI_RELU_RES = 1, EPI_ADD = 2 };
-
-// What the GEMM epilogue does with v = acc (+ bias[col]):
-//   zout <- v;  v <- res + relu(v) (RELU_RES) or res + v (ADD);  out <- v;
-//   w = v, or 0 where mask <= 0;  outb[row][col] <- bf16(w);  outT[col][row] <- bf16(w).
-// Every pointer may be null (that store is skipped).
+// Where the GEMM epilogue puts v = acc (+ bias[col]): out[row][col].
 struct Epi {
-    const float* bias;
-    float* zout;
-    int ldz;
-    int mode;
-    const float* res;
-    int ldr;
+    const float* bias;  // may be null
     float* out;
     int ldo;
-    const float* mask;
-    int ldm;
-    bf16_t* outb;
-    int ldb;
-    bf16_t* outT;
-    int ldt;
 };
 
 __device__ __forceinline__ void epilogue(const Epi& e, int row, int col, float s) {
-    float v = s + (e.bias ? e.bias[col] : 0.0f);
-    if (e.zout) e.zout[(size_t)row * e.ldz + col] = v;
-    if (e.mode == EPI_RELU_RES)
-        v = e.res[(size_t)row * e.ldr + col] + fmaxf(v, 0.0f);
-    else if (e.mode == EPI_ADD)
-        v = e.res[(size_t)row * e.ldr + col] + v;
-    if (e.out) e.out[(size_t)row * e.ldo + col] = v;
-    float w = v;
-    if (e.mask && !(e.mask[(size_t)row * e.ldm + col] > 0.0f)) w = 0.0f;
-    if (e.outb) e.outb[(size_t)row * e.ldb + col] = f2bf(w);
-    if (e.outT) e.outT[(size_t)col * e.ldt + row] = f2bf(w);
+    e.out[(size_t)row * e.ldo + col] = s + (e.bias ? e.bias[col] : 0.0f);
 }
 
 // C[rows][cols] = A[rows][K] B[cols][K]^T on v_mfma_f32_32x32x16_bf16.
@@ -93,14 +68,13 @@ __device__ __forceinline__ void epilogue(const Epi& e, int row, int col, float s
 // gridDim.z ranges of kc, workgroup z writes its raw partial tile to
 // part[z][rows][cols] for k_gemm_reduce.
 // Requires rows, cols multiples of 32, K and kc of 16, lda, ldb multiples of 8.
-__global__ __launch_bounds__(256) void k_gemm(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B,
-                                              int ldb, int K, int kc, Epi e, float* __restrict__ part) {
+template <typename Store>
+__device__ __forceinline__ void gemm_tile(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B, int ldb,
+                                          int m0, int n0, int kb, int ke, Store store) {
     __shared__ float red[4][16][64];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
     const int rr = lane & 31, kq = (lane >> 5) * 8;
-    const int kb = blockIdx.z * kc, ke = min(K, kb + kc);
     f32x16 acc = {};
     const bf16_t* ap = A + (size_t)(m0 + rr) * lda + kq;
     const bf16_t* bp = B + (size_t)(n0 + rr) * ldb + kq;
@@ -122,17 +96,21 @@ __global__ __launch_bounds__(256) void k_gemm(const bf16_t* __restrict__ A, int 
 #pragma unroll
     for (int i = 0; i < 16; ++i) red[wv][i][lane] = acc[i];
     __syncthreads();
-    const int cols = gridDim.x * GT, rows = gridDim.y * GT;
     for (int q = threadIdx.x; q < 1024; q += 256) {
         const int i = q >> 6, l = q & 63;
         const float s = ((red[0][i][l] + red[1][i][l]) + red[2][i][l]) + red[3][i][l];
-        const int row = m0 + 8 * (i >> 2) + 4 * (l >> 5) + (i & 3);
-        const int col = n0 + (l & 31);
+        store(m0 + 8 * (i >> 2) + 4 * (l >> 5) + (i & 3), n0 + (l & 31), s);
+    }
+}
+__global__ __launch_bounds__(256) void k_gemm(const bf16_t* __restrict__ A, int lda, const bf16_t* __restrict__ B,
+                                              int ldb, int K, int kc, Epi e, float* __restrict__ part) {
+    const int kb = blockIdx.z * kc, cols = gridDim.x * GT, rows = gridDim.y * GT;
+    gemm_tile(A, lda, B, ldb, blockIdx.y * GT, blockIdx.x * GT, kb, min(K, kb + kc), [&](int row, int col, float s) {
         if (part)
             part[((size_t)blockIdx.z * rows + row) * cols + col] = s;
         else
             epilogue(e, row, col, s);
-    }
+    });
 }
 
 // The same product for large shapes: one 128 x 128 tile of C per workgroup,
@@ -220,6 +198,11 @@ __global__ __launch_bounds__(256) void k_gemm128(const bf16_t* __restrict__ A, i
             }
 }
 
+// Products k_gemm128 takes.
+inline bool large_product(int rows, int cols, int K) {
+    return rows % G2 == 0 && cols % G2 == 0 && K % GK2 == 0 && (double)rows * cols * K >= (double)(1L << 30);
+}
+
 // Sum of the split partial tiles in order, then the epilogue.
 __global__ void k_gemm_reduce(const float* __restrict__ part, int rows, int cols, int nsplit, Epi e) {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -290,99 +273,431 @@ __global__ __launch_bounds__(256) void k_loss(float* __restrict__ y, const float
     if (lane == 0) lrow[row] = w * acc;
 }
 
-// *out = sum_r lrow[r] / *wsum, rows < n; one workgroup.
-__global__ __launch_bounds__(256) void k_loss_total(const float* __restrict__ lrow, int n,
-                                                    const float* __restrict__ wsum, float* out) {
-    __shared__ float part[4];
-    float s = 0.0f;
-    for (int i = threadIdx.x; i < n; i += 256) s += lrow[i];
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) *out = (((part[0] + part[1]) + part[2]) + part[3]) / *wsum;
-}
-
-// Column sums in two passes (bias gradients):
-// part[c][col] = sum over rows c*ch .. c*ch+ch-1 (< rows) of src[row][col]
-// (times [mask > 0] when mask is given), 32 columns x 8 row groups per
-// workgroup; then out[col] = sum_c part[c][col] in order.  Deterministic.
-constexpr int CS_CHUNKS = 64;  // largest number of row chunks
+constexpr int CS_CHUNKS = 64;  // largest number of row chunks of a column sum
 constexpr int GSPLIT = 8;                     // largest K split of a GEMM
 constexpr size_t GPART = (size_t)1 << 23;     // floats of split partial tiles (split x rows x cols)
-__global__ __launch_bounds__(256) void k_colsum_part(const float* __restrict__ src, const float* __restrict__ mask,
-                                                     int rows, int ld, int ch, float* __restrict__ part) {
-    __shared__ float red[8][32];
-    const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
-    const int col = blockIdx.x * 32 + c;
-    const int r0 = blockIdx.y * ch, r1 = min(rows, r0 + ch);
-    float s = 0.0f;
-    for (int r = r0 + g; r < r1; r += 8) {
-        const size_t i = (size_t)r * ld + col;
-        const float v = src[i];
-        s += (!mask || mask[i] > 0.0f) ? v : 0.0f;
-    }
-    red[g][c] = s;
-    __syncthreads();
-    if (g == 0) {
-        float t = 0.0f;
-        for (int q = 0; q < 8; ++q) t += red[q][c];
-        part[(size_t)blockIdx.y * ld + col] = t;
-    }
-}
-__global__ void k_colsum_fin(const float* __restrict__ part, int nch, int ld, float* __restrict__ out) {
-    const int col = blockIdx.x * 256 + threadIdx.x;
-    if (col >= ld) return;
-    float t = 0.0f;
-    for (int c = 0; c < nch; ++c) t += part[(size_t)c * ld + col];
-    out[col] = t;
-}
 
 // Parameter segments: weight matrices [rows][cols] and bias vectors.
 struct Segs {
     int n;
     long off[MAXSEG + 1];
-    int rows[MAXSEG], cols[MAXSEG], mat[MAXSEG];
+    int rows[MAXSEG], cols[MAXSEG], mat[MAXSEG];  // mat: 0 bias, 1 weights, 2 weights of a residual layer
+    int blk[MAXSEG + 1];                          // first workgroup of the segment (k_adam, k_refresh)
 };
 
-__device__ inline int seg_of(const Segs& s, long i) {
+// bfloat16 weights of a residual layer [n][k], k < H, as the operand requests
+// of a chain read them: 32 x 16 tiles of 1 KB, entry (n, k) of a tile with
+// lane n + 32 (k / 8), element k % 8, so that a wave's request of 16 bytes a
+// lane is 1 KB in a row (row-major weights give 32 pieces of 32 bytes; the
+// chains took 25.7 and 31.8 us then, 1536 rows x 256 x 4 layers).
+__host__ __device__ inline long frag_at(int n, int k, int H) {
+    return ((long)(n / 32) * (H / 16) + k / 16) * 512 + (n % 32 + 32 * (k % 16 / 8)) * 8 + k % 8;
+}
+
+// One workgroup of k_adam and k_refresh: 64 x 32 parameters of a weight
+// matrix, or 2048 of a bias.  A matrix tile's bfloat16 copies wb ([rows][cols]
+// at the parameter offset) and wt ([cols][rows], through LDS) are written in
+// runs of 64 and 128 bytes, both in frag_at's order for a residual layer.
+// step(i) returns the new values of parameters i..i+3.
+constexpr int PT = 64;  // rows of a tile
+template <typename Step>
+__device__ __forceinline__ void param_tile(const Segs& s, bf16_t* __restrict__ wb, bf16_t* __restrict__ wt, Step step) {
+    __shared__ bf16_t tile[32][PT + 4];
     int j = 0;
-    while (j + 1 < s.n && i >= s.off[j + 1]) ++j;
-    return j;
+    while (j + 1 < s.n && (int)blockIdx.x >= s.blk[j + 1]) ++j;
+    const int b = blockIdx.x - s.blk[j], t = threadIdx.x;
+    const long off = s.off[j];
+    if (!s.mat[j]) {
+        for (int i = b * 2048 + 4 * t; i < min(s.cols[j], (b + 1) * 2048); i += 1024) step(off + i);
+        return;
+    }
+    const int rows = s.rows[j], cols = s.cols[j];
+    const int r0 = b / (cols / 32) * PT, c0 = b % (cols / 32) * 32;
+    const int c = 4 * (t & 7);
+#pragma unroll
+    for (int h = 0; h < PT; h += 32) {
+        const int r = r0 + h + (t >> 3);
+        if (r >= rows) break;  // rows is a multiple of 32
+        const long i = off + (long)r * cols + c0 + c;
+        const f32x4 p = step(i);
+        bf16_t v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) tile[c + q][h + (t >> 3)] = v[q] = f2bf(p[q]);
+        uint2 u;
+        u.x = (uint32_t)v[0] | ((uint32_t)v[1] << 16);
+        u.y = (uint32_t)v[2] | ((uint32_t)v[3] << 16);
+        *reinterpret_cast<uint2*>(wb + (s.mat[j] == 2 ? off + frag_at(r, c0 + c, cols) : i)) = u;
+    }
+    __syncthreads();
+    const int rq = 4 * (t & 15);
+    if (r0 + rq >= rows) return;
+#pragma unroll
+    for (int q = t >> 4; q < 32; q += 16) {
+        const uint2 u = *reinterpret_cast<const uint2*>(&tile[q][rq]);
+        const long at = s.mat[j] == 2 ? frag_at(c0 + q, r0 + rq, rows) : (long)(c0 + q) * rows + r0 + rq;
+        *reinterpret_cast<uint2*>(wt + off + at) = u;
+    }
 }
 
-// bfloat16 copies of the weights: wb [rows][cols] at the parameter offset,
-// wt [cols][rows] at the same offset.
-__device__ inline void store_copies(const Segs& s, long i, float p, bf16_t* wb, bf16_t* wt) {
-    const int j = seg_of(s, i);
-    if (!s.mat[j]) return;
-    const long loc = i - s.off[j];
-    const int r = (int)(loc / s.cols[j]), c = (int)(loc % s.cols[j]);
-    const bf16_t b = f2bf(p);
-    wb[i] = b;
-    wt[s.off[j] + (long)c * s.rows[j] + r] = b;
+__global__ __launch_bounds__(256) void k_refresh(const float* __restrict__ p, Segs s, bf16_t* wb, bf16_t* wt) {
+    param_tile(s, wb, wt, [&](long i) { return *reinterpret_cast<const f32x4*>(p + i); });
 }
 
-__global__ void k_refresh(const float* __restrict__ p, long n, Segs s, bf16_t* wb, bf16_t* wt) {
+// The residual layers, forward and backward, run as chains: a workgroup keeps
+// 32 rows and takes them through all layers, so a layer costs one barrier
+// instead of a launch (1536 rows x 256 x 4 layers, the mode rows of a
+// 48 x 24 x 32 grid: a launch per layer and direction took 7.2..9.5 us, the
+// chains 16.4 and 24.2 us for all layers).  The FP32 residual stays in the
+// registers of the lane that owns the entry, the bfloat16 operand goes
+// through a double-buffered LDS tile (rows padded by 16 bytes, so that the
+// 16-byte operand reads of 16 consecutive lanes hit distinct banks), and the
+// weights, which do not depend on the rows, are requested one tile ahead
+// straight into operand registers.  Each wave owns a 32 x 32 tile: its
+// four accumulators take the 16-wide K slices s = 0..3 mod 4 and are added in
+// that order, which is the sum of k_gemm's four waves.  Few rows leave most
+// of the chip idle; what bounds a chain there is the latency of a layer.
+// WIDE (H > 256): up to 16 waves of 128 registers, which hold one accumulator
+// and 8 slices.  FULL: every slice of every chunk exists.
+template <bool WIDE>
+constexpr int chain_waves() { return WIDE ? 16 : 8; }  // at most: a 32 x 32 tile each
+
+__device__ __forceinline__ void lds_barrier() {  // orders LDS only: requests and stores stay in flight
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Where a lane's 16 entries of a tile lie, and the operand requests.
+template <bool WIDE, bool FULL>
+struct Chain {
+    static constexpr int SC = WIDE ? 8 : 16, KC = 16 * SC, NC = WIDE ? 4 : 1;  // K chunks of a tile
+    static constexpr int NA = WIDE ? 1 : 4;                                    // accumulators
+    int lane, rr, kq, wv, H, HS;
+    uint32_t off;
+    u32x4 b[SC];  // one chunk of the weights, requested ahead
+    __device__ __forceinline__ Chain(int H_)
+        : lane(threadIdx.x & 63), rr(lane & 31), kq((lane >> 5) * 8),
+          wv(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)), H(H_), HS(H_ + 8), off(4 * (lane >> 5) * H_ + wv * 32 + rr) {}
+    __device__ __forceinline__ int col() const { return wv * 32 + rr; }
+    // entry i of the tile lies in row row0(i) + 4 (lane / 32), column col():
+    // at(x, i)[off] for x the first of the workgroup's rows (one offset per
+    // lane from a pointer per i that all lanes share)
+    static __device__ __forceinline__ constexpr int row0(int i) { return 8 * (i >> 2) + (i & 3); }
+    template <typename T> __device__ __forceinline__ T* at(T* x, int i) const { return x + (size_t)row0(i) * H; }
+    __device__ __forceinline__ void fetch(const bf16_t* __restrict__ w, int c) {
+        const bf16_t* p = w + ((size_t)wv * (H / 16) + c * SC) * 512 + lane * 8;
+#pragma unroll
+        for (int i = 0; i < SC; ++i)
+            if (FULL || c * KC + 16 * i < H) b[i] = *reinterpret_cast<const u32x4*>(p + 512 * i);
+    }
+    __device__ __forceinline__ void multiply(const bf16_t* hs, int c, f32x16* acc) const {
+        const bf16_t* p = hs + rr * HS + kq;
+#pragma unroll
+        for (int i = 0; i < SC; ++i)
+            if (FULL || c * KC + 16 * i < H)
+                acc[i % NA] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                    *reinterpret_cast<const bf16x8*>(p + c * KC + 16 * i), __builtin_bit_cast(bf16x8, b[i]), acc[i % NA], 0, 0, 0);
+    }
+    __device__ __forceinline__ float sum(const f32x16* acc, int i) const {
+        if constexpr (WIDE) return acc[0][i];
+        else return ((acc[0][i] + acc[1][i]) + acc[2][i]) + acc[3][i];
+    }
+    // the bfloat16 entries w[16] of the tile: into the LDS tile and, transposed, to dst[col][m0 + row]
+    __device__ __forceinline__ void publish(const float* w, bf16_t* hs, bf16_t* dst, int R, int m0) const {
+        const int hi = 4 * (lane >> 5), cc = col();
+        const uint32_t to = (uint32_t)cc * R + hi;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            bf16_t h[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                h[i] = f2bf(w[4 * g + i]);
+                if (hs) hs[(hi + row0(4 * g + i)) * HS + cc] = h[i];
+            }
+            if (dst) {
+                uint2 u;
+                u.x = (uint32_t)h[0] | ((uint32_t)h[1] << 16);
+                u.y = (uint32_t)h[2] | ((uint32_t)h[3] << 16);
+                *reinterpret_cast<uint2*>((dst + m0 + 8 * g) + to) = u;
+            }
+        }
+    }
+};
+
+struct ChainArgs {
+    const bf16_t* X;  // [rows][NCOND]
+    const bf16_t* W;  // bfloat16 weights: Wb forward, Wt backward
+    const float* P;   // parameters (biases)
+    long woff[MAXL + 1], boff[MAXL + 1];
+    int H, L, R, rows;
+    float* Z;      // [L][R][H] pre-activations (forward, training only: else null; backward: read)
+    bf16_t* HT;    // [L + 1][H][R] transposed activations (training only, else null)
+    bf16_t* HL;    // [R][H] activations of the last layer
+    const float* src;  // backward: dL/dh_L as nsplit partial products [rows][H], stride floats apart
+    size_t stride;
+    int nsplit;
+    float* D;    // [L + 1][R][H] dL/dh_l
+    bf16_t* DT;  // [L + 1][H][R] dL/dh_l where z_{l-1} > 0 (all of it for l = 0), transposed
+};
+
+// h_0 = W_in x + b_in; z_l = W_l h_l + b_l; h_{l+1} = h_l + relu(z_l).
+template <bool WIDE, bool FULL>
+__global__ __launch_bounds__(64 * chain_waves<WIDE>()) __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : 2, WIDE ? 4 : 2)))
+void k_chain_fwd(ChainArgs a) {
+    extern __shared__ __attribute__((aligned(16))) bf16_t hsm16[];
+    Chain<WIDE, FULL> q(a.H);
+    const int H = a.H, m0 = blockIdx.x * 32, buf = 32 * q.HS;
+    const size_t RH = (size_t)a.R * H;
+    q.fetch(a.W + a.woff[1], 0);
+    float res[16];
+    {
+        const bf16_t* ap = a.X + (size_t)(m0 + q.rr) * NCOND + q.kq;
+        const bf16_t* bp = a.W + a.woff[0] + (size_t)q.col() * NCOND + q.kq;
+        f32x16 acc[2] = {};
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(ap + 16 * i),
+                                                             *reinterpret_cast<const bf16x8*>(bp + 16 * i), acc[i], 0, 0, 0);
+        const float bias = a.P[a.boff[0] + q.col()];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) res[i] = (acc[0][i] + acc[1][i]) + bias;
+        q.publish(res, hsm16, a.HT, a.R, m0);
+    }
+    lds_barrier();
+    for (int l = 0; l < a.L; ++l) {
+        const bf16_t* in = hsm16 + (l & 1) * buf;
+        bf16_t* out = hsm16 + ((l + 1) & 1) * buf;
+        const float bias = a.P[a.boff[l + 1] + q.col()];
+        f32x16 acc[q.NA] = {};
+#pragma unroll
+        for (int c = 0; c < q.NC; ++c) {
+            q.multiply(in, c, acc);
+            if (c + 1 < q.NC) q.fetch(a.W + a.woff[l + 1], c + 1);
+            else if (l + 1 < a.L) q.fetch(a.W + a.woff[l + 2], 0);
+        }
+        float z[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            z[i] = q.sum(acc, i) + bias;
+            res[i] += fmaxf(z[i], 0.0f);
+        }
+        if (a.HT) {
+            float* zp = a.Z + (size_t)l * RH + (size_t)m0 * H;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) q.at(zp, i)[q.off] = z[i];
+        }
+        q.publish(res, out, a.HT ? a.HT + (size_t)(l + 1) * RH : nullptr, a.R, m0);
+        lds_barrier();
+    }
+    const bf16_t* h = hsm16 + (a.L & 1) * buf;
+    for (int i = threadIdx.x; i < 4 * H; i += blockDim.x) {  // 16 bytes each
+        const int r = i / (H / 8), c = (i - r * (H / 8)) * 8;
+        *reinterpret_cast<u32x4*>(a.HL + (size_t)(m0 + r) * H + c) = *reinterpret_cast<const u32x4*>(h + r * q.HS + c);
+    }
+}
+
+// D_L = the sum of src's partial products; dz_l = D_{l+1} where z_l > 0;
+// D_l = D_{l+1} + W_l^T dz_l.
+template <bool WIDE, bool FULL>
+__global__ __launch_bounds__(64 * chain_waves<WIDE>()) __attribute__((amdgpu_waves_per_eu(WIDE ? 4 : 2, WIDE ? 4 : 2)))
+void k_chain_bwd(ChainArgs a) {
+    extern __shared__ __attribute__((aligned(16))) bf16_t hsm16[];
+    Chain<WIDE, FULL> q(a.H);
+    const int H = a.H, L = a.L, m0 = blockIdx.x * 32, buf = 32 * q.HS;
+    const size_t RH = (size_t)a.R * H, at = (size_t)m0 * H;
+    q.fetch(a.W + a.woff[L], 0);
+    float res[16], zm[16], w[16];
+    auto mask = [&](int l) {  // request z_l
+        const float* zp = a.Z + (size_t)l * RH + at;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) zm[i] = q.at(zp, i)[q.off];
+    };
+    mask(L - 1);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) res[i] = 0.0f;
+#pragma unroll 2
+    for (int p = 0; p < a.nsplit; ++p)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) res[i] += q.at(a.src + (size_t)p * a.stride + at, i)[q.off];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        q.at(a.D + (size_t)L * RH + at, i)[q.off] = res[i];
+        w[i] = zm[i] > 0.0f ? res[i] : 0.0f;
+    }
+    q.publish(w, hsm16, a.DT + (size_t)L * RH, a.R, m0);
+    lds_barrier();
+    for (int l = L - 1; l >= 0; --l) {
+        const bf16_t* in = hsm16 + ((L - 1 - l) & 1) * buf;
+        bf16_t* out = hsm16 + ((L - l) & 1) * buf;
+        mask(l > 0 ? l - 1 : 0);
+        f32x16 acc[q.NA] = {};
+#pragma unroll
+        for (int c = 0; c < q.NC; ++c) {
+            q.multiply(in, c, acc);
+            if (c + 1 < q.NC) q.fetch(a.W + a.woff[l + 1], c + 1);
+            else if (l > 0) q.fetch(a.W + a.woff[l], 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            res[i] += q.sum(acc, i);
+            q.at(a.D + (size_t)l * RH + at, i)[q.off] = res[i];
+            w[i] = l == 0 || zm[i] > 0.0f ? res[i] : 0.0f;
+        }
+        q.publish(w, l > 0 ? out : nullptr, a.DT + (size_t)l * RH, a.R, m0);
+        lds_barrier();
+    }
+}
+
+// What is left of the gradients once the chain has run, in one launch of
+// independent workgroups and one that adds their partial sums (a launch each
+// cost 4.5 us or more at 1536 rows, whatever it did; 31 in all):
+//  - the first ngemm workgroups: 32 x 32 tiles of the weight gradients of the
+//    input layer and of nhid residual layers, dW = DT HT^T with K = rows split
+//    over nsplit ranges of kc, raw partial tiles to gpart[split][parameter];
+//  - then the column sums over row chunks of ch (32 columns x 8 row groups
+//    per workgroup, part[chunk][column]): columns of dL/dY, then of D_l where
+//    z_{l-1} > 0 (D_0: all), l = 0..L;
+//  - the last workgroup: the loss, *loss = sum_r lrow[r] / (*wsum or count).
+struct GradArgs {
+    const bf16_t *DT, *HT, *XT;
+    const float *D, *Z, *Y;
+    long woff[MAXL + 1];
+    int H, L, R, dout, rows;
+    int nhid, nsplit, kc, ngemm;
+    int ch, nch;
+    float* gpart;
+    long nph;  // parameters before the output layer's
+    float* part;
+    const float *lrow, *wsum;
+    float count;
+    int nlive;
+    float* loss;
+    // for k_grad_sum
+    float* G;
+    long wout, bout;
+    int osplit;          // partial products of the output layer's weight gradient in opart (0: already in G)
+    const float* opart;  // [osplit][dout][H]
+};
+
+__global__ __launch_bounds__(256) void k_grad_parts(GradArgs a) {
+    const int H = a.H, R = a.R, th = H / GT;
+    int b = blockIdx.x;
+    if (b < a.ngemm) {
+        const int z = b % a.nsplit, kb = z * a.kc, ke = min(a.rows, kb + a.kc);
+        b /= a.nsplit;
+        const bf16_t *A = a.DT, *B = a.XT;
+        long off = a.woff[0];
+        int m0 = b * GT, n0 = 0, ldc = NCOND;
+        if (b >= th) {  // (the input layer's th tiles come first)
+            b -= th;
+            const int l = b / (th * th);
+            b -= l * th * th;
+            m0 = b / th * GT, n0 = b % th * GT, ldc = H;
+            A = a.DT + (size_t)(l + 1) * H * R;
+            B = a.HT + (size_t)l * H * R;
+            off = a.woff[l + 1];
+        }
+        float* out = a.gpart + (size_t)z * a.nph + off;
+        gemm_tile(A, R, B, R, m0, n0, kb, ke, [&](int row, int col, float s) { out[(size_t)row * ldc + col] = s; });
+        return;
+    }
+    b -= a.ngemm;
+    const int ncol = a.dout + (a.L + 1) * H;
+    __shared__ float red[8][32];
+    if (b < a.nch * (ncol / 32)) {
+        const int cb = b % (ncol / 32), k = b / (ncol / 32);
+        const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
+        const float *src = a.Y, *mask = nullptr;
+        int col = cb * 32, ld = a.dout;
+        if (col >= a.dout) {
+            const int l = (col - a.dout) / H;
+            col -= a.dout + l * H;
+            ld = H;
+            src = a.D + (size_t)l * R * H;
+            if (l > 0) mask = a.Z + (size_t)(l - 1) * R * H;
+        }
+        const int r1 = min(a.rows, (k + 1) * a.ch);
+        float s = 0.0f;
+#pragma unroll 4
+        for (int r = k * a.ch + g; r < r1; r += 8) {
+            const size_t i = (size_t)r * ld + col + c;
+            const float v = src[i];
+            s += (!mask || mask[i] > 0.0f) ? v : 0.0f;
+        }
+        red[g][c] = s;
+        __syncthreads();
+        if (g == 0) {
+            float t = 0.0f;
+            for (int r = 0; r < 8; ++r) t += red[r][c];
+            a.part[(size_t)k * ncol + cb * 32 + c] = t;
+        }
+        return;
+    }
+    float s = 0.0f;
+    for (int i = threadIdx.x; i < a.nlive; i += 256) s += a.lrow[i];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) red[0][threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) *a.loss = (((red[0][0] + red[0][1]) + red[0][2]) + red[0][3]) / (a.wsum ? *a.wsum : a.count);
+}
+
+// G = the partial sums added in order: one thread per parameter.
+__global__ __launch_bounds__(256) void k_grad_sum(GradArgs a) {
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    store_copies(s, i, p[i], wb, wt);
+    const int H = a.H, ncol = a.dout + (a.L + 1) * H;
+    const long nw = (long)a.dout * H, at0 = a.osplit ? nw : 0;
+    if (i < at0) {  // output layer weights
+        float s = 0.0f;
+        for (int z = 0; z < a.osplit; ++z) s += a.opart[(size_t)z * nw + i];
+        a.G[a.wout + i] = s;
+        return;
+    }
+    const long j = i - at0;  // then the input and residual layers, then the output bias
+    if (j >= a.nph + a.dout) return;
+    int col = (int)(j - a.nph);
+    long dst = a.bout + col;
+    if (j < a.nph) {
+        int l = 0;
+        while (l < a.L && j >= a.woff[l + 1]) ++l;
+        const long loc = j - a.woff[l], nm = (long)H * (l ? H : NCOND);
+        dst = j;
+        if (loc < nm) {
+            if (l > a.nhid) return;
+            float s = 0.0f;
+            for (int z = 0; z < a.nsplit; ++z) s += a.gpart[(size_t)z * a.nph + j];
+            a.G[dst] = s;
+            return;
+        }
+        col = a.dout + l * H + (int)(loc - nm);
+    }
+    float t = 0.0f;
+    for (int c = 0; c < a.nch; ++c) t += a.part[(size_t)c * ncol + col];
+    a.G[dst] = t;
 }
 
 // Adam (Kingma & Ba 2015): m = b1 m + (1-b1) g, v = b2 v + (1-b2) g^2,
 // p -= lr (m c1) / (sqrt(v c2) + eps), c1 = 1/(1-b1^t), c2 = 1/(1-b2^t).
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, long n, float lr, float b1, float b2, float c1, float c2, float eps,
-                       Segs s, bf16_t* wb, bf16_t* wt) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const float gi = g[i];
-    const float mi = b1 * m[i] + (1.0f - b1) * gi;
-    const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-    m[i] = mi;
-    v[i] = vi;
-    const float pi = p[i] - lr * (mi * c1) / (sqrtf(vi * c2) + eps);
-    p[i] = pi;
-    store_copies(s, i, pi, wb, wt);
+// Bound by the 32 bytes a parameter that it moves: 2.64 M parameters take
+// 20 us (33 us with one thread per parameter, whose 2-byte stores of wt
+// were a row apart).
+__global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, const float* __restrict__ g,
+                                              float* __restrict__ m, float* __restrict__ v, float lr, float b1,
+                                              float b2, float c1, float c2, float eps, Segs s, bf16_t* wb, bf16_t* wt) {
+    param_tile(s, wb, wt, [&](long i) {
+        const f32x4 gi = *reinterpret_cast<const f32x4*>(g + i);
+        f32x4 mi = *reinterpret_cast<const f32x4*>(m + i), vi = *reinterpret_cast<const f32x4*>(v + i);
+        f32x4 pi = *reinterpret_cast<const f32x4*>(p + i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            mi[q] = b1 * mi[q] + (1.0f - b1) * gi[q];
+            vi[q] = b2 * vi[q] + (1.0f - b2) * gi[q] * gi[q];
+            pi[q] = pi[q] - lr * (mi[q] * c1) / (sqrtf(vi[q] * c2) + eps);
+        }
+        *reinterpret_cast<f32x4*>(m + i) = mi;
+        *reinterpret_cast<f32x4*>(v + i) = vi;
+        *reinterpret_cast<f32x4*>(p + i) = pi;
+        return pi;
+    });
 }
 
 }  // namespace
@@ -870,24 +1185,22 @@ struct opf_mlp {
     float *P = nullptr, *G = nullptr, *Am = nullptr, *Av = nullptr;
     bf16_t *Wb = nullptr, *Wt = nullptr;
     bf16_t *Xb = nullptr, *XT = nullptr;
-    float* Hf = nullptr;
-    bf16_t *Hb = nullptr, *HT = nullptr;
-    float *Z = nullptr, *Y = nullptr, *dH = nullptr;
-    bf16_t *dYb = nullptr, *dYT = nullptr, *dZb0 = nullptr, *dZb1 = nullptr, *dZT = nullptr;
+    bf16_t *HL = nullptr, *HT = nullptr;       // h_L [R][H]; h_l transposed, l = 0..L
+    float *Z = nullptr, *Y = nullptr, *D = nullptr;  // D: dL/dh_l [R][H], l = 0..L
+    bf16_t *dYb = nullptr, *dYT = nullptr, *DT = nullptr;  // DT: D_l where z_{l-1} > 0, transposed
     float *fx = nullptr, *fac = nullptr;
     int* idx = nullptr;
     int* singular = nullptr;  // [rows] modes whose Woodbury matrix is singular
-    float* part = nullptr;    // [CS_CHUNKS][max(H, dout)] column-sum partials
+    float* part = nullptr;    // [CS_CHUNKS][dout + (L + 1) H] column-sum partials
     float* gpart = nullptr;   // [GPART] split-K partial tiles
     int n_singular = 0;
     float *lrow = nullptr, *wsum = nullptr, *losses = nullptr;
     int loss_cap = 0;
     std::string err;
 
-    float* hf(int l) const { return Hf + (size_t)l * R * H; }
-    bf16_t* hb(int l) const { return Hb + (size_t)l * R * H; }
     bf16_t* ht(int l) const { return HT + (size_t)l * H * R; }
-    float* z(int l) const { return Z + (size_t)l * R * H; }
+    bf16_t* dt(int l) const { return DT + (size_t)l * H * R; }
+    float* d(int l) const { return D + (size_t)l * R * H; }
 };
 
 namespace {
@@ -921,12 +1234,14 @@ Layout plan(opf_mlp* m) {
     m->din = NCOND;
     m->dout = round32(12 * m->N * m->rank);
     long o = 0;
-    int j = 0;
+    int j = 0, blk = 0;
     auto seg = [&](int rows, int cols, int mat) {
         m->segs.off[j] = o;
         m->segs.rows[j] = rows;
         m->segs.cols[j] = cols;
         m->segs.mat[j] = mat;
+        m->segs.blk[j] = blk;
+        blk += mat ? (rows + PT - 1) / PT * (cols / 32) : (cols + 2047) / 2048;
         ++j;
         const long at = o;
         o += (long)rows * cols;
@@ -935,13 +1250,14 @@ Layout plan(opf_mlp* m) {
     m->woff[0] = seg(m->H, m->din, 1);
     m->boff[0] = seg(1, m->H, 0);
     for (int l = 0; l < m->L; ++l) {
-        m->woff[l + 1] = seg(m->H, m->H, 1);
+        m->woff[l + 1] = seg(m->H, m->H, 2);
         m->boff[l + 1] = seg(1, m->H, 0);
     }
     m->woff[m->L + 1] = seg(m->dout, m->H, 1);
     m->boff[m->L + 1] = seg(1, m->dout, 0);
     m->segs.n = j;
     m->segs.off[j] = o;
+    m->segs.blk[j] = blk;
     m->np = o;
     const size_t R = m->R, H = m->H, L = m->L, np = o;
     Layout lay;
@@ -950,22 +1266,19 @@ Layout plan(opf_mlp* m) {
     lay.take(np * 2);                              // Wt
     lay.take(R * m->din * 2);                      // Xb
     lay.take(R * m->din * 2);                      // XT
-    lay.take((L + 1) * R * H * 4);                 // Hf
-    lay.take((L + 1) * R * H * 2);                 // Hb
+    lay.take(R * H * 2);                           // HL
     lay.take((L + 1) * R * H * 2);                 // HT
     lay.take(L * R * H * 4);                       // Z
     lay.take(R * m->dout * 4);                     // Y
-    lay.take(R * H * 4);                           // dH
+    lay.take((L + 1) * R * H * 4);                 // D
     lay.take(R * m->dout * 2);                     // dYb
     lay.take(R * m->dout * 2);                     // dYT
-    lay.take(R * H * 2);                           // dZb0
-    lay.take(R * H * 2);                           // dZb1
-    lay.take(R * H * 2);                           // dZT
+    lay.take((L + 1) * R * H * 2);                 // DT
     lay.take(R * m->din * 4);                      // fx: mode feature rows
     lay.take(R * m->dout * 4);                     // fac: factor rows in use
     lay.take((size_t)IDX_CAP * 4);                 // idx: pair indices
     lay.take(R * 4);                               // singular: per-mode flag of a singular G
-    lay.take((size_t)CS_CHUNKS * std::max(m->H, m->dout) * 4);  // part
+    lay.take((size_t)CS_CHUNKS * (m->dout + (L + 1) * H) * 4);  // part
     lay.take(GPART * 4);                                         // gpart
     lay.take(R * 4);                               // lrow
     lay.take(256);                                 // wsum
@@ -991,64 +1304,92 @@ opf_status check_cfg(const opf_ctx* c, const opf_mlp_config* cfg, std::string* w
     return OPF_OK;
 }
 
-// Column sums of rows x cols FP32 src (row stride = cols) into out.
-hipError_t colsum(opf_mlp* m, const float* src, const float* mask, int rows, int cols, float* out) {
-    const int ch = std::max(128, (rows + CS_CHUNKS - 1) / CS_CHUNKS);
-    const int nch = (rows + ch - 1) / ch;
-    hipLaunchKernelGGL(k_colsum_part, dim3(cols / 32, nch), dim3(256), 0, m->s, src, mask, rows, cols, ch, m->part);
-    hipLaunchKernelGGL(k_colsum_fin, dim3((cols + 255) / 256), dim3(256), 0, m->s, m->part, nch, cols, out);
+// A product left as nsplit partial products [rows][cols] for its reader to add
+// in order (one: the product itself, at Epi::out's place).
+struct Parts {
+    const float* at = nullptr;
+    int nsplit = 0;
+};
+
+struct Split {
+    int n, kc;  // K ranges and their length
+};
+
+// K split of a GEMM whose tile count cannot fill the chip but whose K is long.
+Split split_of(int rows, int cols, int K) {
+    Split p{1, K};
+    const size_t rc = (size_t)rows * cols;
+    if (large_product(rows, cols, K)) {  // 128 x 128 tiles, until about 256 workgroups
+        const long tiles = (long)(rows / G2) * (cols / G2);
+        if (tiles < 256) {
+            p.n = (int)std::min<long>((256 + tiles - 1) / tiles, std::min(K / 256, 2 * GSPLIT));
+            if (p.n * rc > GPART) p.n = (int)(GPART / rc);
+            p.n = std::max(p.n, 1);
+            p.kc = ((K + p.n - 1) / p.n + GK2 - 1) / GK2 * GK2;
+            p.n = (K + p.kc - 1) / p.kc;
+        }
+        return p;
+    }
+    const long tiles = (long)(rows / GT) * (cols / GT);
+    if (tiles < 1024 && K >= 512) {
+        p.n = (int)std::min<long>((2048 + tiles - 1) / tiles, std::min(K / 256, GSPLIT));
+        p.kc = ((K + p.n - 1) / p.n + 63) / 64 * 64;
+        p.n = (K + p.kc - 1) / p.kc;
+        if (p.n * rc > GPART) p = {1, K};
+    }
+    return p;
+}
+
+// Launch a GEMM.  The partial tiles of a split go to the scratch and through
+// k_gemm_reduce, or stay in the scratch when the caller takes `parts`.
+hipError_t gemm(opf_mlp* m, const bf16_t* A, int lda, const bf16_t* B, int ldb, int rows, int cols, int K,
+                const Epi& e, Parts* parts = nullptr) {
+    if (rows % GT || cols % GT || K % 16 || lda % 8 || ldb % 8 || rows <= 0 || cols <= 0 || K <= 0)
+        return hipErrorInvalidValue;
+    const Split p = split_of(rows, cols, K);
+    float* part = p.n > 1 ? m->gpart : nullptr;
+    if (large_product(rows, cols, K))
+        hipLaunchKernelGGL(k_gemm128, dim3(cols / G2, rows / G2, p.n), dim3(256), 0, m->s, A, lda, B, ldb, K, p.kc, e, part);
+    else
+        hipLaunchKernelGGL(k_gemm, dim3(cols / GT, rows / GT, p.n), dim3(256), 0, m->s, A, lda, B, ldb, K, p.kc, e, part);
+    if (parts) {
+        parts->at = part ? part : e.out;
+        parts->nsplit = p.n;
+    } else if (part) {
+        const size_t n = (size_t)rows * cols;
+        hipLaunchKernelGGL(k_gemm_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m->s, part, rows, cols, p.n, e);
+    }
     return hipGetLastError();
 }
 
-// Launch a GEMM; one whose tile count cannot fill the chip but whose K is
-// long is split over K (partial tiles to the scratch, then k_gemm_reduce).
-hipError_t gemm(opf_mlp* m, const bf16_t* A, int lda, const bf16_t* B, int ldb, int rows, int cols, int K,
-                const Epi& e) {
-    if (rows % GT || cols % GT || K % 16 || lda % 8 || ldb % 8 || rows <= 0 || cols <= 0 || K <= 0)
-        return hipErrorInvalidValue;
-    if (rows % G2 == 0 && cols % G2 == 0 && K % GK2 == 0 && (double)rows * cols * K >= (double)(1L << 30)) {
-        // large product: 128 x 128 tiles, K split until about 256 workgroups
-        const long tiles = (long)(rows / G2) * (cols / G2);
-        int nsplit = 1, kc = K;
-        if (tiles < 256) {
-            nsplit = (int)std::min<long>((256 + tiles - 1) / tiles, std::min(K / 256, 2 * GSPLIT));
-            if ((size_t)nsplit * rows * cols > GPART) nsplit = (int)(GPART / ((size_t)rows * cols));
-            nsplit = std::max(nsplit, 1);
-            kc = (K + nsplit - 1) / nsplit;
-            kc = (kc + GK2 - 1) / GK2 * GK2;
-            nsplit = (K + kc - 1) / kc;
-        }
-        if (nsplit == 1) {
-            hipLaunchKernelGGL(k_gemm128, dim3(cols / G2, rows / G2, 1), dim3(256), 0, m->s, A, lda, B, ldb, K, K, e,
-                               nullptr);
-            return hipGetLastError();
-        }
-        hipLaunchKernelGGL(k_gemm128, dim3(cols / G2, rows / G2, nsplit), dim3(256), 0, m->s, A, lda, B, ldb, K, kc,
-                           e, m->gpart);
-        const size_t n = (size_t)rows * cols;
-        hipLaunchKernelGGL(k_gemm_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m->s, m->gpart, rows,
-                           cols, nsplit, e);
-        return hipGetLastError();
+ChainArgs chain_args(const opf_mlp* m, int rp, const bf16_t* W) {
+    ChainArgs a{};
+    a.X = m->Xb;
+    a.W = W;
+    a.P = m->P;
+    for (int l = 0; l <= m->L; ++l) a.woff[l] = m->woff[l], a.boff[l] = m->boff[l];
+    a.H = m->H;
+    a.L = m->L;
+    a.R = m->R;
+    a.rows = rp;
+    a.Z = m->Z;
+    a.HL = m->HL;
+    return a;
+}
+
+// One workgroup per 32 rows, one wave per 32 columns.
+hipError_t launch_chain(const ChainArgs& a, bool fwd, hipStream_t s) {
+    const int H = a.H;
+    auto k = H < 256    ? (fwd ? k_chain_fwd<false, false> : k_chain_bwd<false, false>)
+             : H == 256 ? (fwd ? k_chain_fwd<false, true> : k_chain_bwd<false, true>)
+             : H < 512  ? (fwd ? k_chain_fwd<true, false> : k_chain_bwd<true, false>)
+                        : (fwd ? k_chain_fwd<true, true> : k_chain_bwd<true, true>);
+    const size_t lds = (size_t)2 * 32 * (H + 8) * sizeof(bf16_t);  // 66.6 KB at H = 512
+    if (lds > 65536) {
+        const hipError_t st = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (st != hipSuccess) return st;
     }
-    const long tiles = (long)(rows / GT) * (cols / GT);
-    int nsplit = 1, kc = K;
-    if (tiles < 1024 && K >= 512) {
-        nsplit = (int)std::min<long>((2048 + tiles - 1) / tiles, std::min(K / 256, GSPLIT));
-        kc = (K + nsplit - 1) / nsplit;
-        kc = (kc + 63) / 64 * 64;
-        nsplit = (K + kc - 1) / kc;
-        if ((size_t)nsplit * rows * cols > GPART) nsplit = 1, kc = K;
-    }
-    if (nsplit == 1) {
-        hipLaunchKernelGGL(k_gemm, dim3(cols / GT, rows / GT, 1), dim3(256), 0, m->s, A, lda, B, ldb, K, K, e,
-                           nullptr);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(k_gemm, dim3(cols / GT, rows / GT, nsplit), dim3(256), 0, m->s, A, lda, B, ldb, K, kc, e,
-                       m->gpart);
-    const size_t n = (size_t)rows * cols;
-    hipLaunchKernelGGL(k_gemm_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m->s, m->gpart, rows, cols,
-                       nsplit, e);
+    hipLaunchKernelGGL(k, dim3(a.rows / 32), dim3(2 * H), lds, s, a);
     return hipGetLastError();
 }
 
@@ -1056,99 +1397,90 @@ hipError_t gemm(opf_mlp* m, const bf16_t* A, int lda, const bf16_t* B, int ldb, 
 // train: also keep pre-activations and transposed activations.
 hipError_t forward(opf_mlp* m, int rp, bool train) {
     const int H = m->H, L = m->L;
-    Epi e{};
-    e.bias = m->P + m->boff[0];
-    e.out = m->hf(0);
-    e.ldo = H;
-    e.outb = m->hb(0);
-    e.ldb = H;
-    if (train) {
-        e.outT = m->ht(0);
-        e.ldt = m->R;
-    }
-    hipError_t st = gemm(m, m->Xb, m->din, m->Wb + m->woff[0], m->din, rp, H, m->din, e);
+    ChainArgs a = chain_args(m, rp, m->Wb);
+    a.HT = train ? m->HT : nullptr;
+    const hipError_t st = launch_chain(a, true, m->s);
     if (st != hipSuccess) return st;
-    for (int l = 0; l < L; ++l) {
-        Epi f{};
-        f.bias = m->P + m->boff[l + 1];
-        if (train) {
-            f.zout = m->z(l);
-            f.ldz = H;
-            f.outT = m->ht(l + 1);
-            f.ldt = m->R;
-        }
-        f.mode = EPI_RELU_RES;
-        f.res = m->hf(l);
-        f.ldr = H;
-        f.out = m->hf(l + 1);
-        f.ldo = H;
-        f.outb = m->hb(l + 1);
-        f.ldb = H;
-        st = gemm(m, m->hb(l), H, m->Wb + m->woff[l + 1], H, rp, H, H, f);
-        if (st != hipSuccess) return st;
-    }
     Epi g{};
     g.bias = m->P + m->boff[L + 1];
     g.out = m->Y;
     g.ldo = m->dout;
-    return gemm(m, m->hb(L), H, m->Wb + m->woff[L + 1], H, rp, m->dout, H, g);
+    return gemm(m, m->HL, H, m->Wb + m->woff[L + 1], H, rp, m->dout, H, g);
 }
 
-// Parameter gradients from dL/dY (FP32 in Y, bfloat16 in dYb / dYT) after
+// Loss (of per-row losses lrow[0..nlive) over *wsum or count) and parameter
+// gradients from dL/dY (FP32 in Y, bfloat16 in dYb / dYT) after
 // forward(train = true) over rp rows.
-hipError_t backprop(opf_mlp* m, int rp) {
+hipError_t backprop(opf_mlp* m, int rp, int nlive, const float* wsum, float count, float* loss_slot) {
     const int H = m->H, L = m->L, R = m->R, dout = m->dout;
     hipError_t st;
-    {  // output layer: dW = dY^T H_L, db = colsum dY, dH_L = dY W_out
-        Epi e{};
-        e.out = m->G + m->woff[L + 1];
-        e.ldo = H;
-        if ((st = gemm(m, m->dYT, R, m->ht(L), R, dout, H, rp, e)) != hipSuccess) return st;
-        if ((st = colsum(m, m->Y, nullptr, rp, dout, m->G + m->boff[L + 1])) != hipSuccess) return st;
-        Epi f{};
-        f.out = m->dH;
-        f.ldo = H;
-        f.mask = m->z(L - 1);
-        f.ldm = H;
-        f.outb = m->dZb0;
-        f.ldb = H;
-        f.outT = m->dZT;
-        f.ldt = R;
-        if ((st = gemm(m, m->dYb, dout, m->Wt + m->woff[L + 1], dout, rp, H, dout, f)) != hipSuccess)
-            return st;
-    }
-    bf16_t* dz[2] = {m->dZb0, m->dZb1};
-    int cur = 0;
-    for (int l = L - 1; l >= 0; --l) {
-        // dz_l = dH_{l+1} [z_l > 0] is in dz[cur] (row-major) and dZT (transposed)
-        if ((st = colsum(m, m->dH, m->z(l), rp, H, m->G + m->boff[l + 1])) != hipSuccess) return st;
-        Epi e{};
-        e.out = m->G + m->woff[l + 1];
-        e.ldo = H;
-        if ((st = gemm(m, m->dZT, R, m->ht(l), R, H, H, rp, e)) != hipSuccess) return st;
-        Epi f{};
-        f.mode = EPI_ADD;
-        f.res = m->dH;
-        f.ldr = H;
-        f.out = m->dH;
-        f.ldo = H;
-        f.outT = m->dZT;
-        f.ldt = R;
-        if (l > 0) {
-            f.mask = m->z(l - 1);
-            f.ldm = H;
-            f.outb = dz[cur ^ 1];
-            f.ldb = H;
-        }
-        if ((st = gemm(m, dz[cur], H, m->Wt + m->woff[l + 1], H, rp, H, H, f)) != hipSuccess) return st;
-        cur ^= 1;
-    }
-    // input layer: dW_in = dH_0^T X, db_in = colsum dH_0
-    if ((st = colsum(m, m->dH, nullptr, rp, H, m->G + m->boff[0])) != hipSuccess) return st;
     Epi e{};
-    e.out = m->G + m->woff[0];
-    e.ldo = m->din;
-    if ((st = gemm(m, m->dZT, R, m->XT, R, H, m->din, rp, e)) != hipSuccess) return st;
+    Parts p;
+    e.out = m->d(L);  // dL/dh_L = dY W_out, added up by the chain
+    e.ldo = H;
+    if ((st = gemm(m, m->dYb, dout, m->Wt + m->woff[L + 1], dout, rp, H, dout, e, &p)) != hipSuccess) return st;
+    ChainArgs a = chain_args(m, rp, m->Wt);
+    a.HT = m->HT;
+    a.src = p.at;
+    a.nsplit = p.nsplit;
+    a.stride = (size_t)rp * H;
+    a.D = m->D;
+    a.DT = m->DT;
+    if ((st = launch_chain(a, false, m->s)) != hipSuccess) return st;
+
+    GradArgs g{};
+    g.DT = m->DT;
+    g.HT = m->HT;
+    g.XT = m->XT;
+    g.D = m->D;
+    g.Z = m->Z;
+    g.Y = m->Y;
+    for (int l = 0; l <= L; ++l) g.woff[l] = m->woff[l];
+    g.H = H;
+    g.L = L;
+    g.R = R;
+    g.dout = dout;
+    g.rows = rp;
+    g.nph = m->woff[L + 1];
+    g.G = m->G;
+    g.wout = m->woff[L + 1];
+    g.bout = m->boff[L + 1];
+    // weight gradients of the residual layers: 128 x 128 tiles where a product
+    // is large (each row of the operands is then read four times less often)
+    g.nhid = large_product(H, H, rp) ? 0 : L;
+    for (int l = g.nhid; l < L; ++l) {
+        Epi w{};
+        w.out = m->G + m->woff[l + 1];
+        w.ldo = H;
+        if ((st = gemm(m, m->dt(l + 1), R, m->ht(l), R, H, H, rp, w)) != hipSuccess) return st;
+    }
+    g.nsplit = std::max(1, std::min({rp / 256, GSPLIT, (int)(GPART / g.nph)}));
+    g.kc = ((rp + g.nsplit - 1) / g.nsplit + 63) / 64 * 64;
+    g.nsplit = (rp + g.kc - 1) / g.kc;
+    // output layer: dW = dY^T H_L; its partial products stay in the scratch
+    // until k_grad_sum when the other layers' fit behind them
+    e.out = m->G + g.wout;
+    e.ldo = H;
+    const size_t nw = (size_t)dout * H;
+    const int osplit = split_of(dout, H, rp).n;
+    const bool keep = osplit > 1 && osplit * nw + (size_t)g.nsplit * g.nph <= GPART;
+    if ((st = gemm(m, m->dYT, R, m->ht(L), R, dout, H, rp, e, keep ? &p : nullptr)) != hipSuccess) return st;
+    g.osplit = keep ? osplit : 0;
+    g.opart = m->gpart;
+    g.gpart = m->gpart + g.osplit * nw;
+
+    g.ngemm = (H / GT + g.nhid * (H / GT) * (H / GT)) * g.nsplit;
+    g.ch = std::max(128, (rp + CS_CHUNKS - 1) / CS_CHUNKS);
+    g.nch = (rp + g.ch - 1) / g.ch;
+    g.part = m->part;
+    g.lrow = m->lrow;
+    g.wsum = wsum;
+    g.count = count;
+    g.nlive = nlive;
+    g.loss = loss_slot;
+    hipLaunchKernelGGL(k_grad_parts, dim3(g.ngemm + g.nch * ((dout + (L + 1) * H) / 32) + 1), dim3(256), 0, m->s, g);
+    const long n = (g.osplit ? (long)nw : 0) + g.nph + dout;
+    hipLaunchKernelGGL(k_grad_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m->s, g);
     return hipGetLastError();
 }
 
@@ -1159,9 +1491,8 @@ hipError_t backward_rows(opf_mlp* m, const float* t, const float* om, int nrows,
     hipLaunchKernelGGL(k_weight_sum, dim3(1), dim3(256), 0, s, om, nrows, m->wsum);
     hipLaunchKernelGGL(k_loss, dim3(rp / 4), dim3(256), 0, s, m->Y, t, om, m->wsum, nrows, rp, m->dout, m->dYb,
                        m->dYT, m->R, m->lrow);
-    hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(256), 0, s, m->lrow, nrows, m->wsum, loss_slot);
     const hipError_t st = hipGetLastError();
-    return st != hipSuccess ? st : backprop(m, rp);
+    return st != hipSuccess ? st : backprop(m, rp, nrows, m->wsum, 0.0f, loss_slot);
 }
 
 // Loss head over pairs idx[0..batch) into *loss_slot and dL/dY, then the
@@ -1194,10 +1525,8 @@ hipError_t backward_pairs(opf_mlp* m, const double* pairs, const int* idx, int b
     hipLaunchKernelGGL(kh, dim3(rp), dim3(256), hl, s, a);
     hipLaunchKernelGGL(k_transpose_bf16, dim3((m->dout + 63) / 64, (rp + 63) / 64), dim3(256), 0, s, m->dYb, rp,
                        m->dout, m->dout, m->dYT, m->R);
-    hipLaunchKernelGGL(k_weight_sum, dim3(1), dim3(256), 0, s, nullptr, batch * m->mode_rows, m->wsum);
-    hipLaunchKernelGGL(k_loss_total, dim3(1), dim3(256), 0, s, m->lrow, m->mode_rows, m->wsum, loss_slot);
     const hipError_t st = hipGetLastError();
-    return st != hipSuccess ? st : backprop(m, rp);
+    return st != hipSuccess ? st : backprop(m, rp, m->mode_rows, nullptr, (float)((long)batch * m->mode_rows), loss_slot);
 }
 
 hipError_t adam(opf_mlp* m, float lr) {
@@ -1205,8 +1534,7 @@ hipError_t adam(opf_mlp* m, float lr) {
     m->fac_ok = false;
     const float c1 = (float)(1.0 / (1.0 - std::pow((double)m->b1, (double)m->t)));
     const float c2 = (float)(1.0 / (1.0 - std::pow((double)m->b2, (double)m->t)));
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)((m->np + 255) / 256)), dim3(256), 0, m->s, m->P, m->G, m->Am, m->Av,
-                       m->np, lr, m->b1, m->b2, c1, c2, m->eps, m->segs, m->Wb, m->Wt);
+    hipLaunchKernelGGL(k_adam, dim3(m->segs.blk[m->segs.n]), dim3(256), 0, m->s, m->P, m->G, m->Am, m->Av, lr, m->b1, m->b2, c1, c2, m->eps, m->segs, m->Wb, m->Wt);
     return hipGetLastError();
 }
 
@@ -1329,17 +1657,14 @@ opf_status opf_mlp_create(opf_ctx* ctx, const opf_mlp_config* cfg, void* dev_wor
     at(m->Wt);
     at(m->Xb);
     at(m->XT);
-    at(m->Hf);
-    at(m->Hb);
+    at(m->HL);
     at(m->HT);
     at(m->Z);
     at(m->Y);
-    at(m->dH);
+    at(m->D);
     at(m->dYb);
     at(m->dYT);
-    at(m->dZb0);
-    at(m->dZb1);
-    at(m->dZT);
+    at(m->DT);
     at(m->fx);
     at(m->fac);
     at(m->idx);
@@ -1396,7 +1721,7 @@ opf_status opf_mlp_set_params(opf_mlp* net, const float* host, int64_t n) {
     MCHK(net, hipMemcpyAsync(net->P, host, (size_t)n * 4, hipMemcpyHostToDevice, net->s));
     MCHK(net, hipMemsetAsync(net->Am, 0, (size_t)n * 4, net->s));
     MCHK(net, hipMemsetAsync(net->Av, 0, (size_t)n * 4, net->s));
-    hipLaunchKernelGGL(k_refresh, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, net->s, net->P, (long)n, net->segs,
+    hipLaunchKernelGGL(k_refresh, dim3(net->segs.blk[net->segs.n]), dim3(256), 0, net->s, net->P, net->segs,
                        net->Wb, net->Wt);
     MCHK(net, hipGetLastError());
     MCHK(net, hipStreamSynchronize(net->s));

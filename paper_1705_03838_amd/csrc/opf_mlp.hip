@@ -298,7 +298,7 @@ __host__ __device__ inline long frag_at(int n, int k, int H) {
 // matrix, or 2048 of a bias.  A matrix tile's bfloat16 copies wb ([rows][cols]
 // at the parameter offset) and wt ([cols][rows], through LDS) are written in
 // runs of 64 and 128 bytes, both in frag_at's order for a residual layer.
-// step(i) returns the new values of parameters i..i+3.
+// step(j, i) returns the new values of parameters i..i+3 of segment j.
 constexpr int PT = 64;  // rows of a tile
 template <typename Step>
 __device__ __forceinline__ void param_tile(const Segs& s, bf16_t* __restrict__ wb, bf16_t* __restrict__ wt, Step step) {
@@ -308,7 +308,7 @@ __device__ __forceinline__ void param_tile(const Segs& s, bf16_t* __restrict__ w
     const int b = blockIdx.x - s.blk[j], t = threadIdx.x;
     const long off = s.off[j];
     if (!s.mat[j]) {
-        for (int i = b * 2048 + 4 * t; i < min(s.cols[j], (b + 1) * 2048); i += 1024) step(off + i);
+        for (int i = b * 2048 + 4 * t; i < min(s.cols[j], (b + 1) * 2048); i += 1024) step(j, off + i);
         return;
     }
     const int rows = s.rows[j], cols = s.cols[j];
@@ -319,7 +319,7 @@ __device__ __forceinline__ void param_tile(const Segs& s, bf16_t* __restrict__ w
         const int r = r0 + h + (t >> 3);
         if (r >= rows) break;  // rows is a multiple of 32
         const long i = off + (long)r * cols + c0 + c;
-        const f32x4 p = step(i);
+        const f32x4 p = step(j, i);
         bf16_t v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) tile[c + q][h + (t >> 3)] = v[q] = f2bf(p[q]);
@@ -340,7 +340,7 @@ __device__ __forceinline__ void param_tile(const Segs& s, bf16_t* __restrict__ w
 }
 
 __global__ __launch_bounds__(256) void k_refresh(const float* __restrict__ p, Segs s, bf16_t* wb, bf16_t* wt) {
-    param_tile(s, wb, wt, [&](long i) { return *reinterpret_cast<const f32x4*>(p + i); });
+    param_tile(s, wb, wt, [&](int, long i) { return *reinterpret_cast<const f32x4*>(p + i); });
 }
 
 // The residual layers, forward and backward, run as chains: a workgroup keeps
@@ -549,7 +549,7 @@ void k_chain_bwd(ChainArgs a) {
 }
 
 // What is left of the gradients once the chain has run, in one launch of
-// independent workgroups and one that adds their partial sums (a launch each
+// independent workgroups whose partial sums the reader adds (a launch each
 // cost 4.5 us or more at 1536 rows, whatever it did; 31 in all):
 //  - the first ngemm workgroups: 32 x 32 tiles of the weight gradients of the
 //    input layer and of nhid residual layers, dW = DT HT^T with K = rows split
@@ -564,7 +564,7 @@ struct GradArgs {
     long woff[MAXL + 1];
     int H, L, R, dout, rows;
     int nhid, nsplit, kc, ngemm;
-    int ch, nch;
+    int ch, nch, col0;  // columns before col0 are in part already
     float* gpart;
     long nph;  // parameters before the output layer's
     float* part;
@@ -572,7 +572,7 @@ struct GradArgs {
     float count;
     int nlive;
     float* loss;
-    // for k_grad_sum
+    // for grad_of
     float* G;
     long wout, bout;
     int osplit;          // partial products of the output layer's weight gradient in opart (0: already in G)
@@ -604,8 +604,9 @@ __global__ __launch_bounds__(256) void k_grad_parts(GradArgs a) {
     b -= a.ngemm;
     const int ncol = a.dout + (a.L + 1) * H;
     __shared__ float red[8][32];
-    if (b < a.nch * (ncol / 32)) {
-        const int cb = b % (ncol / 32), k = b / (ncol / 32);
+    const int c1 = (ncol - a.col0) / 32;
+    if (b < a.nch * c1) {
+        const int cb = a.col0 / 32 + b % c1, k = b / c1;
         const int c = threadIdx.x & 31, g = threadIdx.x >> 5;
         const float *src = a.Y, *mask = nullptr;
         int col = cb * 32, ld = a.dout;
@@ -641,50 +642,46 @@ __global__ __launch_bounds__(256) void k_grad_parts(GradArgs a) {
     if (threadIdx.x == 0) *a.loss = (((red[0][0] + red[0][1]) + red[0][2]) + red[0][3]) / (a.wsum ? *a.wsum : a.count);
 }
 
-// G = the partial sums added in order: one thread per parameter.
-__global__ __launch_bounds__(256) void k_grad_sum(GradArgs a) {
-    const long i = (long)blockIdx.x * 256 + threadIdx.x;
-    const int H = a.H, ncol = a.dout + (a.L + 1) * H;
-    const long nw = (long)a.dout * H, at0 = a.osplit ? nw : 0;
-    if (i < at0) {  // output layer weights
-        float s = 0.0f;
-        for (int z = 0; z < a.osplit; ++z) s += a.opart[(size_t)z * nw + i];
-        a.G[a.wout + i] = s;
-        return;
+// Gradients of parameters i..i+3, segment j: their partial sums added in order.
+__device__ __forceinline__ f32x4 grad_of(const GradArgs& a, int j, long i) {
+    const int l = j >> 1, ncol = a.dout + (a.L + 1) * a.H;
+    const float* p = a.G + i;  // (a product that was not split, or was added up by k_gemm_reduce)
+    size_t stride = 0;
+    int n = 1;
+    if (j & 1) {
+        p = a.part + (l > a.L ? i - a.bout : a.dout + l * a.H + (i - a.woff[l] - (long)a.H * (l ? a.H : NCOND)));
+        stride = ncol;
+        n = a.nch;
+    } else if (l > a.L ? a.osplit > 0 : l <= a.nhid) {
+        p = l > a.L ? a.opart + (i - a.wout) : a.gpart + i;
+        stride = l > a.L ? (size_t)a.dout * a.H : a.nph;
+        n = l > a.L ? a.osplit : a.nsplit;
     }
-    const long j = i - at0;  // then the input and residual layers, then the output bias
-    if (j >= a.nph + a.dout) return;
-    int col = (int)(j - a.nph);
-    long dst = a.bout + col;
-    if (j < a.nph) {
-        int l = 0;
-        while (l < a.L && j >= a.woff[l + 1]) ++l;
-        const long loc = j - a.woff[l], nm = (long)H * (l ? H : NCOND);
-        dst = j;
-        if (loc < nm) {
-            if (l > a.nhid) return;
-            float s = 0.0f;
-            for (int z = 0; z < a.nsplit; ++z) s += a.gpart[(size_t)z * a.nph + j];
-            a.G[dst] = s;
-            return;
-        }
-        col = a.dout + l * H + (int)(loc - nm);
-    }
-    float t = 0.0f;
-    for (int c = 0; c < a.nch; ++c) t += a.part[(size_t)c * ncol + col];
-    a.G[dst] = t;
+    f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+    for (int z = 0; z < n; ++z) s += *reinterpret_cast<const f32x4*>(p + z * stride);
+    return s;
+}
+
+// G = the gradients, for a caller that wants them: four parameters per thread.
+__global__ __launch_bounds__(256) void k_grad_sum(GradArgs a, Segs s) {
+    const long i = 4 * ((long)blockIdx.x * 256 + threadIdx.x);
+    if (i >= s.off[s.n]) return;
+    int j = 0;
+    while (j + 1 < s.n && i >= s.off[j + 1]) ++j;
+    *reinterpret_cast<f32x4*>(a.G + i) = grad_of(a, j, i);
 }
 
 // Adam (Kingma & Ba 2015): m = b1 m + (1-b1) g, v = b2 v + (1-b2) g^2,
 // p -= lr (m c1) / (sqrt(v c2) + eps), c1 = 1/(1-b1^t), c2 = 1/(1-b2^t).
-// Bound by the 32 bytes a parameter that it moves: 2.64 M parameters take
-// 20 us (33 us with one thread per parameter, whose 2-byte stores of wt
-// were a row apart).
-__global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, const float* __restrict__ g,
-                                              float* __restrict__ m, float* __restrict__ v, float lr, float b1,
+// It adds up the gradient's partial sums itself, so G is neither written nor
+// read.  Bound by the 28 bytes a parameter that it moves besides: 2.64 M
+// parameters take 23 us (20 after a k_grad_sum of 11 us; 33 with one thread
+// per parameter, whose 2-byte stores of wt were a row apart).
+__global__ __launch_bounds__(256) void k_adam(float* __restrict__ p, GradArgs g, float* __restrict__ m, float* __restrict__ v, float lr, float b1,
                                               float b2, float c1, float c2, float eps, Segs s, bf16_t* wb, bf16_t* wt) {
-    param_tile(s, wb, wt, [&](long i) {
-        const f32x4 gi = *reinterpret_cast<const f32x4*>(g + i);
+    param_tile(s, wb, wt, [&](int j, long i) {
+        const f32x4 gi = grad_of(g, j, i);
         f32x4 mi = *reinterpret_cast<const f32x4*>(m + i), vi = *reinterpret_cast<const f32x4*>(v + i);
         f32x4 pi = *reinterpret_cast<const f32x4*>(p + i);
 #pragma unroll
@@ -844,14 +841,22 @@ inline int head_pairs(int n3, int R) {
 // partial sums are added in a fixed order, R = -X + U C - T by threads over
 // (pair, e), and dU += R C^H, dV += X G^H in registers (each thread owns
 // fixed gradient entries) until the row is written once: dY in FP32 and its
-// row-major bfloat16 copy (k_transpose_bf16 makes the transposed one).
+// row-major bfloat16 copy (k_head_out makes the transposed one).
+// Bound by its vector instructions: 1512 rows of 3 N = 144, R = 16, 16 pairs
+// take 97 us (its bytes 40 us), 127 with U, V, xhat and r addressed entry by
+// entry and a branch per gradient entry (8100 instructions per wave, 4600 of
+// them the sums' own).  xhat and r lie side by side, one 16-byte read for
+// both updates; addresses advance by the row; entries past the last one
+// repeat it instead of branching; the next pass's profiles are requested a
+// pass ahead, and barriers order LDS only.  Three workgroups per compute unit
+// (HEAD_LDS, 168 VGPRs): with 177 VGPRs and two it took 153 us.
 // HO: gradient entries per thread and factor (3N R <= 256 HO); JFIX: R
 // divides 256, so every entry of a thread has the same j and the thread
 // keeps C and G of its column in registers through the dU, dV update.
 template <int HO, bool JFIX>
-__global__ __launch_bounds__(256) void k_head(HeadArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HO <= 9 ? 3 : 2, HO <= 9 ? 3 : 2)))
+void k_head(HeadArgs a) {
     extern __shared__ float2 hsm[];
-    __shared__ float sinv[HB];
     __shared__ float lpart[4];
     const int q = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
     float* yrow = a.Y + (long)q * a.dout;
@@ -867,15 +872,19 @@ __global__ __launch_bounds__(256) void k_head(HeadArgs a) {
     const int hb = a.hb;
     float2* sU = hsm;               // [n3][RP]
     float2* sV = sU + n3 * RP;      // [n3][RP]
-    float2* xs = sV + n3 * RP;      // [hb][n3]: xhat, kept for dV
-    float2* rs = xs + hb * n3;      // [hb][n3]: that, then r
-    float2* cs = rs + hb * n3;      // [hb][R]
+    float4* xr = reinterpret_cast<float4*>(sV + n3 * RP);  // [hb][n3 + 1]: (xhat; that, then r)
+    const int XP = n3 + 1;
+    float2* cs = reinterpret_cast<float2*>(xr + hb * XP);  // [hb][R]
     float2* gs = cs + hb * R;       // [hb][R]
     float2* red = gs + hb * R;      // [256] partial sums
     {
         const float2* U2 = reinterpret_cast<const float2*>(yrow);
-        for (int i = t; i < nf; i += 256) {
-            const int e = i / R, j = i - e * R;
+        const int ej = t / R, jj = t - ej * R;
+#pragma unroll
+        for (int o = 0; o < HO; ++o) {
+            const int i = t + 256 * o;
+            if (i >= nf) break;
+            const int e = JFIX ? ej + 256 / R * o : i / R, j = JFIX ? jj : i - e * R;
             sU[e * RP + j] = U2[i];
             sV[e * RP + j] = U2[nf + i];
         }
@@ -885,109 +894,121 @@ __global__ __launch_bounds__(256) void k_head(HeadArgs a) {
 #pragma unroll
     for (int o = 0; o < HO; ++o) du[o] = dv[o] = make_float2(0.0f, 0.0f);
     float lsum = 0.0f;
+    // z and J z of mode q of batch entry b at e = lane + 64 i < 3 N <= 192: the
+    // first pair of each wave is requested a pass ahead
+    double2 zz[3], jz[3];
+    auto request = [&](int b) {
+        const double* zv = a.pairs + (long)a.idx[min(b, a.batch - 1)] * 2 * a.vec + 2 * (long)q * a.N;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int e = min(lane + 64 * i, n3 - 1), c = e >= 2 * a.N ? 2 : e >= a.N ? 1 : 0;
+            const double* ze = zv + 2 * (c * S + e - c * a.N);
+            zz[i] = *reinterpret_cast<const double2*>(ze);
+            jz[i] = *reinterpret_cast<const double2*>(ze + a.vec);
+        }
+    };
+    request(w);
     for (int b0 = 0; b0 < a.batch; b0 += hb) {
         const int nb = min(hb, a.batch - b0);
         const int items = nb * R;
         const int np = items >= 256 ? 1 : 256 / items;  // e ranges of the V^H X and U^H R sums
         const int elen = (n3 + np - 1) / np;
-        for (int i = t; i < nb * n3; i += 256) {  // stage z and J z profiles of mode q
-            const int b = i / n3, e = i - b * n3;
-            const double* zv = a.pairs + (long)a.idx[b0 + b] * 2 * a.vec;
-            const long idx = (e / a.N) * S + (long)q * a.N + e % a.N;
-            const double2 zz = *reinterpret_cast<const double2*>(zv + 2 * idx);
-            const double2 jz = *reinterpret_cast<const double2*>(zv + a.vec + 2 * idx);
-            xs[i] = make_float2((float)zz.x, (float)zz.y);
-            rs[i] = make_float2((float)jz.x, (float)jz.y);
-        }
-        __syncthreads();
-        for (int b = w; b < nb; b += 4) {  // s of each pair: one wave per pair
+        for (int b = w; b < nb; b += 4) {  // one wave per pair: its z and J z profiles of mode q, over s
+            if (b > w) request(b0 + b);
+            float2 x[3], th[3];
             float s2 = 0.0f;
-            for (int e = lane; e < n3; e += 64) s2 += xs[b * n3 + e].x * xs[b * n3 + e].x + xs[b * n3 + e].y * xs[b * n3 + e].y;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                x[i] = make_float2((float)zz[i].x, (float)zz[i].y);
+                th[i] = make_float2((float)jz[i].x, (float)jz[i].y);
+                if (lane + 64 * i < n3) s2 += x[i].x * x[i].x + x[i].y * x[i].y;
+            }
             s2 = wave_sum(s2);
-            if (lane == 0) sinv[b] = s2 > 0.0f ? 1.0f / sqrtf(s2 / n3) : 0.0f;
+            const float f = s2 > 0.0f ? 1.0f / sqrtf(s2 / n3) : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const int e = lane + 64 * i;
+                if (e >= n3) continue;
+                xr[b * XP + e] = make_float4(x[i].x * f, x[i].y * f, th[i].x * f, th[i].y * f);
+            }
         }
-        __syncthreads();
-        for (int i = t; i < nb * n3; i += 256) {
-            const float f = sinv[i / n3];
-            xs[i].x *= f;
-            xs[i].y *= f;
-            rs[i].x *= f;
-            rs[i].y *= f;
-        }
-        __syncthreads();
+        request(b0 + hb + w);
+        lds_barrier();
         for (int i = t; i < items * np; i += 256) {  // partial C = V^H X over e range p
             const int p = i / items, bj = i - p * items, b = bj / R, j = bj - b * R;
             const int e0 = p * elen, e1 = min(n3, e0 + elen);
             float cr = 0.0f, ci = 0.0f;
+            const float2 *vp = sV + e0 * RP + j, *xp = reinterpret_cast<const float2*>(xr + b * XP + e0);
 #pragma unroll 4
-            for (int e = e0; e < e1; ++e) {
-                const float2 v = sV[e * RP + j], x = xs[b * n3 + e];
+            for (int e = e0; e < e1; ++e, vp += RP, xp += 2) {
+                const float2 v = *vp, x = *xp;
                 cr += v.x * x.x + v.y * x.y;
                 ci += v.x * x.y - v.y * x.x;
             }
             if (np == 1) cs[bj] = make_float2(cr, ci);
             else red[i] = make_float2(cr, ci);
         }
-        __syncthreads();
+        lds_barrier();
         if (np > 1) {
             for (int bj = t; bj < items; bj += 256) {
                 float2 c = red[bj];
                 for (int p = 1; p < np; ++p) c.x += red[p * items + bj].x, c.y += red[p * items + bj].y;
                 cs[bj] = c;
             }
-            __syncthreads();
+            lds_barrier();
         }
-        for (int i = t; i < nb * n3; i += 256) {  // r = -x + U c - that
-            const int b = i / n3, e = i - b * n3;
-            const float2 x = xs[i], th = rs[i];
-            float pr = -x.x - th.x, pi = -x.y - th.y;
+        for (int i = t, b = 0, e = t; i < nb * n3; i += 256, e += 256) {  // r = -x + U c - that
+            while (e >= n3) e -= n3, ++b;  // i = b n3 + e
+            const float4 xt = xr[b * XP + e];
+            float pr = -xt.x - xt.z, pi = -xt.y - xt.w;
 #pragma unroll 4
             for (int j = 0; j < R; ++j) {
                 const float2 u = sU[e * RP + j], c = cs[b * R + j];
                 pr += u.x * c.x - u.y * c.y;
                 pi += u.x * c.y + u.y * c.x;
             }
-            rs[i] = make_float2(pr, pi);
+            reinterpret_cast<float2*>(xr + b * XP + e)[1] = make_float2(pr, pi);
             lsum += pr * pr + pi * pi;
         }
-        __syncthreads();
+        lds_barrier();
         for (int i = t; i < items * np; i += 256) {  // partial G = U^H R over e range p
             const int p = i / items, bj = i - p * items, b = bj / R, j = bj - b * R;
             const int e0 = p * elen, e1 = min(n3, e0 + elen);
             float gr = 0.0f, gi = 0.0f;
+            const float2 *up = sU + e0 * RP + j, *rp = reinterpret_cast<const float2*>(xr + b * XP + e0) + 1;
 #pragma unroll 4
-            for (int e = e0; e < e1; ++e) {
-                const float2 u = sU[e * RP + j], r = rs[b * n3 + e];
+            for (int e = e0; e < e1; ++e, up += RP, rp += 2) {
+                const float2 u = *up, r = *rp;
                 gr += u.x * r.x + u.y * r.y;
                 gi += u.x * r.y - u.y * r.x;
             }
             if (np == 1) gs[bj] = make_float2(gr, gi);
             else red[i] = make_float2(gr, gi);
         }
-        __syncthreads();
+        lds_barrier();
         if (np > 1) {
             for (int bj = t; bj < items; bj += 256) {
                 float2 g = red[bj];
                 for (int p = 1; p < np; ++p) g.x += red[p * items + bj].x, g.y += red[p * items + bj].y;
                 gs[bj] = g;
             }
-            __syncthreads();
+            lds_barrier();
         }
         if constexpr (JFIX) {  // dU += r c^H, dV += x g^H on this thread's entries (column j0)
             const int j0 = t % R, e0 = t / R, es = 256 / R;
-#pragma unroll 2
+            const float4* at[HO];  // entries past the last one repeat it and are not stored
+#pragma unroll
+            for (int o = 0; o < HO; ++o) at[o] = xr + min(e0 + es * o, n3 - 1);
             for (int b = 0; b < nb; ++b) {
                 const float2 c = cs[b * R + j0], g = gs[b * R + j0];
 #pragma unroll
                 for (int o = 0; o < HO; ++o) {
-                    const int e = e0 + es * o;
-                    if (e < n3) {
-                        const float2 r = rs[b * n3 + e], x = xs[b * n3 + e];
-                        du[o].x += r.x * c.x + r.y * c.y;
-                        du[o].y += r.y * c.x - r.x * c.y;
-                        dv[o].x += x.x * g.x + x.y * g.y;
-                        dv[o].y += x.y * g.x - x.x * g.y;
-                    }
+                    const float4 x = *at[o];
+                    at[o] += XP;
+                    du[o].x += x.z * c.x + x.w * c.y;
+                    du[o].y += x.w * c.x - x.z * c.y;
+                    dv[o].x += x.x * g.x + x.y * g.y;
+                    dv[o].y += x.y * g.x - x.x * g.y;
                 }
             }
         } else {
@@ -997,17 +1018,17 @@ __global__ __launch_bounds__(256) void k_head(HeadArgs a) {
                 if (i < nf) {
                     const int e = i / R, j = i - e * R;
                     for (int b = 0; b < nb; ++b) {
-                        const float2 r = rs[b * n3 + e], c = cs[b * R + j];
-                        du[o].x += r.x * c.x + r.y * c.y;
-                        du[o].y += r.y * c.x - r.x * c.y;
-                        const float2 x = xs[b * n3 + e], g = gs[b * R + j];
+                        const float4 x = xr[b * XP + e];
+                        const float2 c = cs[b * R + j], g = gs[b * R + j];
+                        du[o].x += x.z * c.x + x.w * c.y;
+                        du[o].y += x.w * c.x - x.z * c.y;
                         dv[o].x += x.x * g.x + x.y * g.y;
                         dv[o].y += x.y * g.x - x.x * g.y;
                     }
                 }
             }
         }
-        __syncthreads();
+        lds_barrier();
     }
     lsum = wave_sum(lsum);
     if (lane == 0) lpart[w] = lsum;
@@ -1033,22 +1054,43 @@ __global__ __launch_bounds__(256) void k_head(HeadArgs a) {
     }
 }
 
-// dst[c][r] = src[r][c] for r < rows, c < cols (bfloat16), through a 64 x 64
-// LDS tile so that both the reads and the writes are row-contiguous.
-__global__ __launch_bounds__(256) void k_transpose_bf16(const bf16_t* __restrict__ src, int rows, int cols, int lds,
-                                                        bf16_t* __restrict__ dst, int ldd) {
-    __shared__ bf16_t tile[64][66];
-    const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
+// dL/dY [rows][cols] of the loss head: the transposed bfloat16 copy dst[col][row]
+// and the column sums of each 128-row chunk, part[chunk][col] (the sums of
+// k_grad_parts, in its order), from one reading.  64 columns x 128 rows per
+// workgroup: 32 rows a thread in flight, runs of 256 bytes read and written,
+// the transposition through LDS (rows of 65 words, so that neither side
+// conflicts).  Bound by its bytes: 1536 x 9216 (85 MB) take 13.7 us; a
+// transposition of the bfloat16 rows and column sums apart took 17 + 13 us.
+constexpr int HC = 128;  // rows of a chunk
+__global__ __launch_bounds__(256) void k_head_out(const float* __restrict__ Y, int rows, int cols,
+                                                  bf16_t* __restrict__ dst, int ldd, float* __restrict__ part, int ncol) {
+    __shared__ bf16_t tile[64][HC + 2];
+    __shared__ float red[8][64];
+    const int c0 = blockIdx.x * 64, r0 = blockIdx.y * HC;
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    for (int y = ty; y < 64; y += 4) {
-        const int r = r0 + y, c = c0 + tx;
-        tile[y][tx] = (r < rows && c < cols) ? src[(size_t)r * lds + c] : (bf16_t)0;
+    float v[HC / 4], s[2] = {0.0f, 0.0f};  // this thread's rows ty + 4 i; their sums by row % 8
+#pragma unroll
+    for (int i = 0; i < HC / 4; ++i) {
+        const int r = r0 + ty + 4 * i;
+        v[i] = r < rows && c0 + tx < cols ? Y[(size_t)r * cols + c0 + tx] : 0.0f;
     }
+#pragma unroll
+    for (int i = 0; i < HC / 4; ++i) {
+        s[i & 1] += v[i];
+        tile[tx][ty + 4 * i] = f2bf(v[i]);
+    }
+    red[ty][tx] = s[0];
+    red[ty + 4][tx] = s[1];
     __syncthreads();
-    for (int y = ty; y < 64; y += 4) {
-        const int c = c0 + y, r = r0 + tx;
-        if (c < cols && r < rows) dst[(size_t)c * ldd + r] = tile[tx][y];
+    if (ty == 0 && c0 + tx < cols) {
+        float t = 0.0f;
+        for (int g = 0; g < 8; ++g) t += red[g][tx];
+        part[(size_t)blockIdx.y * ncol + c0 + tx] = t;
     }
+    for (int c = ty; c < 64; c += 4)
+        if (c0 + c < cols && r0 + 2 * tx < rows)
+            *reinterpret_cast<uint32_t*>(dst + (size_t)(c0 + c) * ldd + r0 + 2 * tx) =
+                *reinterpret_cast<const uint32_t*>(&tile[c][2 * tx]);
 }
 
 // Preconditioner factors from the Jacobian model of each mode: with
@@ -1409,9 +1451,10 @@ hipError_t forward(opf_mlp* m, int rp, bool train) {
 }
 
 // Loss (of per-row losses lrow[0..nlive) over *wsum or count) and parameter
-// gradients from dL/dY (FP32 in Y, bfloat16 in dYb / dYT) after
-// forward(train = true) over rp rows.
-hipError_t backprop(opf_mlp* m, int rp, int nlive, const float* wsum, float count, float* loss_slot) {
+// gradients, as the partial sums that `g` describes, from dL/dY (FP32 in Y,
+// bfloat16 in dYb / dYT; ysums: its column sums already in part) after
+// forward(train = true) over rp rows.  k_grad_sum or k_adam adds them up.
+hipError_t backprop(opf_mlp* m, int rp, bool ysums, int nlive, const float* wsum, float count, float* loss_slot, GradArgs& g) {
     const int H = m->H, L = m->L, R = m->R, dout = m->dout;
     hipError_t st;
     Epi e{};
@@ -1428,7 +1471,7 @@ hipError_t backprop(opf_mlp* m, int rp, int nlive, const float* wsum, float coun
     a.DT = m->DT;
     if ((st = launch_chain(a, false, m->s)) != hipSuccess) return st;
 
-    GradArgs g{};
+    g = GradArgs{};
     g.DT = m->DT;
     g.HT = m->HT;
     g.XT = m->XT;
@@ -1470,7 +1513,7 @@ hipError_t backprop(opf_mlp* m, int rp, int nlive, const float* wsum, float coun
     g.gpart = m->gpart + g.osplit * nw;
 
     g.ngemm = (H / GT + g.nhid * (H / GT) * (H / GT)) * g.nsplit;
-    g.ch = std::max(128, (rp + CS_CHUNKS - 1) / CS_CHUNKS);
+    g.ch = std::max(HC, (rp + CS_CHUNKS - 1) / CS_CHUNKS);
     g.nch = (rp + g.ch - 1) / g.ch;
     g.part = m->part;
     g.lrow = m->lrow;
@@ -1478,26 +1521,25 @@ hipError_t backprop(opf_mlp* m, int rp, int nlive, const float* wsum, float coun
     g.count = count;
     g.nlive = nlive;
     g.loss = loss_slot;
-    hipLaunchKernelGGL(k_grad_parts, dim3(g.ngemm + g.nch * ((dout + (L + 1) * H) / 32) + 1), dim3(256), 0, m->s, g);
-    const long n = (g.osplit ? (long)nw : 0) + g.nph + dout;
-    hipLaunchKernelGGL(k_grad_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, m->s, g);
+    g.col0 = ysums ? dout : 0;
+    hipLaunchKernelGGL(k_grad_parts, dim3(g.ngemm + g.nch * ((dout + (L + 1) * H - g.col0) / 32) + 1), dim3(256), 0, m->s, g);
     return hipGetLastError();
 }
 
 // Squared-error loss of rows (targets t, weights om) into *loss_slot and
 // dL/dY, then the parameter gradients.
-hipError_t backward_rows(opf_mlp* m, const float* t, const float* om, int nrows, int rp, float* loss_slot) {
+hipError_t backward_rows(opf_mlp* m, const float* t, const float* om, int nrows, int rp, float* loss_slot, GradArgs& g) {
     hipStream_t s = m->s;
     hipLaunchKernelGGL(k_weight_sum, dim3(1), dim3(256), 0, s, om, nrows, m->wsum);
     hipLaunchKernelGGL(k_loss, dim3(rp / 4), dim3(256), 0, s, m->Y, t, om, m->wsum, nrows, rp, m->dout, m->dYb,
                        m->dYT, m->R, m->lrow);
     const hipError_t st = hipGetLastError();
-    return st != hipSuccess ? st : backprop(m, rp, nrows, m->wsum, 0.0f, loss_slot);
+    return st != hipSuccess ? st : backprop(m, rp, false, nrows, m->wsum, 0.0f, loss_slot, g);
 }
 
 // Loss head over pairs idx[0..batch) into *loss_slot and dL/dY, then the
 // parameter gradients (forward over the mode feature rows first).
-hipError_t backward_pairs(opf_mlp* m, const double* pairs, const int* idx, int batch, float* loss_slot) {
+hipError_t backward_pairs(opf_mlp* m, const double* pairs, const int* idx, int batch, float* loss_slot, GradArgs& g) {
     hipStream_t s = m->s;
     const int rp = round32(m->mode_rows);
     HeadArgs a{};
@@ -1517,24 +1559,32 @@ hipError_t backward_pairs(opf_mlp* m, const double* pairs, const int* idx, int b
     a.lrow = m->lrow;
     a.scale = (float)(1.0 / ((double)batch * m->mode_rows));
     a.hb = head_pairs(3 * m->N, m->rank);
-    const size_t hl = (size_t)head_slots(3 * m->N, m->rank, a.hb) * sizeof(float2);
+    const size_t hl = (size_t)(head_slots(3 * m->N, m->rank, a.hb) + 2 * a.hb) * sizeof(float2);  // (one entry of padding per pair)
     const int nf = 3 * m->N * m->rank, ho = nf <= 768 ? 3 : nf <= 1536 ? 6 : nf <= 2304 ? 9 : 12;
     const bool jfix = 256 % m->rank == 0;
     auto kh = jfix ? (ho == 3 ? k_head<3, true> : ho == 6 ? k_head<6, true> : ho == 9 ? k_head<9, true> : k_head<12, true>)
                    : (ho == 3 ? k_head<3, false> : ho == 6 ? k_head<6, false> : ho == 9 ? k_head<9, false> : k_head<12, false>);
     hipLaunchKernelGGL(kh, dim3(rp), dim3(256), hl, s, a);
-    hipLaunchKernelGGL(k_transpose_bf16, dim3((m->dout + 63) / 64, (rp + 63) / 64), dim3(256), 0, s, m->dYb, rp,
-                       m->dout, m->dout, m->dYT, m->R);
+    // (a chunk of the column sums is HC rows up to CS_CHUNKS HC = 8192 rows; the
+    // longest transform lines allow 64 x 127 modes)
+    if (rp > CS_CHUNKS * HC) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_head_out, dim3((m->dout + 63) / 64, (rp + HC - 1) / HC), dim3(256), 0, s, m->Y, rp, m->dout,
+                       m->dYT, m->R, m->part, m->dout + (m->L + 1) * m->H);
     const hipError_t st = hipGetLastError();
-    return st != hipSuccess ? st : backprop(m, rp, m->mode_rows, nullptr, (float)((long)batch * m->mode_rows), loss_slot);
+    return st != hipSuccess ? st : backprop(m, rp, true, m->mode_rows, nullptr, (float)((long)batch * m->mode_rows), loss_slot, g);
 }
 
-hipError_t adam(opf_mlp* m, float lr) {
+hipError_t adam(opf_mlp* m, const GradArgs& g, float lr) {
     m->t += 1;
     m->fac_ok = false;
     const float c1 = (float)(1.0 / (1.0 - std::pow((double)m->b1, (double)m->t)));
     const float c2 = (float)(1.0 / (1.0 - std::pow((double)m->b2, (double)m->t)));
-    hipLaunchKernelGGL(k_adam, dim3(m->segs.blk[m->segs.n]), dim3(256), 0, m->s, m->P, m->G, m->Am, m->Av, lr, m->b1, m->b2, c1, c2, m->eps, m->segs, m->Wb, m->Wt);
+    hipLaunchKernelGGL(k_adam, dim3(m->segs.blk[m->segs.n]), dim3(256), 0, m->s, m->P, g, m->Am, m->Av, lr, m->b1, m->b2, c1, c2, m->eps, m->segs, m->Wb, m->Wt);
+    return hipGetLastError();
+}
+
+hipError_t grad_sum(opf_mlp* m, const GradArgs& g) {
+    hipLaunchKernelGGL(k_grad_sum, dim3((unsigned)((m->np / 4 + 255) / 256)), dim3(256), 0, m->s, g, m->segs);
     return hipGetLastError();
 }
 
@@ -1752,7 +1802,9 @@ opf_status opf_mlp_gradient(opf_mlp* net, const float* x_dev, const float* t_dev
     const int rp = round32(rows);
     MCHK(net, rows_bf16(net, x_dev, rows, rp, true));
     MCHK(net, forward(net, rp, true));
-    MCHK(net, backward_rows(net, t_dev, w_dev, rows, rp, net->losses));
+    GradArgs g;
+    MCHK(net, backward_rows(net, t_dev, w_dev, rows, rp, net->losses, g));
+    if (grad_host) MCHK(net, grad_sum(net, g));
     float l = 0.0f;
     MCHK(net, hipMemcpyAsync(&l, net->losses, 4, hipMemcpyDeviceToHost, net->s));
     if (grad_host) MCHK(net, hipMemcpyAsync(grad_host, net->G, (size_t)net->np * 4, hipMemcpyDeviceToHost, net->s));
@@ -1778,9 +1830,10 @@ opf_status opf_mlp_train(opf_mlp* net, const float* x_dev, const float* t_dev, c
             const int rp = round32(n);
             MCHK(net, rows_bf16(net, x_dev + (size_t)r0 * net->din, n, rp, true));
             MCHK(net, forward(net, rp, true));
+            GradArgs g;
             MCHK(net, backward_rows(net, t_dev + (size_t)r0 * net->dout, w_dev ? w_dev + r0 : nullptr, n, rp,
-                                    net->losses + step));
-            MCHK(net, adam(net, net->lr));
+                                    net->losses + step, g));
+            MCHK(net, adam(net, g, net->lr));
             ++step;
         }
     }
@@ -1805,7 +1858,9 @@ opf_status opf_mlp_pair_gradient(opf_ctx* ctx, opf_mlp* net, const void* pairs_d
     MCHK(net, hipMemcpyAsync(net->idx, idx_host, (size_t)batch * 4, hipMemcpyHostToDevice, net->s));
     MCHK(net, feature_input(net));
     MCHK(net, forward(net, round32(net->mode_rows), true));
-    MCHK(net, backward_pairs(net, static_cast<const double*>(pairs_dev), net->idx, batch, net->losses));
+    GradArgs g;
+    MCHK(net, backward_pairs(net, static_cast<const double*>(pairs_dev), net->idx, batch, net->losses, g));
+    if (grad_host) MCHK(net, grad_sum(net, g));
     float l = 0.0f;
     MCHK(net, hipMemcpyAsync(&l, net->losses, 4, hipMemcpyDeviceToHost, net->s));
     if (grad_host) MCHK(net, hipMemcpyAsync(grad_host, net->G, (size_t)net->np * 4, hipMemcpyDeviceToHost, net->s));
@@ -1837,9 +1892,10 @@ opf_status opf_mlp_train_pairs(opf_ctx* ctx, opf_mlp* net, const void* pairs_dev
         const double c = 0.5 * (1.0 + std::cos(M_PI * st / std::max(steps, 1)));
         const float lr = (float)(net->lr_final + (net->lr - net->lr_final) * c);
         MCHK(net, forward(net, rp, true));
+        GradArgs g;
         MCHK(net, backward_pairs(net, static_cast<const double*>(pairs_dev), net->idx + (size_t)st * batch, batch,
-                                 net->losses + st));
-        MCHK(net, adam(net, lr));
+                                 net->losses + st, g));
+        MCHK(net, adam(net, g, lr));
     }
     if (loss_host && steps > 0) MCHK(net, hipMemcpyAsync(loss_host, net->losses, (size_t)steps * 4,
                                                          hipMemcpyDeviceToHost, net->s));

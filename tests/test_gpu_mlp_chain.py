@@ -45,3 +45,35 @@ def test_gradients_and_step_match_bf16_oracle(torch_cuda, width, layers, n):  # 
     assert nrel(net.forward(xd).cpu().numpy().astype(np.float64), y) <= 1e-2
     _, g = net.gradient(xd, td)
     check_grads(g, backward(q, cache, y, t64, layers, bf16=True), layers)
+
+
+@pytest.mark.parametrize("N, M, K, rank, batch", [
+    (24, 2, 2, 1, 1),     # fewest rows; output columns end half way through a 64-wide tile
+    (24, 12, 6, 3, 9),    # 132 rows: a second chunk of column sums; two pairs per wave, a last pass of one pair
+    (48, 3, 4, 16, 13),   # the benchmark's profile length and rank: four passes, the last of one pair
+    (64, 2, 3, 16, 5),    # the most gradient entries per thread
+    (64, 2, 3, 13, 6)])   # the same with a rank that does not divide 256
+def test_pair_gradient_edges(torch_cuda, N, M, K, rank, batch):  # noqa: F811
+    """The loss head and the one reading of dL/dY that follows it.  Loss: 1e-5
+    against the oracle's head on the device's own rows (FP32 sums over 3 N
+    entries, 192 2^-24); gradients as above."""
+    import paper_1705_03838_amd as opf
+    from gpu_support import make_solver
+    from oracle.mlp import backprop, feature_rows, flatten, forward, head, init_params, unflatten
+    s = make_solver(N=N, M=M, K=K, mp=1, alpha=0.9, Re=1500.0, dt=0.005)
+    net = opf.Mlp(s, width=64, layers=2, rank=rank)
+    flat = flatten(init_params(net.din, 64, 2, net.dout, seed=N + rank), 2).astype(np.float32)
+    net.set_params(flat)
+    p = unflatten(flat.astype(np.float64), net.din, 64, 2, net.dout)
+    rng = np.random.default_rng(rank + batch)
+    pairs = rng.standard_normal((4, 2) + s.shape) + 1j * rng.standard_normal((4, 2) + s.shape)
+    idx = rng.integers(0, 4, batch).astype(np.int32)
+    say("pair gradient", N, M, K, rank, batch)
+    lg, g = net.pair_gradient(torch_cuda.from_numpy(pairs), idx)
+    X = feature_rows(M, K, 1, 0.9)
+    rows_dev = net.forward(torch_cuda.from_numpy(X.astype(np.float32))).cpu().numpy().astype(np.float64)
+    ldev, _ = head(rows_dev, pairs[idx], rank)
+    assert abs(lg - ldev) <= 1e-5 * ldev
+    F, cache = forward(p, X, 2, bf16=True)
+    _, dF = head(F.astype(np.float32).astype(np.float64), pairs[idx], rank)
+    check_grads(g, backprop(p, cache, dF, 2, bf16=True), 2)

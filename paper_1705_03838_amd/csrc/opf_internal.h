@@ -123,7 +123,7 @@ struct AuxArgs {
     double alpha;
     const double* u;    // complex128 external layout
     double* w;          // complex128 output (vorticity)
-    double* partial;    // [M][2] per-m sums of |u|^2 and |omega|^2 (quadrature weighted)
+    double* partial;    // [M nk][4] diagnostics per mode (k_diag)
     const double* wall; // wall velocity as in SolveArgs, or null
     Tables t;
 };
@@ -196,10 +196,9 @@ int context_gm(int mp, int M, int K);    // of a single context
 bool gm_ok(int gm, int mp);
 constexpr int NFH = 6;  // Helmholtz operators that the m of one solve workgroup may use
 hipError_t launch_vorticity(const AuxArgs& a, hipStream_t s);
-hipError_t launch_energy(const AuxArgs& a, hipStream_t s);
-// Per mode q: part[2q] = max |g| of (u+(1), u-(1), u_z(1), div u(1)),
-// part[2q+1] = max over interior nodes of |div u|.
-hipError_t launch_divg(const AuxArgs& a, double* part, hipStream_t s);
+hipError_t launch_diag(const AuxArgs& a, hipStream_t s);
+// out[2M + 2N + 4]: see k_diag_pack
+hipError_t launch_diag_pack(const AuxArgs& a, const double* cpart, int ncp, const double* beta, double* out, hipStream_t s);
 // Largest |u_r| wr[n] + |u_theta| wt[n] + |u_z| wz over the physical points
 // of each (n, 4-point z tile) workgroup into out[block], from the
 // z-transformed fields in a.H (stage 0 of the nonlinear term).

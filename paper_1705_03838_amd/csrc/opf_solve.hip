@@ -606,40 +606,123 @@ __global__ __launch_bounds__(64) void k_vorticity(AuxArgs a) {
     }
 }
 
-// Per-m quadrature sums of |u|^2 and |omega|^2 over k and the three
-// components (diagnostics); fixed summation order.
-__global__ __launch_bounds__(256) void k_energy(AuxArgs a) {
-    __shared__ double s_u[256], s_w[256];
-    const int N = a.N, nk = a.nk, mi = blockIdx.x;
-    const size_t S = (size_t)a.M * nk * N;
-    double eu = 0.0, ew = 0.0;
-    for (int i = threadIdx.x; i < nk * N; i += 256) {
-        const int n = i % N;
-        const size_t off = (size_t)mi * nk * N + i;
-        double su = 0.0, sw = 0.0;
-        for (int c = 0; c < 3; ++c) {
-            const dcplx u = load_c<double>(a.u, c * S + off);
-            const dcplx w = load_c<double>(a.w, c * S + off);
-            su += u.x * u.x + u.y * u.y;
-            sw += w.x * w.x + w.y * w.y;
-        }
-        eu += a.t.quad[n] * su;
-        ew += a.t.quad[n] * sw;
-    }
-    s_u[threadIdx.x] = eu;
-    s_w[threadIdx.x] = ew;
+// Diagnostics of the state.  Per mode q = (m, k): partial[4q] = max |g| of
+// (u+(1), u-(1), u_z(1), div u(1)), then max over the interior nodes of
+// |div u|, and the quadrature sums of |u|^2 and |omega|^2 over the three
+// components.  One wave per mode, lanes are radial nodes: u is read once and
+// omega stays in registers.  (Vorticity, energies by one workgroup per m and
+// divergence apart took 4.5 + 8.8 + 4.0 us at 48 x 32 x 63 modes and a launch
+// each; this one 5.9.)
+__global__ __launch_bounds__(64) void k_diag(AuxArgs a) {
+    __shared__ dcplx sL[3][LSTR];
+    const int N = a.N, K = a.K, nk = a.nk;
+    const int q = blockIdx.x, mi = q / nk, kk = q % nk;
+    const int m = a.mp * mi, n = threadIdx.x, nr = min(n, N - 1);
+    const double kap = a.alpha * (kk - (K - 1)), rinv = a.t.rinv[nr];
+    const size_t S = (size_t)a.M * nk * N, off = (size_t)q * N + nr;
+    const dcplx ur = load_c<double>(a.u, off), ut = load_c<double>(a.u, S + off), uz = load_c<double>(a.u, 2 * S + off);
+    Row9 de, dod;  // d/dr, parity of m and of m +- 1
+    de.load(a.t.d1, N, m & 1, nr);
+    dod.load(a.t.d1, N, (m + 1) & 1, nr);
+    sL[0][n] = ur;
+    sL[1][n] = ut;
+    sL[2][n] = uz;
     __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (threadIdx.x < h) {
-            s_u[threadIdx.x] += s_u[threadIdx.x + h];
-            s_w[threadIdx.x] += s_w[threadIdx.x + h];
+    const int s0 = a.t.s0[nr];
+    const dcplx dr = dod.apply(sL[0], s0), dt = dod.apply(sL[1], s0), dz = de.apply(sL[2], s0);
+    dcplx w[3];
+    curl_row(dz, dt, rinv, m, kap, ur, ut, uz, w[0], w[1], w[2]);
+    double gv = 0.0, dv = 0.0, eu = 0.0, ew = 0.0;
+    if (n < N) {
+        const double wq = a.t.quad[n];
+        eu = wq * ((ur.x * ur.x + ur.y * ur.y) + (ut.x * ut.x + ut.y * ut.y) + (uz.x * uz.x + uz.y * uz.y));
+        ew = wq * ((w[0].x * w[0].x + w[0].y * w[0].y) + (w[1].x * w[1].x + w[1].y * w[1].y) +
+                   (w[2].x * w[2].x + w[2].y * w[2].y));
+        // div u from u+- = u_r +- i u_theta, as the influence matrix drives it
+        const dcplx up = ur + ix(ut), um = ur - ix(ut);
+        const dcplx ap = (dr + ix(dt)) + (double(1 + m) * rinv) * up;
+        const dcplx am = (dr - ix(dt)) + (double(1 - m) * rinv) * um;
+        const dcplx d = 0.5 * (ap + am) + kap * ix(uz);
+        const double ad = sqrt(d.x * d.x + d.y * d.y);
+        if (n == N - 1) {
+            dcplx bp = {0.0, 0.0}, bm = {0.0, 0.0}, bz = {0.0, 0.0};
+            if (a.wall) {  // residual against the wall velocity
+                const size_t wi = (size_t)q * 2, ws = (size_t)a.M * nk * 2;
+                const dcplx br = {a.wall[wi], a.wall[wi + 1]}, bt = {a.wall[ws + wi], a.wall[ws + wi + 1]};
+                bp = br + ix(bt);
+                bm = br - ix(bt);
+                bz = dcplx{a.wall[2 * ws + wi], a.wall[2 * ws + wi + 1]};
+            }
+            const dcplx ep = up - bp, em = um - bm, ez = uz - bz;
+            const double a1 = sqrt(ep.x * ep.x + ep.y * ep.y), a2 = sqrt(em.x * em.x + em.y * em.y);
+            const double a3 = sqrt(ez.x * ez.x + ez.y * ez.y);
+            gv = fmax(fmax(a1, a2), fmax(a3, ad));
+        } else {
+            dv = ad;
         }
-        __syncthreads();
     }
-    if (threadIdx.x == 0) {
-        a.partial[2 * mi] = s_u[0];
-        a.partial[2 * mi + 1] = s_w[0];
+    for (int o = 32; o > 0; o >>= 1) {
+        gv = fmax(gv, __shfl_xor(gv, o, 64));
+        dv = fmax(dv, __shfl_xor(dv, o, 64));
+        eu += __shfl_xor(eu, o, 64);
+        ew += __shfl_xor(ew, o, 64);
     }
+    if (n == 0) {
+        double* p = a.partial + 4 * (size_t)q;
+        p[0] = gv;
+        p[1] = dv;
+        p[2] = eu;
+        p[3] = ew;
+    }
+}
+
+// What the host needs of the diagnostics, packed for one copy (five copies to
+// host memory cost 25..30 us each): out[2m], out[2m + 1] = the sums of k_diag
+// over k, then the (0,0) profile of u_z (2 N), the maxima of |g|, |div u| and of
+// the ncp CFL parts, and beta.  One workgroup.
+__global__ __launch_bounds__(1024) void k_diag_pack(AuxArgs a, const double* __restrict__ cpart, int ncp,
+                                                    const double* __restrict__ beta, double* __restrict__ out) {
+    __shared__ double red[16][3];
+    const int M = a.M, N = a.N, nk = a.nk, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    double g = 0.0, d = 0.0, c = 0.0;
+    for (int mi = wv; mi < M; mi += 16) {
+        double eu = 0.0, ew = 0.0;
+        for (int k = lane; k < nk; k += 64) {
+            const double* p = a.partial + 4 * ((size_t)mi * nk + k);
+            g = fmax(g, p[0]);
+            d = fmax(d, p[1]);
+            eu += p[2];
+            ew += p[3];
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            eu += __shfl_xor(eu, o, 64);
+            ew += __shfl_xor(ew, o, 64);
+        }
+        if (lane == 0) {
+            out[2 * mi] = eu;
+            out[2 * mi + 1] = ew;
+        }
+    }
+    for (int i = t; i < ncp; i += 1024) c = fmax(c, cpart[i]);
+    const double* uz = a.u + 2 * (2 * (size_t)M * nk * N + (size_t)(a.K - 1) * N);
+    for (int i = t; i < 2 * N; i += 1024) out[2 * M + i] = uz[i];
+    for (int o = 32; o > 0; o >>= 1) {
+        g = fmax(g, __shfl_xor(g, o, 64));
+        d = fmax(d, __shfl_xor(d, o, 64));
+        c = fmax(c, __shfl_xor(c, o, 64));
+    }
+    if (lane == 0) {
+        red[wv][0] = g;
+        red[wv][1] = d;
+        red[wv][2] = c;
+    }
+    __syncthreads();
+    if (t < 3) {
+        double v = 0.0;
+        for (int i = 0; i < 16; ++i) v = fmax(v, red[i][t]);
+        out[2 * M + 2 * N + t] = v;
+    }
+    if (t == 3) out[2 * M + 2 * N + 3] = *beta;
 }
 
 int default_gm(int mp) { return mp == 1 ? 4 : (mp <= 3 ? 2 : 1); }
@@ -686,75 +769,18 @@ hipError_t launch_solve(const SolveArgs& a, int precision, hipStream_t s, const 
     return launch_solve_any(a, nullptr, 1, precision, s, kt);
 }
 
-// Boundary-condition residual and interior divergence of every mode (one
-// 64-lane workgroup per mode, lanes = radial nodes), in the (+,-,z) form
-// (u+- = u_r +- i u_theta): div u = (1/2)[u+' + (1+m) u+/r]
-// + (1/2)[u-' + (1-m) u-/r] + i kappa u_z.  part[2q] = max(|u+(1)|, |u-(1)|,
-// |u_z(1)|, |div u(1)|), part[2q+1] = max over n < N-1 of |div u(r_n)|.
-__global__ __launch_bounds__(64) void k_divg(AuxArgs a, double* __restrict__ part) {
-    __shared__ dcplx sL[3][LSTR];
-    const int N = a.N, K = a.K, nk = a.nk;
-    const int q = blockIdx.x, mi = q / nk, kk = q % nk;
-    const int m = a.mp * mi, n = threadIdx.x;
-    const double kap = a.alpha * (kk - (K - 1));
-    const size_t S = (size_t)a.M * nk * N;
-    const size_t off = (size_t)q * N + n;
-    if (n < N) {
-        const dcplx ur = load_c<double>(a.u, off), ut = load_c<double>(a.u, S + off);
-        sL[0][n] = ur + ix(ut);
-        sL[1][n] = ur - ix(ut);
-        sL[2][n] = load_c<double>(a.u, 2 * S + off);
-    }
-    __syncthreads();
-    double gv = 0.0, dv = 0.0;
-    if (n < N) {
-        const int s0 = a.t.s0[n];
-        const double rinv = a.t.rinv[n];
-        const double* w1 = a.t.d1 + (((m + 1) & 1) * N + n) * W9;
-        const dcplx up = sL[0][n], um = sL[1][n], uz = sL[2][n];
-        const dcplx ap = stencil(w1, sL[0], s0) + (double(1 + m) * rinv) * up;
-        const dcplx am = stencil(w1, sL[1], s0) + (double(1 - m) * rinv) * um;
-        const dcplx d = 0.5 * (ap + am) + kap * ix(uz);
-        const double ad = sqrt(d.x * d.x + d.y * d.y);
-        if (n == N - 1) {
-            dcplx bp = {0.0, 0.0}, bm = {0.0, 0.0}, bz = {0.0, 0.0};
-            if (a.wall) {  // residual against the wall velocity
-                const size_t wi = (size_t)q * 2, ws = (size_t)a.M * nk * 2;
-                const dcplx br = {a.wall[wi], a.wall[wi + 1]}, bt = {a.wall[ws + wi], a.wall[ws + wi + 1]};
-                bp = br + ix(bt);
-                bm = br - ix(bt);
-                bz = dcplx{a.wall[2 * ws + wi], a.wall[2 * ws + wi + 1]};
-            }
-            const dcplx ep = up - bp, em = um - bm, ez = uz - bz;
-            const double a1 = sqrt(ep.x * ep.x + ep.y * ep.y), a2 = sqrt(em.x * em.x + em.y * em.y);
-            const double a3 = sqrt(ez.x * ez.x + ez.y * ez.y);
-            gv = fmax(fmax(a1, a2), fmax(a3, ad));
-        } else {
-            dv = ad;
-        }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        gv = fmax(gv, __shfl_xor(gv, o, 64));
-        dv = fmax(dv, __shfl_xor(dv, o, 64));
-    }
-    if (n == 0) {
-        part[2 * q] = gv;
-        part[2 * q + 1] = dv;
-    }
-}
-
-hipError_t launch_divg(const AuxArgs& a, double* part, hipStream_t s) {
-    hipLaunchKernelGGL(k_divg, dim3(a.M * a.nk), dim3(64), 0, s, a, part);
-    return hipGetLastError();
-}
-
 hipError_t launch_vorticity(const AuxArgs& a, hipStream_t s) {
     hipLaunchKernelGGL(k_vorticity, dim3(a.M * a.nk), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_energy(const AuxArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_energy, dim3(a.M), dim3(256), 0, s, a);
+hipError_t launch_diag(const AuxArgs& a, hipStream_t s) {
+    hipLaunchKernelGGL(k_diag, dim3(a.M * a.nk), dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_diag_pack(const AuxArgs& a, const double* cpart, int ncp, const double* beta, double* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_diag_pack, dim3(1), dim3(1024), 0, s, a, cpart, ncp, beta, out);
     return hipGetLastError();
 }
 

@@ -1766,8 +1766,14 @@ opf_status opf_mlp_dims(const opf_mlp* net, int32_t* din, int32_t* dout, int64_t
 
 opf_status opf_mlp_set_params(opf_mlp* net, const float* host, int64_t n) {
     if (!net || !host || n != net->np) return OPF_E_INVALID;
-    for (int64_t i = 0; i < n; ++i)
-        if (!std::isfinite(host[i])) return OPF_E_INVALID;
+    for (int64_t i = 0; i < n;) {
+        // no exit per value, so that the test vectorises: the call takes
+        // 0.48 ms for 2.64 M values, 0.88 with one
+        const int64_t e = std::min<int64_t>(n, i + 4096);
+        uint32_t bad = 0;
+        for (; i < e; ++i) bad |= (__builtin_bit_cast(uint32_t, host[i]) & 0x7F800000u) == 0x7F800000u;
+        if (bad) return OPF_E_INVALID;
+    }
     MCHK(net, hipMemcpyAsync(net->P, host, (size_t)n * 4, hipMemcpyHostToDevice, net->s));
     MCHK(net, hipMemsetAsync(net->Am, 0, (size_t)n * 4, net->s));
     MCHK(net, hipMemsetAsync(net->Av, 0, (size_t)n * 4, net->s));

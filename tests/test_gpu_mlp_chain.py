@@ -77,3 +77,22 @@ def test_pair_gradient_edges(torch_cuda, N, M, K, rank, batch):  # noqa: F811
     F, cache = forward(p, X, 2, bf16=True)
     _, dF = head(F.astype(np.float32).astype(np.float64), pairs[idx], rank)
     check_grads(g, backprop(p, cache, dF, 2, bf16=True), 2)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+def test_set_params_refuses_non_finite_values(torch_cuda, bad):  # noqa: F811
+    """Wherever the value stands in the blocks of the test, and without a
+    change to the parameters that are there; the largest finite value passes."""
+    import paper_1705_03838_amd as opf
+    s, net, _ = make_net(torch_cuda)
+    p0 = net.get_params()
+    for i in (0, 4095, 4096, net.n_params - 1):
+        q = p0.copy()
+        q[i] = bad
+        with pytest.raises(opf.OpfError):
+            net.set_params(q)
+    assert np.array_equal(net.get_params(), p0)
+    q = p0.copy()
+    q[4096] = np.finfo(np.float32).max
+    net.set_params(q)
+    assert np.array_equal(net.get_params(), q)

@@ -18,7 +18,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("N,M,K,rot", [(64, M, 18, 0.0) for M in (2, 3, 4, 6, 8, 12, 16, 18, 24, 32, 36, 48, 64)] +
-                         [(64, 12, 18, 0.3), (64, 16, 18, 0.3), (52, 6, 24, 0.0), (51, 6, 24, 0.0), (37, 12, 32, 0.0)])
+                         [(64, 12, 18, 0.3), (64, 16, 18, 0.3), (52, 6, 24, 0.0), (51, 6, 24, 0.0), (37, 12, 32, 0.0)] +
+                         # the fewest workgroups in FP64 (144) and on lines of 72 in FP32 (192), and fewer
+                         [(48, 6, 16, 0.0), (47, 6, 16, 0.0), (64, 24, 16, 0.0), (63, 24, 16, 0.0)])
 def test_nonlinear_wide(N, M, K, rot, precision):
     import torch
 

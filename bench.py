@@ -54,15 +54,12 @@ def kernel_bytes(name, N, M, K, mixed):
 
 def solve_table_bytes(N, M, K, mp):
     """Operator tables one solve launch reads once besides the spectral
-    fields, which the algorithmic count leaves out: the substitution images
-    (8 NB + 32 doubles each, for N = NB) of the M K pressure and MU K
-    Helmholtz operators, their 1/U_ii rows (NB doubles), the influence data
-    (7 radial lines per (m, |k|)) and the 4 x 4 complex A^-1 per (m, k).
-    None where N is not a padded row count (other image sizes)."""
-    if N not in (32, 48, 64):
-        return None
-    MU, nk, NB = mp * (M - 1) + 2, 2 * K - 1, N
-    return 8 * ((M + MU) * K * (8 * NB + 32 + NB) + M * K * 7 * N + M * nk * 32)
+    fields, which the algorithmic count leaves out: the block images (4 x 4
+    inverse diagonal blocks, 16 (nt + 4) doubles each, nt of them before the
+    last two) of the M K pressure and MU K Helmholtz operators, the influence
+    data (7 radial lines per (m, |k|)) and the 4 x 4 complex A^-1 per (m, k)."""
+    MU, nk, nt = mp * (M - 1) + 2, 2 * K - 1, ((N - 5) // 4 + 1) // 2 * 2
+    return 8 * ((M + MU) * K * 16 * (nt + 4) + M * K * 7 * N + M * nk * 32)
 
 
 def step_bytes(N, M, K, mixed):
@@ -576,8 +573,8 @@ def main():
         ach = b / (avg_ms * 1e-3) / 1e9
         tr = traffic_for(dom, prec, args.workload)
         extra = {}
-        tab = solve_table_bytes(N, M, K, w["mp"]) if dom == "solve" else None
-        if tab is not None:  # the solve's traffic also holds its operator tables
+        if dom == "solve":  # the solve's traffic also holds its operator tables
+            tab = solve_table_bytes(N, M, K, w["mp"])
             extra = {"tables_bytes_per_launch": tab,
                      "achieved_with_tables": round((b + tab) / (avg_ms * 1e-3) / 1e9, 1)}
         return {"bound": "hbm", "kernel": dom, "achieved": round(ach, 1), "peak": HBM_PEAK_GBS,

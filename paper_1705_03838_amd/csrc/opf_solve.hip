@@ -12,8 +12,8 @@
 // One wave handles |k| and one m, both signs of k: two modes, four real
 // right-hand sides per system.  Lanes are radial nodes for the stencil work;
 // the banded systems are solved in block form (btd_nt in opf_internal.h) on
-// the FP64 matrix cores.  The waves share nothing but a workgroup's L1, so
-// there is no workgroup barrier.  m = 0 solves k >= 0 only and writes the
+// the FP64 matrix cores.  The waves of a workgroup share the coupling
+// tiles and an L1 and meet at one barrier.  m = 0 solves k >= 0 only and writes the
 // conjugate into -k (Hermitian symmetry of a real field); mode (0,0) has
 // u_r = 0, no pressure and the fixed-flux correction.
 #include "opf_internal.h"
@@ -210,7 +210,7 @@ constexpr size_t solve_lds(int nt, int gm) {
 // and, on small grids, the length of one wave's phases.  Predictor / corrector
 // at 64 x 48 x 127 modes: 22.5 / 24.6 us in FP64 (26.0 / 28.1 with scalar
 // banded factors shared through LDS and substituted by one wave of each
-// workgroup), 21.6 / 23.4 in mixed precision (25.1 / 27.0); 24 x 8 x 15: 5.8 us
+// workgroup), 21.2 / 22.9 in mixed precision (25.1 / 27.0); 24 x 8 x 15: 5.8 us
 // (12.4); 41 x 18 x 23, mp = 3: 8.1 us (14.1); 48 x 24 x 63, mp = 2: 10.8 us
 // (15.5).  Measured and dropped: every request made at the start with two waves
 // per SIMD (42 us at 64 x 48 x 127), four waves per SIMD (38 us, spills), the

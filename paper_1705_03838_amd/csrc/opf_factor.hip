@@ -8,6 +8,7 @@
 #include <cmath>
 
 #include "opf_internal.h"
+#include "opf_pair.h"
 
 namespace opf {
 namespace {
@@ -17,30 +18,6 @@ constexpr int BW = 13;  // band entries per row: offsets -8..+4 from the diagona
 __device__ inline double wave_max(double v) {
     for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o));
     return v;
-}
-
-// Unevaluated sums of two doubles (Dekker 1971; products by multiply-add):
-// about 106 bits.
-struct dd {
-    double hi, lo;
-};
-__device__ inline dd two_sum(double a, double b) {
-    const double s = a + b, t = s - a;
-    return {s, (a - (s - t)) + (b - t)};
-}
-__device__ inline dd renorm(double a, double b) {  // |a| >= |b|
-    const double s = a + b;
-    return {s, b - (s - a)};
-}
-__device__ inline dd operator-(dd a) { return {-a.hi, -a.lo}; }
-__device__ inline dd operator+(dd a, dd b) {
-    const dd s = two_sum(a.hi, b.hi), t = two_sum(a.lo, b.lo);
-    const dd u = renorm(s.hi, s.lo + t.hi);
-    return renorm(u.hi, u.lo + t.lo);
-}
-__device__ inline dd operator*(dd a, dd b) {
-    const double p = a.hi * b.hi;
-    return renorm(p, fma(a.hi, b.hi, -p) + (a.hi * b.lo + a.lo * b.hi));
 }
 
 // LDS of one block elimination, entry [r][c] of a block at 8 r + c.
@@ -67,7 +44,7 @@ __device__ dd small_inverse(BlockLds& w, int n, int lane, int& bad) {
     w.x[lane] = v;
     __builtin_amdgcn_wave_barrier();
     dd e = {r == c ? 1.0 : 0.0, 0.0};
-    for (int k = 0; k < n; ++k) e = e + -(w.d[8 * r + k] * dd{w.x[8 * k + c], 0.0});
+    for (int k = 0; k < n; ++k) e = madd(e, w.d[8 * r + k], -w.x[8 * k + c]);
     __builtin_amdgcn_wave_barrier();
     w.gc[lane] = e;
     __builtin_amdgcn_wave_barrier();
@@ -80,10 +57,11 @@ __device__ dd small_inverse(BlockLds& w, int n, int lane, int& bad) {
 // The image of the operator L - shift whose band rows (of L; the wall row is
 // the identity's) are in T, offsets -8..+4: the block elimination described
 // at btd_nt.  It runs on pairs of doubles, so that the inverse blocks are
-// right to about a unit in the last place: their errors act on every step in
-// the same way, and in plain double precision they made the state drift twice
-// as fast as a banded LU's (2.4e-15 against 1.2e-15 of the state after 16
-// steps of the 64 x 48 x 127-mode grid).  Called by all 64 lanes of one wave.
+// right to a unit in the last place (1.2e-15 of a block's largest entry, of
+// which their entries' own rounding; 5e-15 in plain double): their errors act
+// on every step in the same way.  100 diffusion steps of u_theta(0,0) at N =
+// 64 stay within 0.8e-14 of the same steps in extended precision (banded LU
+// factors: 3.5e-14).  Called by all 64 lanes of one wave.
 __device__ void block_image(const FactorArgs& a, const double* T, double shift, double* G, BlockLds& w, int lane, int& bad) {
     const int N = a.N, nt = a.nt, pad = btd_rows(nt) - N, r = lane >> 3, c = lane & 7;
     auto at = [&](int row, int col) {  // padded row and column; padding rows are rows of the identity
@@ -101,11 +79,11 @@ __device__ void block_image(const FactorArgs& a, const double* T, double shift, 
             // D_{I-1}^{-1} C_{I-1}; C reaches the first four columns of block I only
             dd s = {0.0, 0.0};
             if (r < 4 && c < 4)
-                for (int k = 0; k < 4; ++k) s = s + w.inv[8 * r + k] * dd{at(r0 - 4 + k, r0 + c), 0.0};
+                for (int k = 0; k < 4; ++k) s = madd(s, w.inv[8 * r + k], at(r0 - 4 + k, r0 + c));
             w.gc[lane] = s;
             __builtin_amdgcn_wave_barrier();
             if (r < n && c < 4)
-                for (int k = 0; k < 4; ++k) d = d + dd{-at(r0 + r, r0 - 4 + k), 0.0} * w.gc[8 * k + c];
+                for (int k = 0; k < 4; ++k) d = madd(d, w.gc[8 * k + c], -at(r0 + r, r0 - 4 + k));
             __builtin_amdgcn_wave_barrier();
         }
         w.d[lane] = d;

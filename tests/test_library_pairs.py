@@ -1,5 +1,6 @@
-"""Pair arithmetic of the operator tables, compiled for the host with the
-contraction that device code is compiled with, against exact rationals.
+"""Pair arithmetic of the operator tables: compiled for the host, against exact
+rationals; compiled for the device with the library's flags, the operations of
+one product, none of them contracted.
 
 Tolerance: s + a b on pairs of 53-bit numbers loses a few units of 2^-106 of
 its largest term; 2^-100 of |s| + |a b| leaves room for eight of the
@@ -8,6 +9,7 @@ by up to 2^-53 of it.
 """
 import ctypes
 import os
+import re
 import subprocess
 from fractions import Fraction
 
@@ -33,8 +35,7 @@ extern "C" void madds(int n, const double* s, const double* a, const double* b, 
 def test_sum_and_product_of_pairs(tmp_path):
     src, lib = tmp_path / "pairs.hip", tmp_path / "pairs.so"
     src.write_text(SOURCE)
-    subprocess.run(["/opt/rocm/bin/hipcc", "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xarch_host", "-mfma",
-                    "-ffp-contract=fast-honor-pragmas", "-fPIC",
+    subprocess.run(["/opt/rocm/bin/hipcc", "-O3", "-std=c++17", "--offload-arch=gfx950", "-Xarch_host", "-mfma", "-fPIC",
                     "-shared", "-w", "-I", CSRC, str(src), "-o", str(lib)], check=True, timeout=300)
     rng = np.random.default_rng(1)
     n = 4000
@@ -53,3 +54,22 @@ def test_sum_and_product_of_pairs(tmp_path):
         S, A, B, R = (Fraction(float(v[0])) + Fraction(float(v[1])) for v in (s[i], a[i], (b[i], 0.0), out[i]))
         worst = max(worst, float(abs(R - (S + A * B)) / (abs(S) + abs(A * B))))
     assert worst <= 2.0 ** -100, worst
+
+
+KERNEL = """
+#include "opf_pair.h"
+extern "C" __global__ void product(const opf::dd* a, const double* b, opf::dd* out) { *out = *a * *b; }
+"""
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="needs hipcc")
+def test_device_product_is_not_contracted(tmp_path):
+    from paper_1705_03838_amd.build import FLAGS, HIPCC
+    src, out = tmp_path / "product.hip", tmp_path / "product.s"
+    src.write_text(KERNEL)
+    flags = [f for f in FLAGS if f != "-fPIC"]
+    subprocess.run([HIPCC, *flags, "-w", "--cuda-device-only", "-S", "-I", CSRC, str(src), "-o", str(out)], check=True,
+                   timeout=300)
+    ops = re.findall(r"^\s+v_(mul|fma|fmac|add)_f64", out.read_text(), re.M)
+    # a_hi b and a_lo b; the first product's error; their sum and the three sums of the renormalisation
+    assert (ops.count("mul"), ops.count("fma") + ops.count("fmac"), ops.count("add")) == (2, 1, 4), ops

@@ -464,9 +464,11 @@ NLArgs nl_args(const opf_ctx* c, const void* u, const void* w, void* out) {
 // The scale of the Helmholtz systems, Re / c, and the shift Re / (c dt) of the
 // scaled operator.  Steps multiply the state by scale / (dt shift), which has
 // to be 1: of the doubles within four units in the last place of Re / c the
-// one whose product with 1/dt rounds least is taken.
+// one whose product with 1/dt rounds least is taken.  A shift above 2^800,
+// which may not be finite (no viscosity, Re = infinity), is replaced by 2^800:
+// the rest of the operator is below the last place of either.
 void helmholtz_scale(const opf_params& p, double* scale, double* shift) {
-    const double inv_dt = 1.0 / p.dt, mid = p.Re / p.c;
+    const double inv_dt = 1.0 / p.dt, mid = std::min(p.Re / p.c, 0x1p800 * p.dt);
     double h = mid, best = INFINITY;
     for (int j = 0; j < 4; ++j) h = std::nextafter(h, 0.0);
     for (int j = 0; j < 9; ++j, h = std::nextafter(h, INFINITY)) {

@@ -469,15 +469,19 @@ NLArgs nl_args(const opf_ctx* c, const void* u, const void* w, void* out) {
 // the rest of the operator is below the last place of either.
 void helmholtz_scale(const opf_params& p, double* scale, double* shift) {
     const double inv_dt = 1.0 / p.dt, mid = std::min(p.Re / p.c, 0x1p800 * p.dt);
-    double h = mid, best = INFINITY;
-    for (int j = 0; j < 4; ++j) h = std::nextafter(h, 0.0);
-    for (int j = 0; j < 9; ++j, h = std::nextafter(h, INFINITY)) {
+    double best = INFINITY, lo = mid, hi = mid;
+    auto consider = [&](double h) {
         const double k = h * inv_dt, err = std::fabs(std::fma(h, inv_dt, -k)) / k;
         if (err < best) {
             best = err;
             *scale = h;
             *shift = k;
         }
+    };
+    consider(mid);
+    for (int j = 0; j < 4; ++j) {  // outwards: the nearest of equals
+        consider(lo = std::nextafter(lo, 0.0));
+        consider(hi = std::nextafter(hi, INFINITY));
     }
     if (!(best < INFINITY)) {
         *scale = mid;

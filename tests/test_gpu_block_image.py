@@ -123,3 +123,18 @@ def test_images_are_right_to_a_unit_in_the_last_place(N, mp, Re, dt):
     print("worst %.2e, plain double %.2e" % (worst, plain), flush=True)
     assert plain > BOUND
     assert worst <= BOUND
+
+
+@pytest.mark.gpu
+def test_scale_is_not_moved_without_need():
+    """1/dt a power of two: Re / c times 1/dt is exact, so the shift is that of
+    Re / c itself.  At Re = 1e30 the blocks are those of -shift to 1e-20, and
+    their diagonal shows it to a rounding (half a unit in the last place of the
+    reciprocal, 1.1e-16)."""
+    Re, dt, c = 1e30, 2.0 ** -7, 0.5
+    s = make_solver(N=24, M=4, K=4, mp=1, alpha=1.25, Re=Re, dt=dt, c=c)
+    nt, shift = tiles(24), Re / c / dt
+    first = [-np.eye(4) / shift] * nt + [np.diag([-1.0 / shift] * 7 + [1.0])]
+    img = images(s, first, 1, nt)[0]
+    for got, ref in zip(stored(img, nt), first):
+        assert np.max(np.abs(np.diag(got) / np.diag(ref) - 1.0)) <= 1.2e-16 * 2

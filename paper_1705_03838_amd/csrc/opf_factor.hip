@@ -20,115 +20,238 @@ __device__ inline double wave_max(double v) {
     return v;
 }
 
-// LDS of one block elimination, entry [r][c] of a block at 8 r + c.
-struct BlockLds {
-    dd d[64], inv[64], gc[64];
-    double x[64];
+// The radial operators, by number: q < MU K is H_{mu,|k|} with mu = q / K,
+// |k| = q % K; q >= MU K is the pressure operator L_{m,|k|}, m = mp (q - MU K)
+// / K, with P(1) = 0.  The pressure's (0,0) record is not used.
+struct System {
+    bool helm;
+    int mu, ka;
+    size_t image;  // its place among the images: [|k|][mu] (Helmholtz), then [|k|][m] (pressure)
+    __device__ System(const FactorArgs& a, int q) {
+        helm = q < a.MU * a.K;
+        const int i = helm ? q : q - a.MU * a.K, row = i / a.K;
+        ka = i - row * a.K;
+        mu = helm ? row : a.mp * row;
+        image = helm ? (size_t)ka * a.MU + row : (size_t)a.MU * a.K + (size_t)ka * a.M + row;
+    }
+    __device__ bool unused() const { return !helm && mu == 0 && ka == 0; }
 };
 
-// Inverse of the n x n matrix (n = 4 or 8) in w.d, entry [r][c] returned in
-// lane 8 r + c as a pair: Gauss-Jordan elimination in double precision (the
-// pivots are those of the operator's LU factors, which the caller checks), then
-// one Newton step X + X (I - D X) with the residual in pairs.  Called by all
-// 64 lanes of one wave; bad is set where a pivot is zero or not finite.
-__device__ dd small_inverse(BlockLds& w, int n, int lane, int& bad) {
-    const int r = lane >> 3, c = lane & 7;
-    double m = w.d[lane].hi, v = r == c ? 1.0 : 0.0;
-    for (int q = 0; q < n; ++q) {
-        const double piv = __shfl(m, 9 * q), f = __shfl(m, 8 * r + q);
-        if (!(fabs(piv) > 0.0) || isinf(piv)) bad = bad ? bad : 2;
-        const double ip = 1.0 / piv, rm = __shfl(m, 8 * q + c) * ip, rv = __shfl(v, 8 * q + c) * ip;
-        m = r == q ? rm : m - f * rm;
-        v = r == q ? rv : v - f * rv;
-    }
-    w.x[lane] = v;
-    __builtin_amdgcn_wave_barrier();
-    dd e = {r == c ? 1.0 : 0.0, 0.0};
-    for (int k = 0; k < n; ++k) e = madd(e, w.d[8 * r + k], -w.x[8 * k + c]);
-    __builtin_amdgcn_wave_barrier();
-    w.gc[lane] = e;
-    __builtin_amdgcn_wave_barrier();
-    double s = 0.0;
-    for (int k = 0; k < n; ++k) s += w.x[8 * r + k] * w.gc[8 * k + c].hi;
-    __builtin_amdgcn_wave_barrier();
-    return two_sum(v, s);
+// LDS of the block elimination of four systems.  A wave holds 4 x 4 blocks of
+// four systems, entry [r][c] of system s in lane 16 s + 4 r + c, or an 8 x 8
+// block of one, entry [r][c] in lane 8 r + c; two of those at a time.
+struct BlockLds {
+    dd d[128], inv[64];
+    union {
+        double x[128];
+        dd gc[64];
+    };
+};
+
+template <int q>
+__device__ inline double quad_broadcast(double v) {  // lane q of each four
+    const long long u = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)u, 0x55 * q, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), 0x55 * q, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// The image of the operator L - shift whose band rows (of L; the wall row is
-// the identity's) are in T, offsets -8..+4: the block elimination described
-// at btd_nt.  It runs on pairs of doubles, so that the inverse blocks are
-// right to a unit in the last place (1.2e-15 of a block's largest entry, of
-// which their entries' own rounding; 5e-15 in plain double): their errors act
-// on every step in the same way.  100 diffusion steps of u_theta(0,0) at N =
-// 64 stay within 0.8e-14 of the same steps in extended precision (banded LU
-// factors: 3.5e-14).  Called by all 64 lanes of one wave.
-__device__ void block_image(const FactorArgs& a, const double* T, double shift, double* G, BlockLds& w, int lane, int& bad) {
-    const int N = a.N, nt = a.nt, pad = btd_rows(nt) - N, r = lane >> 3, c = lane & 7;
-    auto at = [&](int row, int col) {  // padded row and column; padding rows are rows of the identity
-        const int n = row - pad, k = col - pad;
-        if (n < 0 || k < 0) return row == col ? 1.0 : 0.0;
-        const int off = k - n;
-        return n < N && k < N && off >= -8 && off <= 4 ? T[n * BW + off + 8] : 0.0;
+// Step q of Gauss-Jordan elimination in place: m becomes the inverse after all.
+template <int n, int q, int T>
+__device__ inline void eliminate(double (&m)[T], int (&bad)[T], int base, int r, int c) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const double row = __shfl(m[t], base + n * q + c);
+        double f, piv;  // column q of this row, the pivot
+        if constexpr (n == 4) f = quad_broadcast<q>(m[t]), piv = quad_broadcast<q>(row);
+        else f = __shfl(m[t], base + n * r + q), piv = __shfl(m[t], base + (n + 1) * q);
+        if (!(fabs(piv) > 0.0) || isinf(piv)) bad[t] = 2;
+        double ip = __builtin_amdgcn_rcp(piv);  // two Newton steps: to a unit in the last place
+        ip = fma(fma(-piv, ip, 1.0), ip, ip);
+        ip = fma(fma(-piv, ip, 1.0), ip, ip);
+        const double rm = c == q ? ip : row * ip;
+        m[t] = r == q ? rm : fma(-f, rm, c == q ? 0.0 : m[t]);
+    }
+    if constexpr (q + 1 < n) eliminate<n, q + 1, T>(m, bad, base, r, c);
+}
+
+// Inverses of n x n matrices, D[t] this lane's entries: Gauss-Jordan elimination
+// in double precision (the pivots are those of the operator's LU factors, which
+// are checked), then one Newton step X + X (I - D X) with the residual in
+// pairs.  T matrices per lane, whose chains run side by side.  Called by all 64
+// lanes of one wave; bad is set in the lanes of a matrix with a pivot that is
+// zero or not finite.
+template <int n, int T>
+__device__ inline void small_inverse(BlockLds& w, int lane, const dd (&D)[T], dd (&out)[T], int (&bad)[T]) {
+    const int l = lane & (n * n - 1), base = lane - l, r = l / n, c = l % n;
+    double m[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) m[t] = D[t].hi;
+    eliminate<n, 0, T>(m, bad, base, r, c);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        w.d[64 * t + lane] = D[t];
+        w.x[64 * t + lane] = m[t];
+    }
+    __builtin_amdgcn_wave_barrier();
+    double e[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        dd s = {r == c ? 1.0 : 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < n; ++k) s = madd(s, w.d[64 * t + base + n * r + k], -w.x[64 * t + base + n * k + c]);
+        e[t] = s.hi + s.lo;
+    }
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < T; ++t) w.d[64 * t + lane].hi = e[t];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) s += w.x[64 * t + base + n * r + k] * w.d[64 * t + base + n * k + c].hi;
+        out[t] = two_sum(m[t], s);
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
+// The images of systems q0..q0+3 (those past the last one repeat it): the
+// block elimination described at btd_nt, of L - shift with the couplings of
+// the table wl, as the solve uses them, and the identity's wall row.  It runs
+// on pairs of doubles, so that the inverse blocks are right to a unit in the
+// last place (1.2e-15 of a block's largest entry, of which their entries' own
+// rounding; 5e-15 in plain double): their errors act on every step in the same
+// way.  100 diffusion steps of u_theta(0,0) at N = 64 stay within 0.8e-14 of the
+// same steps in extended precision (banded LU factors: 3.5e-14).
+//
+// Bound by the latency of one tile after the other, so four systems share a
+// wave, 16 lanes each, and their last blocks, 64 entries each, run in pairs side
+// by side.  The next tile's entries are requested a tile ahead.  The factor
+// kernel takes 53 us for the 3136 Helmholtz operators of 64 x 48 x 127 modes (115
+// with a wave to each system, of which 4 x 4 blocks use a quarter) and 29 us for
+// the 1600 of 48 x 24 x 63 (46).  Called by all 64 lanes of one wave.
+__device__ void block_images(const FactorArgs& a, int q0, int nsys, BlockLds& w, int lane) {
+    const int N = a.N, nt = a.nt, pad = btd_rows(nt) - N;
+    // Entry of L at a padded row and column, but for the diagonal terms; padding
+    // rows and the wall row are the identity's.  No select follows the loads, so
+    // that they need no branch and no early wait.
+    const int none = 2 * N * W9;  // 0, then 1
+    auto at = [&](const System& S, int row, int col) {
+        const int n = row - pad, off = col - pad - stencil_column(n, N);
+        const bool in = n >= 0 && n < N - 1 && off >= 0 && off < W9;
+        return a.wl[in ? ((S.mu & 1) * N + n) * W9 + off : none + (row == col && (n < 0 || n >= N - 1))];
+    };
+    auto rinv_at = [&](int row) { return a.rinv[min(max(row - pad, 0), N - 1)]; };
+    // v = at(row, col) of a diagonal block, with - mu^2 / r^2 - |k|^2 - shift
+    auto diagonal = [&](const System& S, int row, int col, double v, double ri) {
+        const double on = row == col && row >= pad && row < pad + N - 1 ? 1.0 : 0.0, kap = a.alpha * S.ka;
+        return two_sum(v - on * (double(S.mu) * S.mu * ri * ri + kap * kap), S.helm ? -on * a.shift : 0.0);
     };
     auto at_image = [](int tile, int i, int k) { return 32 * (tile >> 1) + 2 * (4 * k + i) + (tile & 1); };
-    for (int I = 0; I <= nt; ++I) {
-        const int n = I < nt ? 4 : 8, r0 = 4 * I;
-        dd d = {r < n && c < n ? at(r0 + r, r0 + c) : (r == c ? 1.0 : 0.0), 0.0};
-        if (r == c && r < n && r0 + r >= pad && r0 + r < pad + N - 1) d = two_sum(d.hi, -shift);
-        if (I > 0) {
-            // D_{I-1}^{-1} C_{I-1}; C reaches the first four columns of block I only
-            dd s = {0.0, 0.0};
-            if (r < 4 && c < 4)
-                for (int k = 0; k < 4; ++k) s = madd(s, w.inv[8 * r + k], at(r0 - 4 + k, r0 + c));
-            w.gc[lane] = s;
+    int bad = 0;
+    {
+        const int g = lane & 48, r = (lane >> 2) & 3, c = lane & 3;
+        const System S(a, min(q0 + (lane >> 4), nsys - 1));
+        double* G = a.img + S.image * btd_image(nt);
+        double v0, ri, b[4], u[4];  // the tile's entry and 1 / r, row r of B and column c of the C before it
+        auto request = [&](int I) {
+            v0 = at(S, 4 * I + r, 4 * I + c);
+            ri = rinv_at(4 * I + r);
+            const int J = max(I, 1);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                b[k] = at(S, 4 * J + r, 4 * J - 4 + k);
+                u[k] = at(S, 4 * J - 4 + k, 4 * J + c);
+            }
+        };
+        request(0);
+        for (int I = 0; I < nt; ++I) {
+            dd d = diagonal(S, 4 * I + r, 4 * I + c, v0, ri), s = {0.0, 0.0};  // s: D_{I-1}^{-1} C_{I-1}
+            if (I > 0) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s = madd(s, w.inv[g + 4 * r + k], u[k]);
+                w.gc[lane] = s;
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int k = 0; k < 4; ++k) d = madd(d, w.gc[g + 4 * k + c], -b[k]);
+                __builtin_amdgcn_wave_barrier();
+            }
+            request(min(I + 1, nt - 1));
+            const dd D[1] = {two_sum(d.hi, d.lo)};
+            dd v[1];
+            int wrong[1] = {bad};
+            small_inverse<4, 1>(w, lane, D, v, wrong);
+            bad = wrong[0];
+            w.inv[lane] = v[0];
             __builtin_amdgcn_wave_barrier();
-            if (r < n && c < 4)
-                for (int k = 0; k < 4; ++k) d = madd(d, w.gc[8 * k + c], -at(r0 + r, r0 - 4 + k));
-            __builtin_amdgcn_wave_barrier();
+            G[at_image(I, r, c)] = S.unused() ? 0.0 : v[0].hi;
         }
-        w.d[lane] = d;
+    }
+    const int r = lane >> 3, c = lane & 7, r0 = 4 * nt;
+#pragma unroll 1
+    for (int h = 0; h < 4; h += 2) {
+        dd D[2], v[2];
+        int wrong[2];
+        if (r < 4 && c < 4)  // C reaches the first four columns of the last block only
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const System S(a, min(q0 + h + t, nsys - 1));
+                dd s = {0.0, 0.0};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s = madd(s, w.inv[16 * (h + t) + 4 * r + k], at(S, r0 - 4 + k, r0 + c));
+                w.gc[16 * t + 4 * r + c] = s;
+            }
         __builtin_amdgcn_wave_barrier();
-        const dd v = small_inverse(w, n, lane, bad);
-        w.inv[lane] = v;
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const System S(a, min(q0 + h + t, nsys - 1));
+            dd d = diagonal(S, r0 + r, r0 + c, at(S, r0 + r, r0 + c), rinv_at(r0 + r));
+            if (c < 4)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) d = madd(d, w.gc[16 * t + 4 * k + c], -at(S, r0 + r, r0 - 4 + k));
+            D[t] = two_sum(d.hi, d.lo);
+            wrong[t] = __shfl(bad, 16 * (h + t));
+        }
         __builtin_amdgcn_wave_barrier();
-        if (I < nt) {
-            if (r < 4 && c < 4) G[at_image(I, r, c)] = v.hi;
-        } else {
-            G[at_image(nt + 2 * (r >> 2) + (c >> 2), r & 3, c & 3)] = v.hi;
+        small_inverse<8, 2>(w, lane, D, v, wrong);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int q = min(q0 + h + t, nsys - 1);
+            const System S(a, q);
+            double* G = a.img + S.image * btd_image(nt);
+            G[at_image(nt + 2 * (r >> 2) + (c >> 2), r & 3, c & 3)] = S.unused() ? 0.0 : v[t].hi;
+            if (lane == 0) a.flags[a.MU * a.K + a.M * a.K + a.M * (2 * a.K - 1) + q] = S.unused() ? 0 : wrong[t];
         }
     }
 }
 
-// One system per workgroup of two waves.  System q < MU K is H_{mu,|k|} with
-// mu = q / K, |k| = q % K; q >= MU K is the pressure operator L_{m,|k|},
-// m = mp (q - MU K) / K, with P(1) = 0 (the unused (0,0) record gets
-// 1/U = 1, its image zeros).  Wave 1 makes the image; wave 0 eliminates the
-// band (rows in LDS) without pivoting, one column per pass (8 rows x 4 columns
-// of updates in parallel), and writes it as column records: main record i
-// holds L[i+1..i+4][i], U[i-1..i-4][i] and 1/U_ii, tail record i holds
-// L[i+5..i+8][i].  flags[q]: 0 ok, 1 entry outside the band, 2 pivot below
-// 1e-14 max|A|, 3 element growth (|U| > 1e3 max|A| or |L| > 1e3).
-__global__ __launch_bounds__(128) void k_factor(FactorArgs a, int first) {
-    __shared__ double B[NMAX * BW];
-    __shared__ double T[NMAX * BW];  // the band of L, as the block elimination takes it
-    __shared__ BlockLds blk;
-    __shared__ int image_bad;
-    const int q = first + blockIdx.x;
-    const int N = a.N, n = threadIdx.x & 63;
-    const bool lu = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) == 0;
-    const bool helm = q < a.MU * a.K;
-    const int mu = helm ? q / a.K : a.mp * ((q - a.MU * a.K) / a.K);
-    const int ka = helm ? q % a.K : (q - a.MU * a.K) % a.K;
+// The first (nsys + 3) / 4 workgroups make the images, four systems each
+// (status 2: a pivot that is zero or not finite); the others the LU factors,
+// one system each, which eliminate the band (rows in LDS) without pivoting,
+// one column per pass (8 rows x 4 columns of updates in parallel), and write it
+// as column records: main record i holds L[i+1..i+4][i], U[i-1..i-4][i] and
+// 1/U_ii, tail record i holds L[i+5..i+8][i] (the unused record gets 1/U = 1).
+// flags[q]: 0 ok, 1 entry outside the band, 2 pivot below 1e-14 max|A|, 3
+// element growth (|U| > 1e3 max|A| or |L| > 1e3).
+__global__ __launch_bounds__(64) void k_factor(FactorArgs a, int nsys) {
+    __shared__ union {
+        double B[NMAX * BW];
+        BlockLds blk;
+    } sm;
+    const int nimg = (nsys + 3) / 4;
+    const int N = a.N, n = threadIdx.x;
+    if ((int)blockIdx.x < nimg) {
+        block_images(a, 4 * blockIdx.x, nsys, sm.blk, n);
+        return;
+    }
+    double* const B = sm.B;
+    const int q = blockIdx.x - nimg;
+    const System S(a, q);
+    const bool helm = S.helm;
+    const int mu = S.mu, ka = S.ka;
     double* F = a.fac + (size_t)q * N * FACW;
-    // image of this operator: [|k|][mu] (Helmholtz), [|k|][m] (pressure)
-    const int FW = btd_image(a.nt);
-    const size_t iq = helm ? (size_t)ka * a.MU + mu : (size_t)a.MU * a.K + (size_t)ka * a.M + (q - a.MU * a.K) / a.K;
-    double* G = a.img + iq * FW;
-    if (!helm && mu == 0 && ka == 0) {
-        if (!lu) {
-            for (int e = n; e < FW; e += 64) G[e] = 0.0;
-            return;
-        }
+    if (S.unused()) {
         if (n < N) {
             for (int d = 0; d < FMAIN; ++d) F[(size_t)n * FMAIN + d] = d == 8 ? 1.0 : 0.0;
             for (int d = 0; d < FTAIL; ++d) F[(size_t)N * FMAIN + (size_t)n * FTAIL + d] = 0.0;
@@ -140,11 +263,10 @@ __global__ __launch_bounds__(128) void k_factor(FactorArgs a, int first) {
     const int par = mu & 1;
     int bad = 0;
     double amax = 0.0;
-    double* band = lu ? B : T;
     if (n < N) {
-        for (int d = 0; d < BW; ++d) band[n * BW + d] = 0.0;
+        for (int d = 0; d < BW; ++d) B[n * BW + d] = 0.0;
         if (n == N - 1) {
-            band[n * BW + 8] = 1.0;  // wall row: the boundary value
+            B[n * BW + 8] = 1.0;  // wall row: the boundary value
             amax = 1.0;
         } else {
             const int s = a.s0[n];
@@ -153,7 +275,7 @@ __global__ __launch_bounds__(128) void k_factor(FactorArgs a, int first) {
                 const int col = s + j;
                 double v = a.d2[(par * N + n) * W9 + j] + ri * a.d1[(par * N + n) * W9 + j];
                 if (col == n) v -= double(mu) * mu * ri * ri + kap * kap;
-                if (helm && lu) {
+                if (helm) {
                     v = -a.cr * v;
                     if (col == n) v += a.inv_dt;
                 }
@@ -161,20 +283,13 @@ __global__ __launch_bounds__(128) void k_factor(FactorArgs a, int first) {
                 if (off < -8 || off > 4) {
                     if (v != 0.0) bad = 1;
                 } else {
-                    band[n * BW + off + 8] = v;
+                    B[n * BW + off + 8] = v;
                 }
                 amax = fmax(amax, fabs(v));
             }
         }
     }
     __builtin_amdgcn_wave_barrier();
-    if (!lu) {
-        block_image(a, T, helm ? a.shift : 0.0, G, blk, n, bad);
-        for (int o = 32; o > 0; o >>= 1) bad = max(bad, __shfl_xor(bad, o));
-        if (n == 0) image_bad = bad;
-        __syncthreads();
-        return;
-    }
     amax = wave_max(amax);
     // elimination: lane t updates row j+1+t/4, column j+1+t%4
     const int ti = 1 + (n & 31) / 4, tc = 1 + (n & 3);
@@ -214,8 +329,6 @@ __global__ __launch_bounds__(128) void k_factor(FactorArgs a, int first) {
     // the band check is per row: any lane's flag marks the system
     for (int o = 32; o > 0; o >>= 1) bad = max(bad, __shfl_xor(bad, o));
     if (bad == 0 && (umax > 1e3 * amax || lmax > 1e3)) bad = 3;
-    __syncthreads();
-    if (bad == 0) bad = image_bad;
     if (n == 0) a.flags[q] = bad;
 }
 
@@ -261,14 +374,35 @@ __global__ __launch_bounds__(64) void k_hom_pressure(FactorArgs a) {
     for (int i = 0; i < N; ++i) h[6 * N + i] = v[i * 64 + lane];
 }
 
+// Flux Green's function H_{0,0} u_G = 1 inside, u_G(1) = 0, and
+// qg = int_0^1 u_G r dr (lane 0).
+__device__ void green(const FactorArgs& a, double* v, int lane) {
+    if (lane != 0) return;
+    const int N = a.N;
+    for (int i = 0; i < N; ++i) v[i * 64] = i == N - 1 ? 0.0 : 1.0;
+    rec_solve(hfac(a, 0, 0), N, v, 0);
+    double s = 0.0;
+    for (int i = 0; i < N; ++i) {
+        a.green[i] = v[i * 64];
+        s += a.quad[i] * v[i * 64];
+    }
+    *a.qg = s;
+}
+
 // The six Helmholtz solves of the homogeneous solutions of pair (m, |k|):
 // slot 0 h1+ = H_{m+1}^{-1}(-(P1' - m P1/r)), slot 1 h1- = H_{m-1}^{-1}(-(P1'
 // + m P1/r)), slot 2 q = H_m^{-1} P1 (wall values 0), and slots 3..5 the unit
-// wall values through H_{m+1}, H_{m-1}, H_m.  One thread per (pair, slot).
+// wall values through H_{m+1}, H_{m-1}, H_m.  One thread per (pair, slot); the
+// first workgroup solves for the flux Green's function meanwhile (a launch of
+// its own took 23 us at 24 rows and 47 at 64, a seventh of a rebuild).
 __global__ __launch_bounds__(64) void k_hom_helmholtz(FactorArgs a) {
     __shared__ double v[NMAX * 64];
-    const int lane = threadIdx.x, id = blockIdx.x * 64 + lane;
+    const int lane = threadIdx.x, id = (blockIdx.x - 1) * 64 + lane;
     const int N = a.N;
+    if (blockIdx.x == 0) {
+        green(a, v, lane);
+        return;
+    }
     if (id >= a.M * a.K * 6) return;
     const int pr = id / 6, slot = id % 6;
     const int mi = pr / a.K, ka = pr % a.K;
@@ -380,39 +514,21 @@ __global__ __launch_bounds__(64) void k_influence(FactorArgs a) {
         }
 }
 
-// Flux Green's function H_{0,0} u_G = 1 inside, u_G(1) = 0, and
-// qg = int_0^1 u_G r dr (one thread).
-__global__ __launch_bounds__(64) void k_green(FactorArgs a, double* qg) {
-    __shared__ double v[NMAX * 64];
-    if (threadIdx.x != 0) return;
-    const int N = a.N;
-    for (int i = 0; i < N; ++i) v[i * 64] = i == N - 1 ? 0.0 : 1.0;
-    rec_solve(hfac(a, 0, 0), N, v, 0);
-    double s = 0.0;
-    for (int i = 0; i < N; ++i) {
-        a.green[i] = v[i * 64];
-        s += a.quad[i] * v[i * 64];
-    }
-    *qg = s;
-}
-
 }  // namespace
 
 hipError_t launch_operator_tables(const FactorArgs& a, bool pressure, hipStream_t s) {
-    const int nh = a.MU * a.K, np = a.M * a.K;
-    hipLaunchKernelGGL(k_factor, dim3(pressure ? nh + np : nh), dim3(128), 0, s, a, 0);
+    const int nh = a.MU * a.K, np = a.M * a.K, nsys = pressure ? nh + np : nh;
+    hipLaunchKernelGGL(k_factor, dim3((nsys + 3) / 4 + nsys), dim3(64), 0, s, a, nsys);
     hipError_t he = hipGetLastError();
     if (he != hipSuccess) return he;
     if (pressure) {
         hipLaunchKernelGGL(k_hom_pressure, dim3((np + 63) / 64), dim3(64), 0, s, a);
         if ((he = hipGetLastError()) != hipSuccess) return he;
     }
-    hipLaunchKernelGGL(k_hom_helmholtz, dim3((np * 6 + 63) / 64), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(k_hom_helmholtz, dim3((np * 6 + 63) / 64 + 1), dim3(64), 0, s, a);
     if ((he = hipGetLastError()) != hipSuccess) return he;
     const int modes = a.M * (2 * a.K - 1);
     hipLaunchKernelGGL(k_influence, dim3((modes + 63) / 64), dim3(64), 0, s, a);
-    if ((he = hipGetLastError()) != hipSuccess) return he;
-    hipLaunchKernelGGL(k_green, dim3(1), dim3(64), 0, s, a, a.qg);
     return hipGetLastError();
 }
 

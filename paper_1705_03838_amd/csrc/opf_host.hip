@@ -170,7 +170,7 @@ void build_grid(opf_ctx* c, const double* r_nodes) {
     c->d2.assign(2 * N * W9, 0.0);
     for (int n = 0; n < N; ++n) {
         const int e0 = window_start(n, N);
-        c->s0[n] = std::max(e0, 0);
+        c->s0[n] = stencil_column(n, N);
         double x[W9], w[3][W9];
         for (int j = 0; j < W9; ++j) x[j] = ext(c->r, e0 + j);
         fornberg(c->r[n], x, W9, w);
@@ -230,7 +230,7 @@ Layout layout(const opf_params& p) {
     L.quad = take(N * 8);
     L.d1 = take(2 * N * W9 * 8);
     L.d2 = take(2 * N * W9 * 8);
-    L.wl = take(2 * N * W9 * 8);
+    L.wl = take((2 * N * W9 + 2) * 8);
     L.s0 = take(N * 4);
     L.fac = take(nfac * N * FACW * 8);
     const int nt = btd_nt((int)N);
@@ -239,7 +239,7 @@ Layout layout(const opf_params& p) {
     L.hom = take(M * K * NHOM * N * 8);
     L.ainv = take(M * nk * 16 * 16);
     L.green = take(N * 8);
-    L.flags = take((nfac + M * nk) * 4);
+    L.flags = take((2 * nfac + M * nk) * 4);
     L.qg = take(8);
     L.wall = take(3 * M * nk * 16);
     L.twz = take(3 * K * 16);
@@ -532,6 +532,7 @@ opf_status device_tables(opf_ctx* c, bool pressure) {
     a.cr = p.c / p.Re;
     a.inv_dt = 1.0 / p.dt;
     a.rinv = c->t.rinv;
+    a.wl = c->t.wl;
     a.quad = c->t.quad;
     a.d1 = c->t.d1;
     a.d2 = c->t.d2;
@@ -548,17 +549,19 @@ opf_status device_tables(opf_ctx* c, bool pressure) {
     a.qg = reinterpret_cast<double*>(c->ws + Lo.qg);
     HIPCHK(c, launch_operator_tables(a, pressure, c->stream));
     const int nh = c->MU * p.K, np = p.M * p.K, modes = p.M * c->nk;
-    std::vector<int> fl(nh + np + modes);
+    std::vector<int> fl(2 * (nh + np) + modes);
     double qg = 0.0;
     HIPCHK(c, hipMemcpyAsync(fl.data(), a.flags, fl.size() * 4, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipMemcpyAsync(&qg, a.qg, 8, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
-    for (int q = 0; q < nh + np + modes; ++q)
-        if (fl[q] != 0 && (q < nh || pressure)) {
-            c->err = q < nh ? "Helmholtz factor unstable without pivoting"
-                   : q < nh + np ? "pressure factor unstable without pivoting" : "singular influence matrix";
+    for (int q = 0; q < (int)fl.size(); ++q) {
+        const int i = q < nh + np + modes ? q : q - (nh + np + modes);  // images: as their operators
+        if (fl[q] != 0 && (i < nh || pressure)) {
+            c->err = i < nh ? "Helmholtz factor unstable without pivoting"
+                   : i < nh + np ? "pressure factor unstable without pivoting" : "singular influence matrix";
             return OPF_E_NUMERIC;
         }
+    }
     if (!(std::isfinite(qg) && qg != 0.0)) {
         c->err = "flux Green's function has no flux";
         return OPF_E_NUMERIC;
@@ -785,7 +788,8 @@ opf_status opf_create(const opf_params* p, void* dev_workspace, size_t bytes, vo
     if (he == hipSuccess) he = up(Lo.d2, c->d2.data(), c->d2.size() * 8);
     if (he == hipSuccess) he = up(Lo.s0, c->s0.data(), N * 4);
     // folded weights of d2/dr2 + (1/r) d/dr (the radial part of L), per parity
-    std::vector<double> wl(2 * N * W9);
+    std::vector<double> wl(2 * N * W9 + 2, 0.0);
+    wl.back() = 1.0;
     for (int par = 0; par < 2; ++par)
         for (int n = 0; n < N; ++n)
             for (int j = 0; j < W9; ++j) {

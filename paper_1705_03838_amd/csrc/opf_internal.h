@@ -52,6 +52,11 @@ __host__ __device__ constexpr int btd_coupling(int nt) { return 16 * (2 * nt + 9
 static_assert(btd_nt(12) == 2 && btd_nt(16) == 2 && btd_nt(17) == 4 && btd_nt(64) == 14, "tiles before the last block");
 static_assert(btd_rows(btd_nt(64)) == 64 && btd_rows(btd_nt(12)) == 16, "padded rows");
 constexpr int NMAX = 64;  // radial points handled by one solve workgroup
+// First column of row n's 9-point window: centred, clamped at the wall, folded at the axis.
+__host__ __device__ constexpr int stencil_column(int n, int N) {
+    const int e = n - 4 < N - 9 ? n - 4 : N - 9;
+    return e < 0 ? 0 : e;
+}
 
 // Complex number used by the kernels (interleaved re/im, same layout as
 // complex128 / complex64 in memory).  Aligned to its full size so that one
@@ -73,7 +78,7 @@ struct Tables {
     const double* fac;    // [nfac] banded LU factors of N FACW doubles (main then tail records)
     const double* img;    // inverse diagonal blocks: [K][MU] Helmholtz, then [K][M] pressure (btd_image doubles each)
     const double* coup;   // coupling tiles (btd_coupling doubles)
-    const double* wl;     // [2][N][9] folded weights of d2/dr2 + (1/r) d/dr, parity 0 even / 1 odd
+    const double* wl;     // [2][N][9] folded weights of d2/dr2 + (1/r) d/dr, parity 0 even / 1 odd; then 0, 1
     const double* hom;    // [M][K][NHOM][N] influence data (h1+, h1-, q, h2, h3, h4, P1)
     const double* ainv;   // [M][2K-1][16][2] inverse influence matrices (complex)
     const double* green;  // [N] flux Green's function: H_0 u_G = 1, u_G(1) = 0
@@ -137,6 +142,7 @@ struct FactorArgs {
     double inv_dt;      // 1 / dt
     double shift;       // Re / (c dt), consistent with SolveArgs::hscale
     const double* rinv;
+    const double* wl;   // Tables::wl
     const double* quad;
     const double* d1;
     const double* d2;
@@ -147,7 +153,7 @@ struct FactorArgs {
     double* hom;        // [M][K][NHOM][N]
     double* ainv;       // [M][2K-1][16][2]
     double* green;      // [N]
-    int* flags;         // [MU K + M K] factor status, then [M (2K-1)] influence status
+    int* flags;         // [MU K + M K] factor status, [M (2K-1)] influence status, [MU K + M K] image status
     double* qg;         // int_0^1 u_G r dr (device scalar)
 };
 // Factor the Helmholtz operators (and, with pressure, the pressure

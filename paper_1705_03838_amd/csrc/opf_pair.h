@@ -19,22 +19,13 @@ __host__ __device__ inline dd two_sum(double a, double b) {
     const double s = a + b, t = s - a;
     return {s, (a - (s - t)) + (b - t)};
 }
-__host__ __device__ inline dd renorm(double a, double b) {  // |a| >= |b|
-#pragma clang fp contract(off)
-    const double s = a + b;
-    return {s, b - (s - a)};
-}
-__host__ __device__ inline dd operator+(dd a, dd b) {
-#pragma clang fp contract(off)
-    const dd s = two_sum(a.hi, b.hi), t = two_sum(a.lo, b.lo);
-    const dd u = renorm(s.hi, s.lo + t.hi);
-    return renorm(u.hi, u.lo + t.lo);
-}
-__host__ __device__ inline dd operator*(dd a, double b) {
+// s + a b, not renormalised: the low part takes the errors of the product and
+// of the sum, so that a chain of these waits for one addition each.
+__host__ __device__ inline dd madd(dd s, dd a, double b) {
 #pragma clang fp contract(off)
     const double p = a.hi * b;
-    return renorm(p, fma(a.hi, b, -p) + a.lo * b);
+    const dd t = two_sum(s.hi, p);
+    return {t.hi, t.lo + (s.lo + fma(a.lo, b, fma(a.hi, b, -p)))};
 }
-__host__ __device__ inline dd madd(dd s, dd a, double b) { return s + a * b; }  // s + a b
 
 }  // namespace opf

@@ -1,6 +1,6 @@
 """Pair arithmetic of the operator tables: compiled for the host, against exact
 rationals; compiled for the device with the library's flags, the operations of
-one product, none of them contracted.
+one sum and product, none of them contracted.
 
 Tolerance: s + a b on pairs of 53-bit numbers loses a few units of 2^-106 of
 its largest term; 2^-100 of |s| + |a b| leaves room for eight of the
@@ -58,7 +58,7 @@ def test_sum_and_product_of_pairs(tmp_path):
 
 KERNEL = """
 #include "opf_pair.h"
-extern "C" __global__ void product(const opf::dd* a, const double* b, opf::dd* out) { *out = *a * *b; }
+extern "C" __global__ void product(const opf::dd* a, const double* b, opf::dd* out) { *out = madd(*out, *a, *b); }
 """
 
 
@@ -71,5 +71,5 @@ def test_device_product_is_not_contracted(tmp_path):
     subprocess.run([HIPCC, *flags, "-w", "--cuda-device-only", "-S", "-I", CSRC, str(src), "-o", str(out)], check=True,
                    timeout=300)
     ops = re.findall(r"^\s+v_(mul|fma|fmac|add)_f64", out.read_text(), re.M)
-    # a_hi b and a_lo b; the first product's error; their sum and the three sums of the renormalisation
-    assert (ops.count("mul"), ops.count("fma") + ops.count("fmac"), ops.count("add")) == (2, 1, 4), ops
+    # a_hi b; its error and a_lo b to it; the sum with its error (six) and the low parts (two)
+    assert (ops.count("mul"), ops.count("fma") + ops.count("fmac"), ops.count("add")) == (1, 2, 8), ops

@@ -585,9 +585,9 @@ opf_status opf_ensemble_workspace_size(const opf_params* members, int32_t count,
 
 /* Tile shapes of one class of equal (N, M, K, mp, precision): gm consecutive
  * m per radial-solve workgroup (1, 2 or 4 with mp (gm - 1) + 3 <= 6), tz
- * axial points per theta-stage workgroup (2, 4 or 8; 16 instead where
- * N ceil(3K/16) reaches 144 in FP64, unless 3M = 192, and 192 (3M >= 72) or
- * 256 in mixed precision) and ztile radial lines per z-transform workgroup (4, 8 or 16), each while the longer radix pass
+ * axial points per theta-stage workgroup (2, 4 or 8; grids that fill the chip
+ * take 16 instead, and the tuner leaves their tz alone) and ztile radial lines
+ * per z-transform workgroup (4, 8 or 16), each while the longer radix pass
  * of the transform length fits the workgroup (tz r <= 64; ztile r <= 256,
  * with 256-thread z workgroups when ztile r > 128; r the larger radix of the
  * length's two-pass split: 16 for 192, 12 for 144 ... 3 for 6).  Results

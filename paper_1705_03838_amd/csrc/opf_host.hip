@@ -2922,10 +2922,12 @@ opf_status opf_ensemble_tune(opf_ensemble* e, int32_t nsteps, char* report, size
             cand += buf;
             return OPF_OK;
         };
-        // one tile dimension at a time, each from the best of the previous
+        // one tile dimension at a time, each from the best of the previous; tz
+        // stays where the theta stage does not use it
         double best = 1e300;
         const int gms[] = {1, 2, 4}, tzs[] = {2, 4, 8}, zts[] = {4, 8, 16};
         for (int dim = 0; dim < 3; ++dim) {
+            if (dim == 1 && theta_wide(k.N, k.M, k.K, k.precision == OPF_MIXED)) continue;
             const int* vals = dim == 0 ? gms : dim == 1 ? tzs : zts;
             int* knob = dim == 0 ? &k.gm : dim == 1 ? &k.tz : &k.ztile;
             const int keep = *knob;

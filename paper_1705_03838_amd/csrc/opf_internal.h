@@ -184,6 +184,7 @@ bool nonlinear_supported(int M, int K);
 // workgroup, zt in {4, 8, 16} radial lines per z workgroup, each while the
 // longer radix pass fits the workgroup.
 bool tz_ok(int tz, int M);
+bool theta_wide(int N, int M, int K, bool fp32);  // the theta stage takes 16 axial points whatever tz is
 bool ztile_ok(int zt, int K);
 constexpr int DEFAULT_TZ = 4, DEFAULT_ZTILE = 8;
 // Radial lines per z workgroup before any tuning: 16 with FP32 transforms

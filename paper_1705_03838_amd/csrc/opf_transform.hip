@@ -907,6 +907,24 @@ static int radix_of(int L) {
 bool ztile_ok(int zt, int K) { return (zt == 4 || zt == 8 || zt == 16) && radix_of(3 * K) * zt <= 256; }
 bool tz_ok(int tz, int M) { return (tz == 2 || tz == 4 || tz == 8) && radix_of(3 * M) * tz <= 64; }
 
+// Which grids the wide theta kernel takes, by its workgroups N ceil(3K / 16):
+// with few of them the three lines side by side in k_theta_lp finish sooner.
+// FP64 from 144 on (us, lp / wide): 41 x 54 x 36 points, 123: 5.4 / 6.0; 20 x
+// 144 x 96, 120: 8.5 / 10.0; 24 x 72 x 96, 144: 7.9 / 7.0; 48 x 48 x 48, 144: 5.9 /
+// 5.7; 31 x 96 x 96, 186: 9.2 / 7.7; 33 x 144 x 96, 198: 11.5 / 10.1.  FP32 needs
+// fewer registers in k_theta_lp and more workgroups here: lines of 72 and more
+// from 192 on (160: 6.6 / 6.7; 36 x 72 x 96, 216: 6.5 / 6.15; 24 x 144 x 144, 216: 8.4
+// / 7.6), shorter ones from 256 on (64 x 48 x 48, 192: 4.8 / 5.2; 40 x 36 x 96,
+// 240: 4.5 / 4.6; 64 x 54 x 108, 448: 7.9 / 6.5).  Lines of 192 in FP64 need more
+// registers than two waves per SIMD have (64 x 192 x 192: 36 / 65; 52 with tiles
+// of 8 points).  The rule looks at one member's grid only: the members of a
+// batch and single runs take one path.
+static int theta_w_blocks(int N, int K) { return N * ((3 * K + TZW - 1) / TZW); }
+bool theta_wide(int N, int M, int K, bool fp32) {
+    const int L = 3 * M;
+    return theta_w_blocks(N, K) >= (fp32 ? (L >= 72 ? 192 : 256) : 144) && (fp32 || L < 192);
+}
+
 template <typename TS, typename T, int L, int ZT>
 static void launch_z(const NLArgs& a, const NLArgs* batch, int members, bool inv, hipStream_t s, const KernelTiming& kt) {
     const int ntile = (a.N + ZT - 1) / ZT;
@@ -935,24 +953,11 @@ static void launch_theta(const NLArgs& a, const NLArgs* batch, int members, hipS
     }
 }
 
-// Which grids the wide theta kernel takes, by its workgroups N ceil(3K / 16):
-// with few of them the three lines side by side in k_theta_lp finish sooner.
-// FP64 from 144 on (us, lp / wide): 41 x 54 x 36 points, 123: 5.4 / 6.0; 20 x
-// 144 x 96, 120: 8.5 / 10.0; 24 x 72 x 96, 144: 7.9 / 7.0; 48 x 48 x 48, 144: 5.9 /
-// 5.7; 31 x 96 x 96, 186: 9.2 / 7.7; 33 x 144 x 96, 198: 11.5 / 10.1.  FP32 needs
-// fewer registers in k_theta_lp and more workgroups here: lines of 72 and more
-// from 192 on (160: 6.6 / 6.7; 36 x 72 x 96, 216: 6.5 / 6.15; 24 x 144 x 144, 216: 8.4
-// / 7.6), shorter ones from 256 on (64 x 48 x 48, 192: 4.8 / 5.2; 40 x 36 x 96,
-// 240: 4.5 / 4.6; 64 x 54 x 108, 448: 7.9 / 6.5).  Lines of 192 in FP64 need more
-// registers than two waves per SIMD have (64 x 192 x 192: 36 / 65; 52 with tiles
-// of 8 points).  The rule looks at one member's grid only: the members of a
-// batch and single runs take one path.
 template <typename T, int L>
 static bool launch_theta_wide(const NLArgs& a, const NLArgs* batch, int members, hipStream_t s, const KernelTiming& kt) {
     if constexpr (sizeof(T) == 4 || L < 192) {
-        const int blocks = a.N * ((3 * a.K + TZW - 1) / TZW);
-        if (blocks < (sizeof(T) == 8 ? 144 : L >= 72 ? 192 : 256)) return false;
-        const dim3 g(blocks, batch ? members : 1), b(theta_w_threads<L>());
+        if (!theta_wide(a.N, a.M, a.K, sizeof(T) == 4)) return false;
+        const dim3 g(theta_w_blocks(a.N, a.K), batch ? members : 1), b(theta_w_threads<L>());
         if (batch) hipLaunchKernelGGL((k_theta_w_b<T, L>), g, b, (theta_w_lds<T, L>()), s, batch);
         else if (a.rotating) launch_timed((k_theta_w<T, L, true>), g, b, (theta_w_lds<T, L>()), s, kt, a);
         else launch_timed((k_theta_w<T, L, false>), g, b, (theta_w_lds<T, L>()), s, kt, a);

@@ -840,7 +840,6 @@ opf_status opf_create(const opf_params* p, void* dev_workspace, size_t bytes, vo
     c->t.d1 = reinterpret_cast<const double*>(ws + Lo.d1);
     c->t.d2 = reinterpret_cast<const double*>(ws + Lo.d2);
     c->t.s0 = reinterpret_cast<const int*>(ws + Lo.s0);
-    c->t.fac = reinterpret_cast<const double*>(ws + Lo.fac);
     c->t.img = reinterpret_cast<const double*>(ws + Lo.img);
     c->t.coup = reinterpret_cast<const double*>(ws + Lo.coup);
     c->t.wl = reinterpret_cast<const double*>(ws + Lo.wl);

@@ -16,10 +16,10 @@ namespace opf {
 constexpr int W9 = 9;     // finite-difference stencil width (Section 2: 9 points)
 constexpr int HALF = 4;   // points on each side of a centred stencil
 constexpr int FACW = 14;  // doubles per LU factor row: 8 of L, 4 of U, 1/U_ii, pad
-// In HBM the N rows of one factor are FMAIN-double main records (L[i+1..i+4][i],
+// The N rows of one factor are FMAIN-double main records (L[i+1..i+4][i],
 // U[i-1..i-4][i], 1/U_ii, pad) followed by FTAIL-double tail records
-// (L[i+5..i+8][i]), N FACW doubles in all; in LDS a row is one FACW record
-// (L[i+1..i+8][i], U[i-1..i-4][i], 1/U_ii, pad).
+// (L[i+5..i+8][i]), N FACW doubles in all.  They make the influence data and the
+// Green's function; the substep solve uses the images.
 constexpr int FMAIN = 10;
 constexpr int FTAIL = 4;
 constexpr int NHOM = 7;   // real radial lines of influence data per (m,|k|)
@@ -75,7 +75,6 @@ struct Tables {
     const double* d1;     // [2][N][9] folded first-derivative weights, parity 0 even / 1 odd
     const double* d2;     // [2][N][9] folded second-derivative weights
     const int* s0;        // [N] first column of row n's 9-point window
-    const double* fac;    // [nfac] banded LU factors of N FACW doubles (main then tail records)
     const double* img;    // inverse diagonal blocks: [K][MU] Helmholtz, then [K][M] pressure (btd_image doubles each)
     const double* coup;   // coupling tiles (btd_coupling doubles)
     const double* wl;     // [2][N][9] folded weights of d2/dr2 + (1/r) d/dr, parity 0 even / 1 odd; then 0, 1
@@ -201,7 +200,7 @@ hipError_t launch_solve_batch(const SolveArgs& proto, const SolveArgs* dev_args,
 int default_gm(int mp);                  // of an ensemble class
 int context_gm(int mp, int M, int K);    // of a single context
 bool gm_ok(int gm, int mp);
-constexpr int NFH = 6;  // Helmholtz operators that the m of one solve workgroup may use
+constexpr int GM_SPAN = 6;  // Helmholtz operators that the m of one solve workgroup may use, see gm_ok
 hipError_t launch_vorticity(const AuxArgs& a, hipStream_t s);
 hipError_t launch_diag(const AuxArgs& a, hipStream_t s);
 // out[2M + 2N + 4]: see k_diag_pack

@@ -33,14 +33,6 @@ __device__ __forceinline__ dcplx ix(dcplx a) { return {-a.y, a.x}; }  // i * a
 
 typedef double dpair __attribute__((ext_vector_type(2)));
 
-// Row n of a 9-point stencil applied to a radial line in LDS.
-__device__ __forceinline__ dcplx stencil(const double* w, const dcplx* line, int s0) {
-    dcplx acc = {0.0, 0.0};
-#pragma unroll
-    for (int j = 0; j < W9; ++j) acc = acc + w[j] * line[s0 + j];
-    return acc;
-}
-
 template <typename T>
 __device__ __forceinline__ dcplx load_c(const void* base, size_t idx) {
     const T* p = reinterpret_cast<const T*>(base) + 2 * idx;
@@ -201,10 +193,10 @@ constexpr size_t solve_lds(int nt, int gm) {
     return (size_t)gm * 8 * solve_line(nt) * sizeof(dcplx) + btd_coupling(nt) * sizeof(double);
 }
 
-// A workgroup of GM waves handles |k| = kabs and GM consecutive m (GM = 4,
-// 2, 1 for mp = 1, 2, >= 3), which use neighbouring Helmholtz operators
-// (wavenumbers mp m - 1 .. mp m + 1); wave w handles m0 + w, modes s = 0, 1
-// at +k and -k.
+// A workgroup of GM waves handles |k| = kabs and GM consecutive m, which share
+// the coupling tiles in LDS and read neighbouring Helmholtz operators
+// (wavenumbers mp m - 1 .. mp m + 1) through one L1; wave w handles m0 + w,
+// modes s = 0, 1 at +k and -k.
 //
 // What bounds it: HBM (the spectral fields once, a third more for the tables)
 // and, on small grids, the length of one wave's phases.  Predictor / corrector
@@ -560,7 +552,10 @@ __device__ __forceinline__ void k_solve_body(const SolveArgs& a) {
     }
 }
 
-// Three waves per SIMD: at most 168 VGPRs.
+// Three waves per SIMD: at most 168 VGPRs.  The two largest forms do not quite
+// fit: NT = 12 (49 <= N <= 56) spills 2 registers, 12 bytes of scratch a lane, and
+// NT = 14 (N >= 57) 5, 24 bytes: 4.7 MB written and read again at 64 x 48 x 127
+// modes.
 template <typename TNL, int NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_solve(SolveArgs a) {
     k_solve_body<TNL, NT>(a);
@@ -725,6 +720,10 @@ __global__ __launch_bounds__(1024) void k_diag_pack(AuxArgs a, const double* __r
     if (t == 3) out[2 * M + 2 * N + 3] = *beta;
 }
 
+// The largest gm admitted, by gm_ok.  Ensembles step within 2% with any (us per
+// step of 24 members, gm 1 / 2 / 4: 48 x 24 x 63 modes 709 / 704 / 708 at mp = 1,
+// 715 / 704 at mp = 2, 720 / 716 at mp = 3; 64 x 32 x 95 1851 / 1833 / 1839, 1819
+// / 1799, 1834 / 1822).
 int default_gm(int mp) { return mp == 1 ? 4 : (mp <= 3 ? 2 : 1); }
 
 // A grid of at most one wave per compute unit is spread over all of them (24 x
@@ -733,7 +732,10 @@ int default_gm(int mp) { return mp == 1 ? 4 : (mp <= 3 ? 2 : 1); }
 // (48 x 32 x 63 modes, 1024 waves: 10.6 us against 11.5).
 int context_gm(int mp, int M, int K) { return M * K <= 256 ? 1 : default_gm(mp); }
 
-bool gm_ok(int gm, int mp) { return gm >= 1 && gm <= 4 && mp * (gm - 1) + 3 <= NFH; }
+// The admitted gm are part of the interface: tile caches are checked by them.
+// The kernel itself takes any up to its 256 threads; the span of wavenumbers that
+// the m of a workgroup use is kept to GM_SPAN.
+bool gm_ok(int gm, int mp) { return gm >= 1 && gm <= 4 && mp * (gm - 1) + 3 <= GM_SPAN; }
 
 template <int NT>
 static void launch_solve_nt(const SolveArgs& a, const SolveArgs* batch, int members, int precision, hipStream_t s,

@@ -907,22 +907,31 @@ static int radix_of(int L) {
 bool ztile_ok(int zt, int K) { return (zt == 4 || zt == 8 || zt == 16) && radix_of(3 * K) * zt <= 256; }
 bool tz_ok(int tz, int M) { return (tz == 2 || tz == 4 || tz == 8) && radix_of(3 * M) * tz <= 64; }
 
-// Which grids the wide theta kernel takes, by its workgroups N ceil(3K / 16):
-// with few of them the three lines side by side in k_theta_lp finish sooner.
-// FP64 from 144 on (us, lp / wide): 41 x 54 x 36 points, 123: 5.4 / 6.0; 20 x
-// 144 x 96, 120: 8.5 / 10.0; 24 x 72 x 96, 144: 7.9 / 7.0; 48 x 48 x 48, 144: 5.9 /
-// 5.7; 31 x 96 x 96, 186: 9.2 / 7.7; 33 x 144 x 96, 198: 11.5 / 10.1.  FP32 needs
-// fewer registers in k_theta_lp and more workgroups here: lines of 72 and more
-// from 192 on (160: 6.6 / 6.7; 36 x 72 x 96, 216: 6.5 / 6.15; 24 x 144 x 144, 216: 8.4
-// / 7.6), shorter ones from 256 on (64 x 48 x 48, 192: 4.8 / 5.2; 40 x 36 x 96,
-// 240: 4.5 / 4.6; 64 x 54 x 108, 448: 7.9 / 6.5).  Lines of 192 in FP64 need more
-// registers than two waves per SIMD have (64 x 192 x 192: 36 / 65; 52 with tiles
-// of 8 points).  The rule looks at one member's grid only: the members of a
-// batch and single runs take one path.
+// Which grids the wide theta kernel takes, by their axial points in tiles of 16
+// (N 3K / 16, not rounded up: a ragged last tile costs it a whole one and
+// k_theta_lp a quarter): with few of them the three lines side by side in
+// k_theta_lp finish sooner.  Medians of three runs, us, lp / wide:
+// FP64 from 128 on: 48 x 108 x 36 points (108 tiles) 8.3 / 8.8, 44 x 108 x 48 (132)
+// 9.5 / 8.6; 52 x 54 x 36 (117) 5.7 / 6.5, 44 x 48 x 48 (132) 5.7 / 5.6.
+// Lines of 144, whose workgroups take half a compute unit's LDS, from 196 on (24 x
+// 144 x 96, 144: 9.7 / 10.5; 32 x 144 x 96, 192: 10.2 / 10.7), and not where they
+// begin a second or a third workgroup per compute unit: 44 x 144 x 96 (264) 12.8 /
+// 14.0, 52 x 144 x 96 (312) 13.2 / 14.1, 64 x 144 x 144 (576) 20.3 / 21.2, against 56 x
+// 144 x 96 (336) 15.0 / 14.0 and 64 x 144 x 192 (768) 26.0 / 23.6.
+// FP32 needs fewer registers in k_theta_lp and more tiles here: lines of 72 and
+// more from 196 on (64 x 72 x 48, 192: 6.0 / 6.3; 36 x 72 x 96, 216: 6.5 / 6.15),
+// shorter ones from 260 on (64 x 36 x 54, 216: 4.7 / 4.8; 56 x 48 x 72, 252: 5.45 /
+// 5.9; 64 x 54 x 108, 432: 7.9 / 6.5).  Lines of 192 in FP64 need more registers
+// than two waves per SIMD have (64 x 192 x 192: 36 / 65; 52 with tiles of 8 points).
+// The rule looks at one member's grid only: the members of a batch and single
+// runs take one path.
 static int theta_w_blocks(int N, int K) { return N * ((3 * K + TZW - 1) / TZW); }
 bool theta_wide(int N, int M, int K, bool fp32) {
-    const int L = 3 * M;
-    return theta_w_blocks(N, K) >= (fp32 ? (L >= 72 ? 192 : 256) : 144) && (fp32 || L < 192);
+    const int L = 3 * M, tiles = N * 3 * K / 16;
+    if (fp32) return tiles >= (L >= 72 ? 196 : 260);
+    if (L != 144) return L < 144 && tiles >= 128;
+    const int blocks = theta_w_blocks(N, K);
+    return tiles >= (blocks > 512 ? 600 : blocks > 256 ? 324 : 196);
 }
 
 template <typename TS, typename T, int L, int ZT>

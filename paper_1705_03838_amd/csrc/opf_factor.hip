@@ -120,7 +120,7 @@ __device__ inline void small_inverse(BlockLds& w, int lane, const dd (&D)[T], dd
 // block elimination described at btd_nt, of L - shift with the couplings of
 // the table wl, as the solve uses them, and the identity's wall row.  It runs
 // on pairs of doubles, so that the inverse blocks are right to a unit in the
-// last place (1.2e-15 of a block's largest entry, of which their entries' own
+// last place (0.8e-15 of a block's largest entry with the diagonal entries' own
 // rounding; 5e-15 in plain double): their errors act on every step in the same
 // way.  100 diffusion steps of u_theta(0,0) at N = 64 stay within 0.8e-14 of the
 // same steps in extended precision (banded LU factors: 3.5e-14).

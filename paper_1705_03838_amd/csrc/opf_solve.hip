@@ -720,11 +720,10 @@ __global__ __launch_bounds__(1024) void k_diag_pack(AuxArgs a, const double* __r
     if (t == 3) out[2 * M + 2 * N + 3] = *beta;
 }
 
-// The largest gm admitted, by gm_ok.  Ensembles step within 2% with any (4% at 32 x
-// 16 x 47 modes, mixed: 249 / 257 / 260; us per
-// step of 24 members, gm 1 / 2 / 4: 48 x 24 x 63 modes 709 / 704 / 708 at mp = 1,
-// 715 / 704 at mp = 2, 720 / 716 at mp = 3; 64 x 32 x 95 1851 / 1833 / 1839, 1819
-// / 1799, 1834 / 1822).
+// The largest gm admitted, by gm_ok.  Ensembles step within 2% with any, small
+// members within 4% (us per step, gm 1 / 2 / 4; 24 members of 48 x 24 x 63 modes 709 /
+// 704 / 708 at mp = 1, 715 / 704 at mp = 2, 720 / 716 at mp = 3; of 64 x 32 x 95 1851 /
+// 1833 / 1839, 1819 / 1799, 1834 / 1822; 32 of 32 x 16 x 47, mixed, 249 / 257 / 260).
 int default_gm(int mp) { return mp == 1 ? 4 : (mp <= 3 ? 2 : 1); }
 
 // A grid of at most one wave per compute unit is spread over all of them (24 x

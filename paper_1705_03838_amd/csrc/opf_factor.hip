@@ -221,13 +221,13 @@ __device__ void block_images(const FactorArgs& a, int q0, int nsys, BlockLds& w,
             const System S(a, q);
             double* G = a.img + S.image * btd_image(nt);
             G[at_image(nt + 2 * (r >> 2) + (c >> 2), r & 3, c & 3)] = S.unused() ? 0.0 : v[t].hi;
-            if (lane == 0) a.flags[a.MU * a.K + a.M * a.K + a.M * (2 * a.K - 1) + q] = S.unused() ? 0 : wrong[t];
+            if (lane == 0) a.image_flags[q] = S.unused() ? 0 : wrong[t];
         }
     }
 }
 
 // The first (nsys + 3) / 4 workgroups make the images, four systems each
-// (status 2: a pivot that is zero or not finite); the others the LU factors,
+// (image_flags[q] 2: a pivot that is zero or not finite); the others the LU factors,
 // one system each, which eliminate the band (rows in LDS) without pivoting,
 // one column per pass (8 rows x 4 columns of updates in parallel), and write it
 // as column records: main record i holds L[i+1..i+4][i], U[i-1..i-4][i] and

@@ -152,7 +152,8 @@ struct FactorArgs {
     double* hom;        // [M][K][NHOM][N]
     double* ainv;       // [M][2K-1][16][2]
     double* green;      // [N]
-    int* flags;         // [MU K + M K] factor status, [M (2K-1)] influence status, [MU K + M K] image status
+    int* flags;         // [MU K + M K] factor status, then [M (2K-1)] influence status
+    int* image_flags;   // [MU K + M K] image status
     double* qg;         // int_0^1 u_G r dr (device scalar)
 };
 // Factor the Helmholtz operators (and, with pressure, the pressure
